@@ -166,8 +166,10 @@ LIBRARY_MATCHES = True
 
 def kernel_source_hash() -> str:
     import hashlib
-    src = os.path.join(ROOT, "paper_2609_19190_amd", "csrc", "map_kernel.hip")
-    return hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for f in ("map_body.h", "map_device.h", "map_kernel.hip"):
+        h.update(open(os.path.join(ROOT, "paper_2609_19190_amd", "csrc", f), "rb").read())
+    return h.hexdigest()[:16]
 
 
 def measured_traffic(workload_name: str):

@@ -78,8 +78,8 @@ enum {
   FR_ALL = 0x3Fu           /* 93 maps */
 };
 
-/* Largest kernel radius fr_map accepts (cube side 2r+1 <= 11); radii up to
- * 3 run on the fused fixed-radius kernels, 4 and 5 on the generic kernel. */
+/* Largest kernel radius fr_map accepts (cube side 2r+1 <= 11); every
+ * radius runs on a fused fixed-radius kernel. */
 #define FR_MAX_RADIUS 5
 /* Gray levels (Ng and the levels present in one neighbourhood) go up to 255. */
 #define FR_MAX_LEVELS 255
@@ -182,9 +182,8 @@ const char* fr_map_name(uint32_t families, int32_t k);
  * fr_discretise, into library scratch) check the mask count and Ng on the
  * device; the map kernels follow (a 32-level instance over every voxel,
  * then a 64-level one and a generic kernel for the neighbourhoods holding
- * more present levels, when Ng allows it; radii 4 and 5 use the generic
- * kernel alone), writing one 384-byte staging row per voxel, and a tile
- * transpose writes out_maps.  The library scratch is per device and grows
+ * more present levels, when Ng allows it), writing one 384-byte staging row
+ * per voxel, and a tile transpose writes out_maps.  The library scratch is per device and grows
  * (after waiting for the device) when a larger job arrives: calls on one
  * device are issued on one stream, or they race on it.  Errors returned:
  * FR_E_ARG, FR_E_EMPTY_MASK
@@ -199,8 +198,8 @@ fr_status fr_map(const void* volume, int32_t dtype, int32_t nx, int32_t ny, int3
 
 /*
  * fr_map_ex -- fr_map with the IBSI extraction settings of fr_map_options
- * (NULL = the defaults, i.e. fr_map).  Non-default settings run on the
- * generic kernel.  Errors: those of fr_map, FR_E_RANGE / FR_E_ARG for an
+ * (NULL = the defaults, i.e. fr_map).  Non-default settings run on
+ * instances of their own of the same passes.  Errors: those of fr_map, FR_E_RANGE / FR_E_ARG for an
  * option outside its range.
  */
 fr_status fr_map_ex(const void* volume, int32_t dtype, int32_t nx, int32_t ny, int32_t nz,
@@ -359,7 +358,7 @@ fr_status fr_batch_destroy(fr_batch b);
  * volumes (1 B/voxel), mask-voxel lists (4 B/mask voxel), staging rows
  * (384 B/mask voxel), two overflow lists per variant (8 B/mask voxel each),
  * segment and item tables, and generic-kernel scratch when a job may hold
- * more than 64 levels or uses a radius above 3.  Synchronous (uploads the
+ * more than 64 levels.  Synchronous (uploads the
  * tables); replaces any previous plan and graph, so work enqueued by an
  * earlier fr_batch_launch of this batch must have completed.  The jobs
  * array is copied.
@@ -376,8 +375,8 @@ fr_status fr_batch_prepare(fr_batch b, const fr_job* jobs, int32_t n_jobs);
  * work first; 32 present levels, MCC problems stashed), the MCC kernel over
  * the stash, per raw type one fused pass of the 64-level instances over
  * the neighbourhoods the first pass handed on, the generic kernel over the
- * neighbourhoods with more than 64 present levels (and over every voxel of
- * a radius above 3), and a batched transpose into every job's out_maps.
+ * neighbourhoods with more than 64 present levels, the same passes for each
+ * radius above 3 in use, and a batched transpose into every job's out_maps.
  * All on hip_stream; no host synchronisation and no allocation.  With
  * use_graph != 0 the sequence is captured into a HIP graph on the first
  * call (hip_stream must then be non-NULL) and the graph is replayed on
@@ -411,8 +410,7 @@ fr_status fr_batch_autotune(fr_batch b, void* hip_stream);
  * fr_batch_describe -- the plan: *n_variants, and for each variant 8 int32
  * in table (host, table_len entries): dtype, radius, bound of the present
  * levels (largest min(Ng, cube) of its jobs), jobs, work items, voxels per
- * item, grid of its pass, local levels of the first pass's instance (32;
- * 0: generic).
+ * item, grid of its pass, local levels of the first pass's instance (32).
  */
 fr_status fr_batch_describe(fr_batch b, int32_t* n_variants, int32_t* table, int32_t table_len);
 

@@ -381,48 +381,39 @@ struct PassBuffers {
   unsigned char* mcc;      // MCC stash of n_items problems (NULL: MCC in the map kernel)
 };
 
-// The call needs the generic kernel: radius above 3, non-default options,
-// or neighbourhoods that may hold more than 64 present levels.
-bool needs_generic(int32_t radius, const fr::MapOptions& opt, int lcap) {
-  return radius > 3 || !default_options(opt) || (radius >= 2 && lcap > 64);
-}
+// The call needs the generic kernel: neighbourhoods that may hold more than
+// 64 present levels (never at radius 1).
+bool needs_generic(int32_t radius, int lcap) { return radius >= 2 && lcap > 64; }
 
 // Enqueue the map passes for a.n_items items (a.params, a.list, a.out or
 // a.stage set): the 32-level instance over every voxel, the 64-level one over
 // the voxels it hands on, the generic kernel over the rest (only the passes
-// the level bound can need); radii above 3 and non-default options run
-// entirely on the generic kernel.
+// the level bound can need).
 fr_status enqueue_map_passes(fr::MapArgs a, int32_t dtype, int32_t radius, int lcap, bool debug,
                              const PassBuffers& pb, hipStream_t stream) {
-  const bool fast = radius <= 3 && default_options(a.opt);
-  if (fast) {
-    a.items = nullptr;
-    a.items_count = nullptr;
-    a.over = pb.over[0];
-    a.over_count = &pb.params->n_over[0];
-    a.over_job = 0;
-    a.mcc = debug ? nullptr : pb.mcc;
-    a.mcc_cap = a.n_items;
-    a.mcc_count = pb.params->n_mcc;
-    HIP_TRY(fr::launch_map(a, dtype, radius, 32, debug, stream));
-    if (radius >= 2 && lcap > 32) {
-      // the 64-level instance stashes its problems with <= 32 levels in the
-      // same stash (a voxel reaches one pass only) and solves wider ones
-      fr::MapArgs b = a;
-      b.items = pb.over[0];
-      b.items_count = &pb.params->n_over[0];
-      b.over = pb.over[1];
-      b.over_count = &pb.params->n_over[1];
-      HIP_TRY(fr::launch_map(b, dtype, radius, 64, debug, stream));
-      if (lcap > 64)
-        HIP_TRY(fr::launch_map_generic(a, nullptr, nullptr, pb.over[1], &pb.params->n_over[1], 0,
-                                       dtype, pb.gscratch, lcap, pb.generic_grid, stream));
-    }
-    if (a.mcc) HIP_TRY(fr::launch_mcc(pb.params->n_mcc, &pb.params->err, a.mcc, a.mcc_cap, stream));
-  } else {
-    HIP_TRY(fr::launch_map_generic(a, nullptr, nullptr, nullptr, nullptr, (int32_t)a.n_items, dtype,
-                                   pb.gscratch, lcap, pb.generic_grid, stream));
+  a.items = nullptr;
+  a.items_count = nullptr;
+  a.over = pb.over[0];
+  a.over_count = &pb.params->n_over[0];
+  a.over_job = 0;
+  a.mcc = debug || !default_options(a.opt) ? nullptr : pb.mcc;  // the variants solve theirs in the kernel
+  a.mcc_cap = a.n_items;
+  a.mcc_count = pb.params->n_mcc;
+  HIP_TRY(fr::launch_map(a, dtype, radius, 32, debug, stream));
+  if (radius >= 2 && lcap > 32) {
+    // the 64-level instance stashes its problems with <= 32 levels in the
+    // same stash (a voxel reaches one pass only) and solves wider ones
+    fr::MapArgs b = a;
+    b.items = pb.over[0];
+    b.items_count = &pb.params->n_over[0];
+    b.over = pb.over[1];
+    b.over_count = &pb.params->n_over[1];
+    HIP_TRY(fr::launch_map(b, dtype, radius, 64, debug, stream));
+    if (lcap > 64)
+      HIP_TRY(fr::launch_map_generic(a, nullptr, nullptr, pb.over[1], &pb.params->n_over[1], 0,
+                                     dtype, pb.gscratch, lcap, pb.generic_grid, stream));
   }
+  if (a.mcc) HIP_TRY(fr::launch_mcc(pb.params->n_mcc, &pb.params->err, a.mcc, a.mcc_cap, radius > 3, stream));
   return FR_OK;
 }
 
@@ -500,6 +491,7 @@ fr_status map_common(const void* volume, int32_t dtype, int32_t nx, int32_t ny, 
   memset(&a, 0, sizeof a);
   a.params = p->params;
   a.vol = volume;
+  a.dtype = dtype;
   a.levels = p->levels;
   a.list = p->list;
   a.sample = sample;
@@ -532,10 +524,10 @@ fr_status map_common(const void* volume, int32_t dtype, int32_t nx, int32_t ny, 
     prof = g_prof_on && !debug;
   }
   const int lcap = level_cap(disc_mode, disc_value, kernel_radius);
-  if (needs_generic(kernel_radius, opt, lcap) &&
+  if (needs_generic(kernel_radius, lcap) &&
       (st = pool_gscratch(p, (size_t)fr::kGenericGrid * fr::generic_scratch_bytes(lcap))) != FR_OK)
     return st;
-  if (!debug && kernel_radius <= 3 && default_options(opt) && (st = pool_mcc(p, n_items)) != FR_OK)
+  if (!debug && default_options(opt) && (st = pool_mcc(p, n_items)) != FR_OK)
     return st;
   const PassBuffers pb = {p->params, {p->over[0], p->over[1]}, p->gscratch, fr::kGenericGrid,
                           debug ? nullptr : p->mcc};
@@ -749,7 +741,9 @@ fr_status fr_map_noalloc(const void* volume, int32_t dtype, int32_t nx, int32_t 
   if ((st = check_device_ptr(out_maps, "out_maps")) != FR_OK) return st;
   fr::MapOptions opt = {1, 0, 0, 0};
   const int lcap = level_cap(disc_mode, disc_value, kernel_radius);
-  const size_t gbytes = needs_generic(kernel_radius, opt, lcap)
+  // radii above 3 count the generic region at every level bound: which jobs
+  // fit does not depend on the kernel that maps them
+  const size_t gbytes = kernel_radius > 3 || needs_generic(kernel_radius, lcap)
                             ? (size_t)kNoAllocGenericGrid * fr::generic_scratch_bytes(lcap)
                             : 0;
   // staging rows (coalesced output) when they fit, else direct stores
@@ -782,6 +776,7 @@ fr_status fr_map_noalloc(const void* volume, int32_t dtype, int32_t nx, int32_t 
   memset(&a, 0, sizeof a);
   a.params = ds.params;
   a.vol = volume;
+  a.dtype = dtype;
   a.levels = levels;
   a.list = list;
   a.out = out_maps;

@@ -5,7 +5,7 @@
 //          table and the work items: per raw type, one list of (job, first
 //          voxel) items over every job of radius 1..3, grouped by variant
 //          (radius and level class) and ordered by estimated work, largest
-//          first; generic variants (radii 4 and 5) keep lists of their own;
+//          first; wide variants (radii 4 and 5) keep lists of their own;
 //          allocates the batch's own device workspace and uploads the
 //          tables (synchronous, once).
 // launch   enqueues, on the caller's stream: batched discretisation; per raw
@@ -14,8 +14,9 @@
 //          instances, MCC problems stashed); per raw type one fused
 //          64-level pass over the neighbourhoods with more present levels
 //          (problems with <= 32 levels stashed too); one k_mcc over the
-//          stash; the generic kernel over what remains and
-//          over the generic variants; a batched transpose.  Optionally
+//          stash; the generic kernel over what remains; per wide variant
+//          the same three passes (MCC solved in the kernel); a batched
+//          transpose.  Optionally
 //          captured once into a hipGraph and replayed.  Allocates nothing.
 // status   per-job errors found on the device (mask count, Ng range), read
 //          after the stream has synchronised.
@@ -76,14 +77,20 @@ std::map<std::tuple<int, int, int>, Tuning> g_tuned;
 
 struct Variant {
   int dtype = 0, radius = 0;
-  bool generic = false;  // radius above 3: the generic kernel maps every voxel
+  bool wide = false;     // radius above 3: passes of its own
   int lcap = 1;          // largest present-level bound of its jobs
   int lclass = 32;       // 32 or 64: the tuning key's level class
   Tuning tune;
   std::vector<int> jobs;  // job indices
   int64_t n_vox = 0;      // mask voxels of its jobs
   int32_t n_items = 0;    // its work items (in its group's list, or its own)
-  int2* d_items = nullptr;  // generic variants: their own item list
+  // wide variants: their own item list, the overflow lists of their 32- and
+  // 64-level passes (one entry per voxel; where more levels may be present)
+  // and their place in the counters
+  int2* d_items = nullptr;
+  int2* d_over[2] = {nullptr, nullptr};
+  int grid32 = 0, grid64 = 0;
+  int widx = 0;
 };
 
 // The fixed-radius jobs of one raw type: one fused list of work items and
@@ -137,7 +144,7 @@ struct fr_batch_s {
   float* d_stage = nullptr;
   int2* d_tr_items = nullptr;
   // per group: two overflow counts and two work-queue heads; then the two
-  // MCC stash counts
+  // MCC stash counts; then per wide variant what a group has
   int32_t* d_counters = nullptr;
   void* d_gscratch = nullptr;     // generic-kernel scratch
   // MCC problems of the 32-level passes (one per fixed-radius voxel at
@@ -170,7 +177,11 @@ void free_workspace(fr_batch_s* b) {
   (void)hipFree(b->d_counters);
   (void)hipFree(b->d_gscratch);
   (void)hipFree(b->d_mcc);
-  for (auto& v : b->variants) (void)hipFree(v.d_items);
+  for (auto& v : b->variants) {
+    (void)hipFree(v.d_items);
+    (void)hipFree(v.d_over[0]);
+    (void)hipFree(v.d_over[1]);
+  }
   for (auto& g : b->groups) {
     (void)hipFree(g.d_items);
     (void)hipFree(g.d_over[0]);
@@ -236,10 +247,10 @@ void variant_items(const fr_batch_s* b, const Variant& v, int vpw, std::vector<i
 
 // Every job's work-item size from its variant's tuning, uploaded with the
 // job table; then each group's fused item list (its variants in order) and
-// each generic variant's own list (one voxel per item).
+// each wide variant's own list (one voxel per item).
 fr_status build_items(fr_batch_s* b) {
   for (auto& v : b->variants)
-    for (int j : v.jobs) b->bj[j].vpw = v.generic ? 1 : v.tune.vpw;
+    for (int j : v.jobs) b->bj[j].vpw = v.wide ? 1 : v.tune.vpw;
   BHIP(hipMemcpy(b->d_jobs, b->bj.data(), sizeof(fr::BatchJob) * b->bj.size(), hipMemcpyHostToDevice));
   fr_status e;
   for (auto& g : b->groups) {
@@ -254,7 +265,7 @@ fr_status build_items(fr_batch_s* b) {
     g.n_items = (int32_t)items.size();
   }
   for (auto& v : b->variants) {
-    if (!v.generic) continue;
+    if (!v.wide) continue;
     std::vector<int2> items;
     variant_items(b, v, 1, &items);
     int32_t cap = 0;
@@ -269,7 +280,9 @@ fr_status build_items(fr_batch_s* b) {
 int32_t* group_counters(fr_batch_s* b, int gi) { return b->d_counters + kGroupCounters * gi; }
 // The two MCC stash counts, after the groups' counters.
 int32_t* mcc_counts(fr_batch_s* b) { return b->d_counters + kGroupCounters * 2; }
-constexpr int kCounters = kGroupCounters * 2 + 2;
+// The counters of wide variant w (at most four: two raw types, radii 4, 5).
+int32_t* wide_counters(fr_batch_s* b, int w) { return b->d_counters + kGroupCounters * (2 + w) + 2; }
+constexpr int kCounters = kGroupCounters * 6 + 2;
 
 // The fused first pass of group gi over n items of its list.
 fr_status enqueue_first(fr_batch_s* b, int gi, int32_t n, hipStream_t st) {
@@ -300,7 +313,7 @@ fr_status enqueue(fr_batch_s* b, hipStream_t st) {
     BHIP(fr::launch_map_fused(b->d_jobs, b->d_params, g.d_over[0], 0, c, g.dtype, 64, g.grid64, g.d_over[1],
                               c + 1, c + 3, b->d_mcc, b->cap_mcc, mcc_counts(b), st));
   }
-  BHIP(fr::launch_mcc(mcc_counts(b), nullptr, b->d_mcc, b->cap_mcc, st));
+  BHIP(fr::launch_mcc(mcc_counts(b), nullptr, b->d_mcc, b->cap_mcc, false, st));
   fr::MapArgs none;
   memset(&none, 0, sizeof none);
   for (int gi = 0; gi < 2; ++gi) {  // and more than 64
@@ -310,9 +323,16 @@ fr_status enqueue(fr_batch_s* b, hipStream_t st) {
                                 g.dtype, b->d_gscratch, b->lcap_generic, fr::kGenericGrid, st));
   }
   for (auto& v : b->variants) {
-    if (!v.generic) continue;
-    BHIP(fr::launch_map_generic(none, b->d_jobs, b->d_params, v.d_items, nullptr, v.n_items, v.dtype,
-                                b->d_gscratch, b->lcap_generic, fr::kGenericGrid, st));
+    if (!v.wide) continue;
+    int32_t* c = wide_counters(b, v.widx);
+    BHIP(fr::launch_map_batch(b->d_jobs, b->d_params, v.d_items, v.n_items, nullptr, 1, v.dtype, v.radius, 32,
+                              v.grid32, v.d_over[0], c, c + 2, nullptr, 0, nullptr, st));
+    if (v.lcap <= 32) continue;
+    BHIP(fr::launch_map_batch(b->d_jobs, b->d_params, v.d_over[0], 0, c, 1, v.dtype, v.radius, 64, v.grid64,
+                              v.d_over[1], c + 1, c + 3, nullptr, 0, nullptr, st));
+    if (v.lcap <= 64) continue;
+    BHIP(fr::launch_map_generic(none, b->d_jobs, b->d_params, v.d_over[1], c + 1, 0, v.dtype, b->d_gscratch,
+                                b->lcap_generic, fr::kGenericGrid, st));
   }
   BHIP(fr::launch_transpose_batch(b->d_jobs, b->d_params, b->d_tr_items, (int32_t)b->tr_items.size(),
                                   st));
@@ -485,7 +505,7 @@ fr_status fr_batch_prepare(fr_batch b, const fr_job* jobs, int32_t n_jobs) {
       Variant v;
       v.dtype = J.dtype;
       v.radius = J.kernel_radius;
-      v.generic = J.kernel_radius > 3;
+      v.wide = J.kernel_radius > 3;
       vindex[key] = (int)b->variants.size();
       b->variants.push_back(v);
       it = vindex.find(key);
@@ -496,18 +516,18 @@ fr_status fr_batch_prepare(fr_batch b, const fr_job* jobs, int32_t n_jobs) {
     v.n_vox += J.n_mask;
   }
   for (auto& v : b->variants) {
-    v.lclass = v.generic ? 0 : level_class(v.lcap);
+    v.lclass = v.wide ? 0 : level_class(v.lcap);
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto t = g_tuned.find(std::make_tuple(v.dtype, v.radius, v.lclass));
     if (t != g_tuned.end()) v.tune = t->second;
-    if (v.generic || (v.radius >= 2 && v.lcap > 64)) b->lcap_generic = std::max(b->lcap_generic, v.lcap);
+    if (v.radius >= 2 && v.lcap > 64) b->lcap_generic = std::max(b->lcap_generic, v.lcap);
   }
   // groups: the fast variants of each raw type, largest estimated work first
   for (int gi = 0; gi < 2; ++gi) b->groups[gi].dtype = gi == 0 ? FR_I16 : FR_F32;
   {
     std::vector<int> order;
     for (int vi = 0; vi < (int)b->variants.size(); ++vi)
-      if (!b->variants[vi].generic) order.push_back(vi);
+      if (!b->variants[vi].wide) order.push_back(vi);
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
       return variant_cost(b->variants[x]) > variant_cost(b->variants[y]);
     });
@@ -539,6 +559,18 @@ fr_status fr_batch_prepare(fr_batch b, const fr_job* jobs, int32_t n_jobs) {
     free_workspace(b);
     return bfail(FR_E_NOMEM, "batch workspace allocation failed (%lld voxels, %lld mask voxels)",
                  (long long)vox, (long long)mvox);
+  }
+  int n_wide = 0;
+  for (auto& v : b->variants) {
+    if (!v.wide) continue;
+    v.widx = n_wide++;
+    if (v.lcap > 32 &&
+        (!dal((void**)&v.d_over[0], sizeof(int2) * v.n_vox) || !dal((void**)&v.d_over[1], sizeof(int2) * v.n_vox))) {
+      free_workspace(b);
+      return bfail(FR_E_NOMEM, "overflow-list allocation failed");
+    }
+    v.grid32 = b->n_cu * fr::map_batch_blocks_per_cu(v.dtype, v.radius, 32, false);
+    v.grid64 = b->n_cu * fr::map_batch_blocks_per_cu(v.dtype, v.radius, 64, false);
   }
   for (auto& g : b->groups) {
     if (g.variants.empty()) continue;
@@ -650,7 +682,7 @@ fr_status fr_batch_autotune(fr_batch b, void* hip_stream) {
   // voxels each) and the MCC of the problems it stashed
   for (int vi = 0; vi < (int)b->variants.size(); ++vi) {
     Variant& v = b->variants[vi];
-    if (v.generic) continue;
+    if (v.wide) continue;
     const int gi = v.dtype == FR_I16 ? 0 : 1;
     Group& g = b->groups[gi];
     Tuning best = v.tune;
@@ -667,7 +699,7 @@ fr_status fr_batch_autotune(fr_batch b, void* hip_stream) {
         BHIP(fr::launch_zero_i32(b->d_counters, kCounters, st));
         BHIP(hipEventRecord(e0, st));
         if ((e = enqueue_first(b, gi, (int32_t)items.size(), st)) != FR_OK) return e;
-        BHIP(fr::launch_mcc(mcc_counts(b), nullptr, b->d_mcc, b->cap_mcc, st));
+        BHIP(fr::launch_mcc(mcc_counts(b), nullptr, b->d_mcc, b->cap_mcc, false, st));
         BHIP(hipEventRecord(e1, st));
         BHIP(hipEventSynchronize(e1));
         BHIP(hipEventElapsedTime(&ms, e0, e1));
@@ -702,9 +734,9 @@ fr_status fr_batch_describe(fr_batch b, int32_t* n_variants, int32_t* table, int
       t[2] = v.lcap;
       t[3] = (int32_t)v.jobs.size();
       t[4] = v.n_items;
-      t[5] = v.generic ? 1 : v.tune.vpw;
-      t[6] = v.generic ? fr::kGenericGrid : b->groups[v.dtype == FR_I16 ? 0 : 1].grid32;
-      t[7] = v.generic ? 0 : 32;
+      t[5] = v.wide ? 1 : v.tune.vpw;
+      t[6] = v.wide ? v.grid32 : b->groups[v.dtype == FR_I16 ? 0 : 1].grid32;
+      t[7] = 32;
     }
   return FR_OK;
 }

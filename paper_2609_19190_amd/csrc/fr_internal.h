@@ -52,7 +52,7 @@ hipError_t launch_discretise(const void* vol, int dtype, int64_t nvox, const uin
                              hipStream_t st);
 
 // Settings of the IBSI extraction variants (defaults: distance 1, alpha 0,
-// merged); only the generic kernel implements the non-default ones.
+// merged).
 struct MapOptions {
   int32_t glcm_dist;   // GLCM neighbour offset: distance x each of the 13 directions
   int32_t gldm_alpha;  // GLDM: a neighbour depends on v when |g_u - g_v| <= alpha
@@ -63,6 +63,7 @@ struct MapOptions {
 struct MapArgs {
   const DiscParams* params; // device parameter block of the job (Ng, error state)
   const void* vol;          // raw volume (int16 or float)
+  int32_t dtype;            // its type (1: int16, 2: float)
   const uint8_t* levels;    // discretised volume, 0 outside mask
   const int32_t* list;      // compact index -> linear voxel index
   const int64_t* sample;    // optional: restrict to these compact indices
@@ -142,8 +143,8 @@ enum { kJobOk = 0, kJobNgRange = 1, kJobEmpty = 2, kJobCount = 3 };
 hipError_t launch_discretise_batch(const BatchJob* jobs, int32_t n_jobs, const int32_t* seg_job,
                                    int64_t n_seg, const DiscScratch& s, hipStream_t st);
 
-// Persistent batched map kernel for one (dtype, radius) variant on the
-// instance with lmax (32 or 64) local levels: items[w] = (job, first
+// Persistent batched map kernel for one (dtype, radius) variant, radius 1..5,
+// on the instance with lmax (32 or 64) local levels: items[w] = (job, first
 // compact index), vpw voxels each (items NULL: a single job, jobs[0], item
 // w starting at voxel w * vpw); with n_items_dev set, the item count is
 // read on the device.  A voxel with more than lmax present levels is
@@ -158,6 +159,12 @@ hipError_t launch_map_batch(const BatchJob* jobs, const DiscParams* params, cons
                             int radius, int lmax, int grid, int2* over, int32_t* over_count,
                             int32_t* queue, unsigned char* mcc, int64_t mcc_cap, int32_t* mcc_count,
                             hipStream_t st);
+
+// launch_map_batch's kernels of radius 4 and 5 (no stash) and their occupancy.
+hipError_t launch_map_batch_wide(const BatchJob* jobs, const DiscParams* params, const int2* items,
+                                 int32_t n_items, const int32_t* n_items_dev, int32_t vpw, int radius, int lmax,
+                                 int grid, int2* over, int32_t* over_count, int32_t* queue, hipStream_t st);
+int map_batch_wide_blocks_per_cu(int radius, int lmax);
 
 // Fused batched pass over the jobs of every fixed radius (1..3) of one raw
 // type: one persistent kernel whose work items name their job (and thereby
@@ -208,15 +215,18 @@ hipError_t launch_transpose_batch(const BatchJob* jobs, const DiscParams* params
 // go to the stash and launch_mcc must follow before the maps are read.
 hipError_t launch_map(const MapArgs& a, int dtype, int radius, int lmax, bool debug,
                       hipStream_t st);
-// Resident workgroups of a plain map instance on the current device.
-int map_resident(int dtype, int radius, int lmax);
+// launch_map's kernels of radius 4 and 5, and of the extraction variants
+// (every radius; a.d_glcm set: the matrices are dumped).
+hipError_t launch_map_wide(const MapArgs& a, int radius, int lmax, bool debug, hipStream_t st);
+hipError_t launch_map_variant(const MapArgs& a, int radius, int lmax, hipStream_t st);
 
 // The MCC of every problem in a stash of cap problems (device counts
 // n_mcc[0..1]: problems with <= 16 levels from the stash's start, wider
 // ones from its end), written to each problem's output address; nothing
-// when *err (if err is set) holds a job error.
+// when *err (if err is set) holds a job error.  fine: to the finer search
+// width (the problems of radii 4 and 5).
 hipError_t launch_mcc(const int32_t* n_mcc, const int32_t* err, const unsigned char* stash,
-                      int64_t cap, hipStream_t st);
+                      int64_t cap, bool fine, hipStream_t st);
 // out[k * n + m] = stage[m * kStageStride + k] for k < count, m < n (nothing
 // when params->err is set).
 hipError_t launch_transpose(const float* stage, float* out, int64_t n, int count,

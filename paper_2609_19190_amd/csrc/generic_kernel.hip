@@ -1,15 +1,11 @@
 // Generic spatial-mapping kernel for gfx950: the neighbourhoods the fused
-// fixed-radius kernel does not take.
+// fixed-radius kernels do not take.
 //
 // It computes exactly the maps of the fused kernel (paper: "Software design
 // and extraction modes" -- spatial maps; Table 2's 93 maps; IBSI feature
-// definitions) for
-//   - neighbourhoods holding more present gray levels than the 64-level
-//     tables of the fused kernel (up to 255),
-//   - kernel radii above 3 (up to kGenericMaxRadius),
-//   - the IBSI extraction variants the paper lists among its settings: GLCM
-//     neighbour distance > 1, GLDM coarseness alpha > 0, and GLCM / GLRLM
-//     features averaged over the 13 directions instead of merged.
+// definitions) for neighbourhoods holding more present gray levels than the
+// 64-level tables of the fused kernel (up to 255), at every radius up to
+// kGenericMaxRadius and with every extraction variant.
 // One workgroup of 256 threads (four waves) maps one voxel at a time and is
 // persistent over its share of the items.  The cube (levels, raw values,
 // equal-level bits, zone labels) lives in LDS; the tables indexed by present

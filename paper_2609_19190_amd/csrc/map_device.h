@@ -34,6 +34,13 @@ __host__ __device__ constexpr int fdy(int d) {
 __host__ __device__ constexpr int fdz(int d) {
   return d == 0 ? 0 : d == 1 ? 0 : d == 2 ? 1 : d == 3 ? 0 : d == 4 ? 0 : 1;
 }
+// The same offsets as a table, for a direction known only at run time.
+__constant__ signed char kDir[13][3] = {
+    {fdx(0), fdy(0), fdz(0)},    {fdx(1), fdy(1), fdz(1)},    {fdx(2), fdy(2), fdz(2)},
+    {fdx(3), fdy(3), fdz(3)},    {fdx(4), fdy(4), fdz(4)},    {fdx(5), fdy(5), fdz(5)},
+    {fdx(6), fdy(6), fdz(6)},    {fdx(7), fdy(7), fdz(7)},    {fdx(8), fdy(8), fdz(8)},
+    {fdx(9), fdy(9), fdz(9)},    {fdx(10), fdy(10), fdz(10)}, {fdx(11), fdy(11), fdz(11)},
+    {fdx(12), fdy(12), fdz(12)}};
 __host__ __device__ constexpr int ndx(int n) { return n < 13 ? fdx(n) : -fdx(n - 13); }
 __host__ __device__ constexpr int ndy(int n) { return n < 13 ? fdy(n) : -fdy(n - 13); }
 __host__ __device__ constexpr int ndz(int n) { return n < 13 ? fdz(n) : -fdz(n - 13); }

@@ -217,9 +217,13 @@ struct Layout {
       gscratch, keep, total;
 };
 
-// The job needs the generic kernel: radius above 3, or neighbourhoods that
-// may hold more than 64 present levels.
-bool needs_generic(const fr::BatchJob& B) { return B.radius > 3 || (B.radius >= 2 && B.lcap > 64); }
+// The job may hold neighbourhoods of more than 64 present levels, which the
+// generic kernel maps.
+bool needs_generic(const fr::BatchJob& B) { return B.radius >= 2 && B.lcap > 64; }
+// The job's block has a generic-kernel region (counted for every radius
+// above 3, used by none of them up to 64 levels: a job's footprint, which
+// decides whether it is admitted, is the documented one).
+bool generic_region(const fr::BatchJob& B) { return B.radius > 3 || needs_generic(B); }
 
 Layout layout_of(const fr::BatchJob& B) {
   Layout L;
@@ -245,7 +249,7 @@ Layout layout_of(const fr::BatchJob& B) {
   L.params = take(sizeof(fr::DiscParams));
   L.over0 = take((int64_t)sizeof(int2) * B.n_mask);
   L.over1 = take((int64_t)sizeof(int2) * B.n_mask);
-  L.gscratch = take(needs_generic(B) ? (int64_t)kServeGenericGrid * (int64_t)fr::generic_scratch_bytes(B.lcap) : 0);
+  L.gscratch = take(generic_region(B) ? (int64_t)kServeGenericGrid * (int64_t)fr::generic_scratch_bytes(B.lcap) : 0);
   L.total = o;
   return L;
 }
@@ -341,7 +345,7 @@ hipError_t launch_job(fr_server_s* s, SJob& J, Slot& sl) {
   int2* over1 = (int2*)(blk + L.over1);
   fr::MapArgs none;
   memset(&none, 0, sizeof none);
-  if (B.radius <= 3) {
+  {
     int vpw, mult, klmax;
     fr::tuned_settings(B.dtype, B.radius, J.lcap, &vpw, &mult, &klmax);
     const int32_t n_items = (int32_t)((B.n_mask + vpw - 1) / vpw);
@@ -369,10 +373,6 @@ hipError_t launch_job(fr_server_s* s, SJob& J, Slot& sl) {
                                       sl.st)) != hipSuccess)
         return e;
     }
-  } else if ((e = fr::launch_map_generic(none, djob, dpar, nullptr, nullptr, (int32_t)B.n_mask, B.dtype,
-                                         blk + L.gscratch, B.lcap, kServeGenericGrid, sl.st)) !=
-             hipSuccess) {
-    return e;
   }
   if ((e = fr::launch_transpose_batch(djob, dpar, nullptr, (int32_t)((B.n_mask + 63) / 64), sl.st)) !=
       hipSuccess)

@@ -1,0 +1,127 @@
+"""GPU parity of the kernels of radius 4 and 5 and of the extraction variants
+where their tables can go wrong: present levels at and beyond the 32- and
+64-level tables, uniform neighbourhoods (the largest zones, runs and counts),
+family subsets; and the same maps from a batch, a server and the
+allocation-free entry point, bit for bit.
+"""
+import numpy as np
+import pytest
+
+from helpers import format_report, parity_report, to_dev
+from oracle import oracle as O
+from paper_2609_19190_amd import synth
+
+pytestmark = pytest.mark.gpu
+ALL = 63
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_19190_amd import binding
+    binding.lib()
+    return binding
+
+
+# radius, bins, shape, raw type, families, variant
+CASES = [
+    (4, 2, (9, 9, 9), np.float32, ALL, {}),
+    (4, 32, (11, 12, 13), np.int16, ALL, {}),
+    (4, 33, (11, 12, 13), np.float32, ALL, {}),
+    (4, 64, (10, 11, 12), np.int16, ALL, {}),
+    (4, 65, (10, 11, 12), np.float32, ALL, {}),
+    (5, 1, (11, 11, 11), np.int16, ALL, {}),
+    (5, 32, (12, 13, 14), np.float32, ALL, {}),
+    (5, 64, (11, 12, 13), np.int16, ALL, {}),
+    (5, 90, (11, 11, 12), np.float32, ALL, {}),
+    (5, 40, (12, 11, 13), np.float32, 2, {}),
+    (5, 20, (12, 11, 13), np.int16, 4 | 8, {}),
+    (4, 20, (12, 11, 13), np.float32, 1 | 16 | 32, {}),
+    (1, 27, (8, 9, 10), np.int16, ALL, dict(averaged=True)),
+    (2, 33, (9, 10, 11), np.float32, ALL, dict(averaged=True)),
+    (3, 64, (9, 10, 11), np.int16, ALL, dict(averaged=True, gldm_alpha=254)),
+    (3, 70, (8, 9, 10), np.float32, ALL, dict(averaged=True)),
+    (4, 48, (9, 10, 11), np.int16, ALL, dict(glcm_distance=9, gldm_alpha=3)),
+    (5, 40, (9, 10, 11), np.float32, 2 | 4, dict(glcm_distance=10, averaged=True)),
+    (2, 2, (9, 9, 9), np.float32, ALL, dict(glcm_distance=2)),
+    (3, 65, (8, 9, 10), np.int16, 2 | 16, dict(gldm_alpha=1)),
+]
+
+
+def make(radius, bins, shape, dt, families, mask_fill=0.8):
+    return synth.random_case(700 + 10 * radius + bins, shape=shape, dtype=dt, radius=radius, levels=bins,
+                             mode=O.FBN, value=bins, families=families, mask_fill=mask_fill)
+
+
+@pytest.mark.parametrize("radius,bins,shape,dt,families,v", CASES)
+def test_wide_and_variants_against_the_oracle(B, radius, bins, shape, dt, families, v):
+    import torch
+    case = make(radius, bins, shape, dt, families)
+    print("case", radius, bins, shape, families, v, "n_mask", case.n_mask, flush=True)
+    opt = B.map_options(v.get("glcm_distance", 1), v.get("gldm_alpha", 0),
+                        B.FR_AVERAGED if v.get("averaged") else B.FR_MERGED) if v else None
+    vol, mask = to_dev(case)
+    args = (vol, mask, case.spacing, case.mode, case.value, case.lower, radius, families, case.n_mask)
+    gpu = B.fr_map(*args, options=opt)
+    assert B.fr_map_check() == bins
+    gpu = gpu.cpu().numpy()
+    orc = O.spatial_map(case, **v)
+    ok, rows = parity_report(gpu, orc, O.map_names(families))
+    assert ok, format_report(rows, only_bad=True)
+    samp = np.arange(0, case.n_mask, max(1, case.n_mask // 24), dtype=np.int64)
+    res = B.fr_map_matrices(*args, torch.from_numpy(samp), bins, options=opt)
+    torch.cuda.synchronize()
+    res = {k: t.cpu().numpy() for k, t in res.items()}
+    assert np.array_equal(gpu[:, samp].view(np.uint32), res["maps"].view(np.uint32))
+    olev, _, _, _ = O.discretise(case.volume, case.mask, case.mode, case.value, case.lower)
+    pts = np.argwhere(case.mask)
+    keys = ["hist"] + [k for f, ks in ((2, ["glcm"]), (4, ["glrlm"]), (8, ["glszm"]), (16, ["gldm"]),
+                                       (32, ["ngtdm_n", "ngtdm_S"])) if families & f for k in ks]
+    for q, s in enumerate(samp):
+        m = O.matrices(olev, case.volume, bins, tuple(int(c) for c in pts[s]), radius,
+                       glcm_distance=v.get("glcm_distance", 1), gldm_alpha=v.get("gldm_alpha", 0))
+        for key in keys:
+            assert np.array_equal(res[key][q], m[key]), f"{key} differs at compact index {s}"
+
+
+def test_wide_batch_served_and_noalloc_equal_plain(B):
+    import torch
+    cases = [make(4, 32, (10, 11, 12), np.int16, ALL), make(5, 70, (9, 10, 11), np.float32, ALL),
+             make(4, 50, (11, 9, 10), np.float32, 1 | 2), make(2, 20, (9, 9, 9), np.int16, ALL)]
+    dev = [to_dev(c) for c in cases]
+    args = [(v, m, c.spacing, c.mode, c.value, c.lower, c.radius, c.families, c.n_mask)
+            for c, (v, m) in zip(cases, dev)]
+    plain = [B.fr_map(*a).cpu().numpy().view(np.uint32) for a in args]
+    keys = ("volume", "mask", "spacing", "mode", "value", "lower", "radius", "families", "n_mask")
+    bt = B.Batch([dict(zip(keys, a)) for a in args])
+    srv = B.Server(1 << 30, slots=2)
+    try:
+        print("plan", bt.describe(), flush=True)
+        s = torch.cuda.Stream()
+        for use_graph in (False, True, True):  # eager, captured, replayed
+            for o in bt.outs:
+                o.fill_(0.0)
+            torch.cuda.synchronize()
+            with torch.cuda.stream(s):
+                bt.launch(use_graph=use_graph)
+                rc, st, _ = bt.status()
+            assert rc == B.FR_OK and st == [0] * len(cases)
+            for o, ref in zip(bt.outs, plain):
+                assert np.array_equal(o.cpu().numpy().view(np.uint32), ref)
+        tickets = [srv.submit(*a) for a in args]
+        for t, ref in zip(tickets, plain):
+            srv.wait(t)
+            got = srv.maps(t)
+            torch.cuda.synchronize()
+            assert np.array_equal(got.cpu().numpy().view(np.uint32), ref)
+            srv.release(t)
+    finally:
+        bt.close()
+        srv.close()
+    for a, ref in zip(args, plain):
+        out = torch.empty(ref.shape, dtype=torch.float32, device="cuda:0")
+        B.fr_map_noalloc(*a, out)
+        B.fr_map_check()
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), ref)
