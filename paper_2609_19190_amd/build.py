@@ -23,7 +23,9 @@ ARCH = "gfx950"
 FLAGS = ["-O3", "-std=c++17", f"--offload-arch={ARCH}", "-fPIC", "-Wall",
          # no packed FP32 instructions in any generated code
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-SOURCES = ["discretise.hip", "map_kernel.hip", "map_batch.hip", "map_wide.hip", "map_variant.hip", "generic_kernel.hip", "api.cpp", "batch.cpp", "server.cpp",
+SOURCES = ["discretise.hip", "map_f32.hip", "map_i16.hip", "map_fused.hip", "map_variant.hip", "map_averaged.hip",
+           "map_wide.hip", "map_batch_f32.hip", "map_batch_i16.hip", "map_kernel.hip",
+           "generic_kernel.hip", "api.cpp", "batch.cpp", "server.cpp",
            "scalar.cpp"]
 PEAKS_SOURCE = "peaks.hip"
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")

@@ -160,6 +160,17 @@ hipError_t launch_map_batch(const BatchJob* jobs, const DiscParams* params, cons
                             int32_t* queue, unsigned char* mcc, int64_t mcc_cap, int32_t* mcc_count,
                             hipStream_t st);
 
+// launch_map_batch's kernels of radius 1..3 by raw type and their occupancy.
+hipError_t launch_map_batch_i16(const BatchJob* jobs, const DiscParams* params, const int2* items, int32_t n_items,
+                                const int32_t* n_items_dev, int32_t vpw, int radius, int lmax, int grid, int2* over,
+                                int32_t* over_count, int32_t* queue, unsigned char* mcc, int64_t mcc_cap,
+                                int32_t* mcc_count, hipStream_t st);
+int map_batch_i16_blocks_per_cu(int radius, int lmax, bool stash);
+hipError_t launch_map_batch_f32(const BatchJob* jobs, const DiscParams* params, const int2* items, int32_t n_items,
+                                const int32_t* n_items_dev, int32_t vpw, int radius, int lmax, int grid, int2* over,
+                                int32_t* over_count, int32_t* queue, unsigned char* mcc, int64_t mcc_cap,
+                                int32_t* mcc_count, hipStream_t st);
+int map_batch_f32_blocks_per_cu(int radius, int lmax, bool stash);
 // launch_map_batch's kernels of radius 4 and 5 (no stash) and their occupancy.
 hipError_t launch_map_batch_wide(const BatchJob* jobs, const DiscParams* params, const int2* items,
                                  int32_t n_items, const int32_t* n_items_dev, int32_t vpw, int radius, int lmax,
@@ -215,10 +226,14 @@ hipError_t launch_transpose_batch(const BatchJob* jobs, const DiscParams* params
 // go to the stash and launch_mcc must follow before the maps are read.
 hipError_t launch_map(const MapArgs& a, int dtype, int radius, int lmax, bool debug,
                       hipStream_t st);
+// launch_map's kernels of radius 1..3 by raw type.
+hipError_t launch_map_i16(const MapArgs& a, int radius, int lmax, bool debug, hipStream_t st);
+hipError_t launch_map_f32(const MapArgs& a, int radius, int lmax, bool debug, hipStream_t st);
 // launch_map's kernels of radius 4 and 5, and of the extraction variants
 // (every radius; a.d_glcm set: the matrices are dumped).
 hipError_t launch_map_wide(const MapArgs& a, int radius, int lmax, bool debug, hipStream_t st);
 hipError_t launch_map_variant(const MapArgs& a, int radius, int lmax, hipStream_t st);
+hipError_t launch_map_averaged(const MapArgs& a, int radius, int lmax, hipStream_t st);
 
 // The MCC of every problem in a stash of cap problems (device counts
 // n_mcc[0..1]: problems with <= 16 levels from the stash's start, wider

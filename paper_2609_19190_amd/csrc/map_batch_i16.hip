@@ -1,0 +1,17 @@
+// Batched map kernels of radius 1..3 for int16 volumes (one persistent pass per
+// radius, as served jobs take it).
+#include "map_body.h"
+
+namespace fr {
+
+hipError_t launch_map_batch_i16(const BatchJob* jobs, const DiscParams* params, const int2* items, int32_t n_items,
+                                const int32_t* n_items_dev, int32_t vpw, int radius, int lmax, int grid, int2* over,
+                                int32_t* over_count, int32_t* queue, unsigned char* mcc, int64_t mcc_cap,
+                                int32_t* mcc_count, hipStream_t st) {
+  return launch_b_r<int16_t>(jobs, params, items, n_items, n_items_dev, vpw, radius, lmax, grid, over, over_count,
+                           queue, mcc, mcc_cap, mcc_count, st);
+}
+
+int map_batch_i16_blocks_per_cu(int radius, int lmax, bool stash) { return occ_b_r<int16_t>(radius, lmax, stash); }
+
+}  // namespace fr

@@ -2347,6 +2347,26 @@ hipError_t launch_t(const MapArgs& a, bool debug, hipStream_t st) {
   return a.mcc ? launch_i<T, R, LMAX, false, true>(a, st) : launch_i<T, R, LMAX, false, false>(a, st);
 }
 
+template <typename T>
+hipError_t launch_r(const MapArgs& a, int radius, int lmax, bool debug, hipStream_t st) {
+  if (radius == 1) return launch_t<T, 1, 32>(a, debug, st);
+  if (radius == 2) return lmax <= 32 ? launch_t<T, 2, 32>(a, debug, st) : launch_t<T, 2, 64>(a, debug, st);
+  return lmax <= 32 ? launch_t<T, 3, 32>(a, debug, st) : launch_t<T, 3, 64>(a, debug, st);
+}
+
+// An extraction variant's launch (any radius, both raw types).
+template <int MODE>
+hipError_t launch_v(const MapArgs& a, int radius, int lmax, hipStream_t st) {
+  const bool l32 = lmax <= 32;
+  switch (radius) {
+    case 1: return launch_i<AnyRaw, 1, 32, true, false, MODE>(a, st);
+    case 2: return l32 ? launch_i<AnyRaw, 2, 32, true, false, MODE>(a, st) : launch_i<AnyRaw, 2, 64, true, false, MODE>(a, st);
+    case 3: return l32 ? launch_i<AnyRaw, 3, 32, true, false, MODE>(a, st) : launch_i<AnyRaw, 3, 64, true, false, MODE>(a, st);
+    case 4: return l32 ? launch_i<AnyRaw, 4, 32, true, false, MODE>(a, st) : launch_i<AnyRaw, 4, 64, true, false, MODE>(a, st);
+    default: return l32 ? launch_i<AnyRaw, 5, 32, true, false, MODE>(a, st) : launch_i<AnyRaw, 5, 64, true, false, MODE>(a, st);
+  }
+}
+
 template <typename T, int R, int LMAX, bool MOUT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MOUT && R <= 3 ? 3 : 2))) void k_map_batch(
     const BatchJob* __restrict__ jobs, const DiscParams* __restrict__ params,
@@ -2463,6 +2483,33 @@ int occ_b() {
   return nb > 0 ? nb : 1;
 }
 
+
+template <typename T>
+hipError_t launch_b_r(const BatchJob* jobs, const DiscParams* params, const int2* items,
+                      int32_t n_items, const int32_t* n_items_dev, int32_t vpw, int radius,
+                      int lmax, int grid, int2* over, int32_t* over_count, int32_t* queue,
+                      unsigned char* mcc, int64_t mcc_cap, int32_t* mcc_count, hipStream_t st) {
+  if (radius == 1)
+    return launch_b<T, 1, 32>(jobs, params, items, n_items, n_items_dev, vpw, grid, over, over_count,
+                              queue, mcc, mcc_cap, mcc_count, st);
+  if (radius == 2)
+    return lmax <= 32 ? launch_b<T, 2, 32>(jobs, params, items, n_items, n_items_dev, vpw, grid, over,
+                                           over_count, queue, mcc, mcc_cap, mcc_count, st)
+                      : launch_b<T, 2, 64>(jobs, params, items, n_items, n_items_dev, vpw, grid, over,
+                                           over_count, queue, nullptr, 0, nullptr, st);
+  return lmax <= 32 ? launch_b<T, 3, 32>(jobs, params, items, n_items, n_items_dev, vpw, grid, over,
+                                         over_count, queue, mcc, mcc_cap, mcc_count, st)
+                    : launch_b<T, 3, 64>(jobs, params, items, n_items, n_items_dev, vpw, grid, over,
+                                         over_count, queue, nullptr, 0, nullptr, st);
+}
+
+template <typename T>
+int occ_b_r(int radius, int lmax, bool stash) {
+  if (radius == 1) return stash ? occ_b<T, 1, 32, true>() : occ_b<T, 1, 32, false>();
+  if (radius == 2)
+    return lmax > 32 ? occ_b<T, 2, 64, false>() : (stash ? occ_b<T, 2, 32, true>() : occ_b<T, 2, 32, false>());
+  return lmax > 32 ? occ_b<T, 3, 64, false>() : (stash ? occ_b<T, 3, 32, true>() : occ_b<T, 3, 32, false>());
+}
 
 }  // namespace
 }  // namespace fr

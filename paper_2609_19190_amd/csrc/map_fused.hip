@@ -1,5 +1,4 @@
-// Batched map kernels of radius 1..3: one persistent pass per (raw type,
-// radius) for served jobs, the fused pass over every radius for batches.
+// The fused batched pass over every radius 1..3.
 #include "map_body.h"
 
 namespace fr {
@@ -122,33 +121,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LMAX == 32 ?
 }
 
 
-template <typename T>
-hipError_t launch_b_r(const BatchJob* jobs, const DiscParams* params, const int2* items,
-                      int32_t n_items, const int32_t* n_items_dev, int32_t vpw, int radius,
-                      int lmax, int grid, int2* over, int32_t* over_count, int32_t* queue,
-                      unsigned char* mcc, int64_t mcc_cap, int32_t* mcc_count, hipStream_t st) {
-  if (radius == 1)
-    return launch_b<T, 1, 32>(jobs, params, items, n_items, n_items_dev, vpw, grid, over, over_count,
-                              queue, mcc, mcc_cap, mcc_count, st);
-  if (radius == 2)
-    return lmax <= 32 ? launch_b<T, 2, 32>(jobs, params, items, n_items, n_items_dev, vpw, grid, over,
-                                           over_count, queue, mcc, mcc_cap, mcc_count, st)
-                      : launch_b<T, 2, 64>(jobs, params, items, n_items, n_items_dev, vpw, grid, over,
-                                           over_count, queue, nullptr, 0, nullptr, st);
-  return lmax <= 32 ? launch_b<T, 3, 32>(jobs, params, items, n_items, n_items_dev, vpw, grid, over,
-                                         over_count, queue, mcc, mcc_cap, mcc_count, st)
-                    : launch_b<T, 3, 64>(jobs, params, items, n_items, n_items_dev, vpw, grid, over,
-                                         over_count, queue, nullptr, 0, nullptr, st);
-}
-
-template <typename T>
-int occ_b_r(int radius, int lmax, bool stash) {
-  if (radius == 1) return stash ? occ_b<T, 1, 32, true>() : occ_b<T, 1, 32, false>();
-  if (radius == 2)
-    return lmax > 32 ? occ_b<T, 2, 64, false>() : (stash ? occ_b<T, 2, 32, true>() : occ_b<T, 2, 32, false>());
-  return lmax > 32 ? occ_b<T, 3, 64, false>() : (stash ? occ_b<T, 3, 32, true>() : occ_b<T, 3, 32, false>());
-}
-
 template <typename T, int LMAX>
 int occ_f() {
   int nb = 0;
@@ -158,22 +130,6 @@ int occ_f() {
 }
 
 }  // namespace
-
-hipError_t launch_map_batch(const BatchJob* jobs, const DiscParams* params, const int2* items,
-                            int32_t n_items, const int32_t* n_items_dev, int32_t vpw, int dtype,
-                            int radius, int lmax, int grid, int2* over, int32_t* over_count,
-                            int32_t* queue, unsigned char* mcc, int64_t mcc_cap, int32_t* mcc_count,
-                            hipStream_t st) {
-  if (n_items <= 0 && !n_items_dev) return hipSuccess;
-  if (radius > 3)  // no stashing instances: the problems are solved in the kernel
-    return launch_map_batch_wide(jobs, params, items, n_items, n_items_dev, vpw, radius, lmax, grid, over,
-                                 over_count, queue, st);
-  if (dtype == 1)
-    return launch_b_r<int16_t>(jobs, params, items, n_items, n_items_dev, vpw, radius, lmax, grid,
-                               over, over_count, queue, mcc, mcc_cap, mcc_count, st);
-  return launch_b_r<float>(jobs, params, items, n_items, n_items_dev, vpw, radius, lmax, grid, over,
-                           over_count, queue, mcc, mcc_cap, mcc_count, st);
-}
 
 hipError_t launch_map_fused(const BatchJob* jobs, const DiscParams* params, const int2* items,
                             int32_t n_items, const int32_t* n_items_dev, int dtype, int lmax,
@@ -202,11 +158,6 @@ hipError_t launch_map_fused(const BatchJob* jobs, const DiscParams* params, cons
 int map_fused_blocks_per_cu(int dtype, int lmax) {
   if (dtype == 1) return lmax <= 32 ? occ_f<int16_t, 32>() : occ_f<int16_t, 64>();
   return lmax <= 32 ? occ_f<float, 32>() : occ_f<float, 64>();
-}
-
-int map_batch_blocks_per_cu(int dtype, int radius, int lmax, bool stash) {
-  if (radius > 3) return map_batch_wide_blocks_per_cu(radius, lmax);
-  return dtype == 1 ? occ_b_r<int16_t>(radius, lmax, stash) : occ_b_r<float>(radius, lmax, stash);
 }
 
 }  // namespace fr

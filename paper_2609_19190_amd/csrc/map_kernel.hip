@@ -1,4 +1,4 @@
-// Plain map kernels of radius 1..3, the MCC kernel and the staging transposes.
+// The MCC kernel, the staging transposes and the choice of a plain map kernel.
 #include "map_body.h"
 
 namespace fr {
@@ -26,13 +26,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
       mcc_wide(win, (1u << c) - 1u, fine);
     }
   }
-}
-
-template <typename T>
-hipError_t launch_r(const MapArgs& a, int radius, int lmax, bool debug, hipStream_t st) {
-  if (radius == 1) return launch_t<T, 1, 32>(a, debug, st);
-  if (radius == 2) return lmax <= 32 ? launch_t<T, 2, 32>(a, debug, st) : launch_t<T, 2, 64>(a, debug, st);
-  return lmax <= 32 ? launch_t<T, 3, 32>(a, debug, st) : launch_t<T, 3, 64>(a, debug, st);
 }
 
 // Tile transpose of the staging rows: 64 voxels x up to 96 maps per block
@@ -115,8 +108,27 @@ hipError_t launch_map(const MapArgs& a, int dtype, int radius, int lmax, bool de
   if (a.opt.glcm_dist != 1 || a.opt.gldm_alpha != 0 || a.opt.averaged)
     return launch_map_variant(a, radius, lmax, st);
   if (radius > 3) return launch_map_wide(a, radius, lmax, debug, st);
-  if (dtype == 1) return launch_r<int16_t>(a, radius, lmax, debug, st);
-  return launch_r<float>(a, radius, lmax, debug, st);
+  return dtype == 1 ? launch_map_i16(a, radius, lmax, debug, st) : launch_map_f32(a, radius, lmax, debug, st);
+}
+
+hipError_t launch_map_batch(const BatchJob* jobs, const DiscParams* params, const int2* items,
+                            int32_t n_items, const int32_t* n_items_dev, int32_t vpw, int dtype,
+                            int radius, int lmax, int grid, int2* over, int32_t* over_count,
+                            int32_t* queue, unsigned char* mcc, int64_t mcc_cap, int32_t* mcc_count,
+                            hipStream_t st) {
+  if (n_items <= 0 && !n_items_dev) return hipSuccess;
+  if (radius > 3)  // no stashing instances: the problems are solved in the kernel
+    return launch_map_batch_wide(jobs, params, items, n_items, n_items_dev, vpw, radius, lmax, grid, over,
+                                 over_count, queue, st);
+  auto f = dtype == 1 ? launch_map_batch_i16 : launch_map_batch_f32;
+  return f(jobs, params, items, n_items, n_items_dev, vpw, radius, lmax, grid, over, over_count, queue, mcc,
+           mcc_cap, mcc_count, st);
+}
+
+int map_batch_blocks_per_cu(int dtype, int radius, int lmax, bool stash) {
+  if (radius > 3) return map_batch_wide_blocks_per_cu(radius, lmax);
+  return dtype == 1 ? map_batch_i16_blocks_per_cu(radius, lmax, stash)
+                    : map_batch_f32_blocks_per_cu(radius, lmax, stash);
 }
 
 }  // namespace fr
