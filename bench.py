@@ -166,9 +166,12 @@ LIBRARY_MATCHES = True
 
 def kernel_source_hash() -> str:
     import hashlib
+    import re
     h = hashlib.sha256()
     for f in ("map_body.h", "map_device.h", "map_kernel.hip"):
-        h.update(open(os.path.join(ROOT, "paper_2609_19190_amd", "csrc", f), "rb").read())
+        src = open(os.path.join(ROOT, "paper_2609_19190_amd", "csrc", f)).read()
+        # the code: line comments and white space apart
+        h.update(re.sub(r"\s+", " ", re.sub(r"//[^\n]*", "", src)).encode())
     return h.hexdigest()[:16]
 
 

@@ -120,6 +120,9 @@ struct Smem {
   static constexpr int PS = 512;
   // words of the packed 16-bit upper triangle of the co-occurrence table
   static constexpr int kTriWords = (LMAX * (LMAX + 1) / 2 + 1) / 2;
+  // words of a level's 27 packed dependence counts: odd, so that lanes
+  // reading a row each meet no bank conflicts
+  static constexpr int kGldmWords = 15;
   static constexpr int SQ = S + 2;                                // padded cube side
   static constexpr int PC = (SQ * SQ * SQ + 3) / 4 * 4;
   uint8_t cl[CP];        // level per cube position (0: not in V)
@@ -155,7 +158,8 @@ struct Smem {
       uint32_t parent[CP]; // zone labels
       uint32_t zcnt[CP / 2];  // zone sizes at roots (16-bit, packed as the GLCM)
       uint32_t glrlm[LMAX * S];
-      uint32_t gldm[(LMAX * 27 + 1) / 2];  // 16-bit counts, packed
+      uint32_t gldm[LMAX * kGldmWords];  // 16-bit counts, packed, kGldmWords words a level
+      uint32_t dpl[28];                  // voxels per dependence
       uint32_t ngn[LMAX];
       unsigned long long ngS[LMAX];
       uint32_t zpl[LMAX];
@@ -1136,7 +1140,7 @@ struct Emph {
   double psi2j2;
   double invj2, invi2, invi2j2, i2invj2, j2invi2, clogc;
 };
-// One matrix entry: count c (at most 13 (2r+1)^3 < 2^24) at level value i
+// One matrix entry (its entropy term apart): count c (at most 13 (2r+1)^3 < 2^24) at level value i
 // (<= 255) and index j (run length, zone size or dependence count, <= 1331).
 // The sums of c, c i, c i^2, c j, c j^2 stay below 2^31 (at most 13|V| =
 // 17,303 entries, c i <= 4.5e6, c i^2 <= 1.2e9): 32-bit arithmetic, 24-bit
@@ -1149,7 +1153,7 @@ __device__ inline void emph_add(Emph& a, uint32_t c, int i, int j) {
   const uint32_t ui = (uint32_t)i, uj = (uint32_t)j;
   const uint32_t i2u = __umul24(ui, ui), j2u = __umul24(uj, uj);
   const double i2 = (double)i2u, j2 = (double)j2u;
-  const double ri2 = frcp(i2), rj2 = frcp(j2);
+  const double ri2 = kInvSq.v[ui], rj2 = kInvSq.v[uj];
   const uint32_t cis = __umul24(c, ui), cjs = __umul24(c, uj);
   a.pn += c;
   a.psi += cis;
@@ -1162,7 +1166,6 @@ __device__ inline void emph_add(Emph& a, uint32_t c, int i, int j) {
   a.invi2j2 += ci * ri2 * rj2;
   a.i2invj2 += ci * i2 * rj2;
   a.j2invi2 += ci * j2 * ri2;
-  if (c > 1) a.clogc += ci * flog2(ci);
 }
 // The integer sums fit in 32 bits (see emph_add); x1, x2: two more
 // per-lane integer partials (squared row / column totals, each total below
@@ -1187,10 +1190,74 @@ __device__ inline void emph_reduce(Emph& a, long long& x1, long long& x2) {
   a.clogc = vd[5];
   a.si2j2 = vd[6];
 }
+// The feature sums are VALU-issue bound.  Tables (map_device.h) for c log2 c
+// and 1 / n^2, run and dependence sums taken along rows instead of entry by
+// entry, and fewer wave reductions for the co-occurrence features: 12.1 k ->
+// 10.8 k VALU instructions a voxel and 22.4 -> 20.9 ms for the 1 M-voxel
+// radius-3 workload, 6.3 k -> 5.4 k and 1.39 -> 1.27 ms for the 100 k-voxel
+// radius-2 one.
+// The present level of a lane in a pass over a [level][size] table: with at
+// most 32 levels, the two halves of the wave share a level and take every
+// other column; with more, a lane takes the whole row.
+template <int LMAX>
+struct LevelRow {
+  static constexpr int H = LMAX <= 32 ? 2 : 1;  // lanes per level
+  int l, part;   // compact level; first column of the lane
+  bool ok;       // the level is present
+  uint32_t i;    // level value
+  double i2, ri2;  // i^2, 1 / i^2
+  __device__ LevelRow(const uint8_t* lval, int L, int lane) {
+    l = H == 2 ? lane & 31 : lane;
+    part = H == 2 ? lane >> 5 : 0;
+    ok = l < L;
+    i = ok ? lval[l] : 1u;
+    i2 = (double)__umul24(i, i);
+    ri2 = kInvSq.v[i];
+  }
+};
+// Sums over the columns of a lane's row (or half row).
+struct RowSums {
+  uint32_t n, j1, j2;  // of c, c j, c j^2
+  double invj2, clogc;  // of c / j^2, c log2 c
+};
+template <int R>
+__device__ inline void row_add(RowSums& r, uint32_t c, uint32_t j) {
+  r.n += c;
+  r.j1 += __umul24(c, j);
+  r.j2 += __umul24(c, __umul24(j, j));
+  r.invj2 = fma((double)c, kInvSq.v[j], r.invj2);
+  r.clogc += xlog2x<R>(c);
+}
+// The emphasis sums of the lane's entries: every one is a row sum times a
+// power of the level (the bounds are those of emph_add).
+template <int LMAX>
+__device__ inline void emph_rows(Emph& a, const RowSums& r, const LevelRow<LMAX>& lr) {
+  const double n = (double)r.n, j2 = (double)r.j2;
+  a.pn = r.n;
+  a.psi = __umul24(r.n, lr.i);
+  a.psi2 = __umul24(a.psi, lr.i);
+  a.psj = r.j1;
+  a.psj2 = r.j2;
+  a.psi2j2 = j2 * lr.i2;
+  a.invj2 = r.invj2;
+  a.invi2 = n * lr.ri2;
+  a.invi2j2 = r.invj2 * lr.ri2;
+  a.i2invj2 = r.invj2 * lr.i2;
+  a.j2invi2 = j2 * lr.ri2;
+  a.clogc = r.clogc;
+}
+// The row total of the lane's level (both halves of a split row).
+template <int LMAX>
+__device__ inline uint32_t row_total(uint32_t n) {
+  if constexpr (LMAX > 32) return n;
+  const auto r = __builtin_amdgcn_permlane32_swap((int)n, (int)n, false, false);
+  return (uint32_t)(r[0] + r[1]);
+}
+
 // The 16-value set shared by GLRLM and GLSZM: gln/rln are the sums of
 // squared row/column totals; units = Np (13|V| for runs) or Nv (|V|).
 template <typename O>
-__device__ inline void emph16(const Emph& a, long long gln, long long rln, double units, O* f) {
+__device__ inline void emph16(const Emph& a, long long gln, long long rln, double units, double nlogn, O* f) {
   const double N = (double)a.n;
   const double rN = 1.0 / N, rN2 = rN * rN;  // one division; the rest multiply
   f[0] = (O)(a.invj2 * rN);
@@ -1202,7 +1269,7 @@ __device__ inline void emph16(const Emph& a, long long gln, long long rln, doubl
   f[6] = (O)(N / units);
   f[7] = (O)((double)(a.n * a.si2 - a.si * a.si) * rN2);
   f[8] = (O)((double)(a.n * a.sj2 - a.sj * a.sj) * rN2);
-  f[9] = (O)(flog2(N) - a.clogc * rN);
+  f[9] = (O)((nlogn - a.clogc) * rN);  // nlogn = N log2 N
   f[10] = (O)(a.invi2 * rN);
   f[11] = (O)((double)a.si2 * rN);
   f[12] = (O)(a.invi2j2 * rN);
@@ -1215,31 +1282,39 @@ __device__ inline void emph16(const Emph& a, long long gln, long long rln, doubl
 template <int R, int MODE>
 constexpr bool kFineMcc = R > 3 || MODE != kPlain;
 
-// The 16 GLRLM maps of the counts glrlm [L][S] (compact level, run length - 1).
-template <int S, typename O>
-__device__ FR_INLINE inline void runs_features(const uint32_t* glrlm, const uint8_t* lval, int L, int lane,
+// The 16 GLRLM maps of the counts glrlm [L][S] (compact level, run length
+// - 1).  Rows by lane (LevelRow): the sums over a level's lengths first,
+// the level's powers once a row; a column that no level has is skipped.
+template <int R, int LMAX, typename O>
+__device__ FR_INLINE inline void runs_features(const uint32_t* glrlm, const LevelRow<LMAX>& lr, int L, int lane,
                                                double units, O* f) {
-  Emph er = {};
-  uint32_t nzb = 0;  // bit t: entry lane + 64 t is nonzero (L*S <= 704)
-  for (int t = 0; lane + 64 * t < L * S; ++t) nzb |= (glrlm[lane + 64 * t] != 0u) << t;
-  while (nzb) {
-    const int e = lane + 64 * (__ffs(nzb) - 1);
-    nzb &= nzb - 1;
-    emph_add(er, glrlm[e], lval[e / S], e % S + 1);
-  }
+  constexpr int S = 2 * R + 1, H = LevelRow<LMAX>::H, NT = (S + H - 1) / H;
+  RowSums rs = {};
   long long gln = 0, rln = 0;
-  if (lane < L) {
-    long long t = 0;
-    for (int j = 0; j < S; ++j) t += glrlm[lane * S + j];
-    gln = t * t;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int j = t * H + lr.part;
+    const uint32_t c = lr.ok && j < S ? glrlm[lr.l * S + j] : 0u;
+    if (__ballot(c != 0u) == 0ull) continue;
+    row_add<R>(rs, c, (uint32_t)j + 1u);
+    // the length's total over the levels: in the last lane of each half
+    // wave (H 2, one column per half) or of the wave
+    int v = (int)c;
+    v += __builtin_amdgcn_mov_dpp(v, 0xb1, 0xf, 0xf, true);
+    v += __builtin_amdgcn_mov_dpp(v, 0x4e, 0xf, 0xf, true);
+    v += __builtin_amdgcn_mov_dpp(v, 0x141, 0xf, 0xf, true);
+    v += __builtin_amdgcn_mov_dpp(v, 0x140, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    if constexpr (H == 1) v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    rln += (long long)v * v;
   }
-  if (lane < S) {
-    long long t = 0;
-    for (int l = 0; l < L; ++l) t += glrlm[l * S + lane];
-    rln = t * t;
-  }
+  rln = (H == 2 ? (lane & 31) == 31 : lane == 63) ? rln : 0;
+  const uint32_t tot = row_total<LMAX>(rs.n);
+  if (lr.part == 0) gln = (long long)tot * tot;
+  Emph er = {};
+  emph_rows(er, rs, lr);
   emph_reduce(er, gln, rln);
-  emph16(er, gln, rln, units, f);
+  emph16(er, gln, rln, units, xlog2x<R>((uint32_t)er.n), f);
 }
 
 template <typename T, int R, int LMAX, bool DEBUG, bool MOUT = false, int MODE = kPlain>
@@ -1328,7 +1403,8 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
   // clear the L-sized tables
   for (int e = lane; e < (L * (L + 1) / 2 + 1) / 2; e += 64) sm.u.a.glcm[e] = 0;
   for (int e = lane; e < L * S; e += 64) sm.u.a.glrlm[e] = 0;
-  for (int e = lane; e < (L * 27 + 1) / 2; e += 64) sm.u.a.gldm[e] = 0;
+  for (int e = lane; e < L * SM::kGldmWords; e += 64) sm.u.a.gldm[e] = 0;
+  if (lane < 28) sm.u.a.dpl[lane] = 0;
   if (lane < L) {
     sm.hist[lane] = 0;
     sm.pxc[lane] = 0;
@@ -1400,7 +1476,8 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
 #pragma unroll
           for (int n = 0; n < 26; ++n) dep += h[n] != 0 && abs(h[n] - g) <= a.opt.gldm_alpha;
         }
-        gadd(sm.u.a.gldm, l * 27 + dep, 1u);
+        gadd(sm.u.a.gldm, l * (2 * SM::kGldmWords) + dep, 1u);
+        atomicAdd(&sm.u.a.dpl[dep], 1u);
       }
       if (fNGTDM && cnt) {
         atomicAdd(&sm.u.a.ngn[l], 1u);
@@ -1559,6 +1636,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       if (fGLSZM) gadd(sm.u.a.zcnt, (int)sm.u.a.parent[c], 1u);
     }
   }
+  const LevelRow<LMAX> lrow(sm.lval, L, lane);
   // GLRLM averaged over the directions: each direction's runs counted and
   // reduced in turn; lane k < 16 keeps the sum of feature k
   double rl_acc = 0.0;
@@ -1590,7 +1668,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
           for (int e = lane; e < L * S; e += 64)
             a.d_glrlm[it * a.ng * S + (int64_t)(sm.lval[e / S] - 1) * S + e % S] += (int32_t)sm.u.a.glrlm[e];
         double f[16];
-        runs_features<S>(sm.u.a.glrlm, sm.lval, L, lane, (double)K, f);
+        runs_features<R>(sm.u.a.glrlm, lrow, L, lane, (double)K, f);
         double own = 0.0;
 #pragma unroll
         for (int k = 0; k < 16; ++k) own = lane == k ? f[k] : own;
@@ -1658,7 +1736,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     }
     for (int e = lane; e < L * 27; e += 64) {
       const int l = e / 27, j = e % 27;
-      a.d_gldm[it * ng * 27 + (int64_t)(sm.lval[l] - 1) * 27 + j] = (int32_t)gget(sm.u.a.gldm, e);
+      a.d_gldm[it * ng * 27 + (int64_t)(sm.lval[l] - 1) * 27 + j] = (int32_t)gget(sm.u.a.gldm, l * (2 * SM::kGldmWords) + j);
     }
     if (lane < L) {
       const int64_t o = it * ng + (sm.lval[lane] - 1);
@@ -1693,13 +1771,13 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     double ent = 0.0, uni = 0.0;
     if (lane < L) {
       const double p = (double)sm.hist[lane] * rKd;
-      ent = -p * flog2(p);
+      ent = xlog2x<R>(sm.hist[lane]);
       uni = p * p;
     }
     double r1[8] = {s1, s2, ent, uni, 0.0, 0.0, 0.0, 0.0};
     wsum8d(r1);
     const double S1 = r1[0], S2 = r1[1];
-    ent = r1[2];
+    ent = (xlog2x<R>((uint32_t)K) - r1[2]) * rKd;
     uni = r1[3];
     const double mu = S1 * rKd;
     const float* srt = (const float*)sm.u.a.same;  // sorted: the K values of V first
@@ -1784,7 +1862,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       if (lane < 16) F[oGLRLM + lane] = (float)(rl_acc / 13.0);
     } else {
       float f[16];
-      runs_features<S>(sm.u.a.glrlm, sm.lval, L, lane, 13.0 * Kd, f);
+      runs_features<R>(sm.u.a.glrlm, lrow, L, lane, 13.0 * Kd, f);
       if (lane < 16) F[oGLRLM + lane] = f[lane];
     }
   }
@@ -1794,10 +1872,9 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     double hl = 0.0;
     uint32_t nzb = 0;  // bit t: slot lane + 64 t holds a key (HT <= 256)
     for (int t = 0; lane + 64 * t < HT; ++t) nzb |= (gget(sm.u.a.hcnt, lane + 64 * t) != 0u) << t;
-    while (nzb) {  // only the occupied slots pay for a logarithm
-      const double c = (double)gget(sm.u.a.hcnt, lane + 64 * (__ffs(nzb) - 1));
+    while (nzb) {
+      hl += xlog2x<R>(gget(sm.u.a.hcnt, lane + 64 * (__ffs(nzb) - 1)));
       nzb &= nzb - 1;
-      hl += c * flog2(c);
     }
     ez.clogc = hl;  // zones count once each; the entropy term comes from the hash
     long long gln = 0, szn = 0;
@@ -1811,28 +1888,32 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     }
     emph_reduce(ez, gln, szn);
     float f[16];
-    emph16(ez, gln, szn, Kd, f);
+    emph16(ez, gln, szn, Kd, xlog2x<R>((uint32_t)ez.n), f);
     if (lane < 16) F[oGLSZM + lane] = f[lane];
   }
 
   // ---- GLDM -----------------------------------------------------------
   if (fGLDM) {
-    Emph ed = {};
-    uint32_t nzb = 0;  // bit t: entry lane + 64 t is nonzero (L*27 <= 1728)
-    for (int t = 0; lane + 64 * t < L * 27; ++t) nzb |= (gget(sm.u.a.gldm, lane + 64 * t) != 0u) << t;
-    while (nzb) {
-      const int e = lane + 64 * (__ffs(nzb) - 1);
-      nzb &= nzb - 1;
-      emph_add(ed, gget(sm.u.a.gldm, e), sm.lval[e / 27], e % 27 + 1);
+    // rows by lane, as the runs; two dependences a word
+    constexpr int H = LevelRow<LMAX>::H, NT = (14 + H - 1) / H;
+    RowSums rs = {};
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int w = t * H + lrow.part;
+      const uint32_t c = lrow.ok ? sm.u.a.gldm[lrow.l * SM::kGldmWords + w] : 0u;
+      if (__ballot(c != 0u) == 0ull) continue;
+      row_add<R>(rs, c & 0xffffu, 2u * w + 1u);
+      row_add<R>(rs, c >> 16, 2u * w + 2u);
     }
+    Emph ed = {};
+    emph_rows(ed, rs, lrow);
     long long gln = 0, dn = 0;
     if (lane < L) {
       const long long t = sm.hist[lane];
       gln = t * t;
     }
     if (lane < 27) {
-      long long t = 0;
-      for (int l = 0; l < L; ++l) t += gget(sm.u.a.gldm, l * 27 + lane);
+      const long long t = sm.u.a.dpl[lane];
       dn = t * t;
     }
     emph_reduce(ed, gln, dn);
@@ -1847,7 +1928,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       f[4] = (float)((double)dn * rN2);
       f[5] = (float)((double)(ed.n * ed.si2 - ed.si * ed.si) * rN2);
       f[6] = (float)((double)(ed.n * ed.sj2 - ed.sj * ed.sj) * rN2);
-      f[7] = (float)(flog2(N) - ed.clogc * rN);
+      f[7] = (float)((xlog2x<R>((uint32_t)ed.n) - ed.clogc) * rN);
       f[8] = (float)(ed.invi2 * rN);
       f[9] = (float)((double)ed.si2 * rN);
       f[10] = (float)(ed.invi2j2 * rN);
@@ -1893,7 +1974,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       for (int e0 = 0; e0 < npair; e0 += 64) {
         const int e = e0 + lane;
         if (e < npair) {
-          int jc = (int)((1.0f + sqrtf(8.0f * (float)e + 1.0f)) * 0.5f);
+          int jc = (int)((1.0f + __builtin_amdgcn_sqrtf(8.0f * (float)e + 1.0f)) * 0.5f);
           jc += (jc + 1) * jc / 2 <= e;  // exact: largest jc with jc (jc - 1) / 2 <= e
           jc -= jc * (jc - 1) / 2 > e;
           const int i = e - jc * (jc - 1) / 2;
@@ -1965,17 +2046,19 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     for (int e = lane; e < a.ng; e += 64) sm.u.c.pd[e] = 0;
     for (int e = lane; e <= 2 * a.ng; e += 64) sm.u.c.ps[e] = 0;
     __syncthreads();
-    long long rowc = 0, s1x = 0, s2x = 0;
+    uint32_t rowc = 0;
     double hxp = 0.0;
-    int lv = 0;
+    int ri[8] = {};  // N_P, sum i, sum i^2: totals below 2^31
     if (lane < L) {
       rowc = sm.pxc[lane];
-      lv = sm.lval[lane];
-      s1x = rowc * lv;
-      s2x = rowc * lv * lv;
-      if (rowc) hxp = (double)rowc * flog2((double)rowc);
+      const uint32_t lv = sm.lval[lane];
+      ri[0] = (int)rowc;
+      ri[1] = (int)__umul24(rowc, lv);
+      ri[2] = (int)__umul24((uint32_t)ri[1], lv);
+      hxp = xlog2x<R>(rowc);
     }
-    const long long NP = wsumi(rowc);
+    wsum8i(ri);
+    const long long NP = ri[0], S1x = ri[1], S2x = ri[2];
     if (NP == 0) {
       if constexpr (MODE != kAveraged) {
         if (lane < kNGLCM) F[oGLCM + lane] = NAN;
@@ -1985,26 +2068,26 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       const uint64_t presb = __ballot(lane < L && rowc > 0);
       const int nlev = __popcll(presb);
       const double Nd = (double)NP;
-      const double lgN = flog2(Nd);
+      const double nlogn = xlog2x<R>((uint32_t)NP);
       // entries of the upper triangle (r <= c), one per lane, enumerated
       // compactly (e = c (c + 1) / 2 + r); an entry off the diagonal stands
       // for the two symmetric ones (weight 2)
       const int ntri = L * (L + 1) / 2;
-      long long e2 = 0;
+      uint32_t e2 = 0;  // total at most N_P^2 = 8.1e8
       double plogp = 0.0;
       unsigned pmax = 0;
       for (int e0 = 0; e0 < ntri; e0 += 64) {
         const int e = e0 + lane;
         if (e < ntri) {
-          int c = (int)((sqrtf(8.0f * (float)e + 1.0f) - 1.0f) * 0.5f);
+          int c = (int)((__builtin_amdgcn_sqrtf(8.0f * (float)e + 1.0f) - 1.0f) * 0.5f);
           c += (c + 1) * (c + 2) / 2 <= e;  // exact floor of the root
           c -= c * (c + 1) / 2 > e;
           const int r = e - c * (c + 1) / 2;
           const uint32_t P = gget(sm.u.a.glcm, e);
           if (P) {
             const uint32_t w = r == c ? 1u : 2u;
-            e2 += (long long)(w * P) * P;
-            plogp += (double)w * ((double)P * flog2((double)P));
+            e2 += __umul24(w * P, P);
+            plogp = fma((double)w, xlog2x<R>(P), plogp);
             pmax = max(pmax, P);
             const int i = sm.lval[r], j = sm.lval[c];
             atomicAdd(&sm.u.c.pd[i > j ? i - j : j - i], w * P);
@@ -2012,19 +2095,12 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
           }
         }
       }
-      int gi[8] = {(int)s1x, (int)s2x, (int)e2, 0, 0, 0, 0, 0};  // totals below 2^31
-      wsum8i(gi);
-      const long long S1x = gi[0], S2x = gi[1];
-      e2 = gi[2];
-      double gd[8] = {hxp, plogp, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-      wsum8d(gd);
-      const double HX = lgN - gd[0] / Nd;
-      plogp = gd[1];
       pmax = wmaxu(pmax);
       __syncthreads();
       const int ng = a.ng;
       const double mu = (double)S1x / Nd;
-      long long sd1 = 0, sd2 = 0, ss1 = 0, ss2 = 0;
+      uint32_t sd1 = 0, sd2 = 0, ss1 = 0;
+      std::conditional_t<(R > 3), double, uint32_t> ss2 = 0;
       double dlog = 0, slog = 0, iv = 0, idm = 0, idmn = 0, id = 0, idn = 0, ct = 0, cs = 0, cp = 0;
       const double ngd = (double)ng;
       const double rng = 1.0 / ngd, rng2 = rng * rng;
@@ -2032,10 +2108,11 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
         const uint32_t c = sm.u.c.pd[k];
         if (c) {
           const double cd = (double)c, kd = (double)k;
-          sd1 += (long long)c * k;
-          sd2 += (long long)c * k * k;
-          dlog += cd * flog2(cd);
-          if (k > 0) iv += cd * frcp(kd * kd);
+          const uint32_t ck = __umul24(c, (uint32_t)k);
+          sd1 += ck;
+          sd2 += __umul24(ck, (uint32_t)k);
+          dlog += xlog2x<R>(c);
+          iv += cd * kInvSq.v[k];  // the table's entry 0 is 0
           idm += cd * frcp(1.0 + kd * kd);
           idmn += cd * frcp(1.0 + kd * kd * rng2);
           id += cd * frcp(1.0 + kd);
@@ -2046,9 +2123,13 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
         const uint32_t c = sm.u.c.ps[k];
         if (c) {
           const double cd = (double)c, t = (double)k - 2.0 * mu;
-          ss1 += (long long)c * k;
-          ss2 += (long long)c * k * k;
-          slog += cd * flog2(cd);
+          const uint32_t ck = __umul24(c, (uint32_t)k);
+          ss1 += ck;
+          if constexpr (R > 3)
+            ss2 += (double)ck * (double)k;
+          else
+            ss2 += __umul24(ck, (uint32_t)k);
+          slog += xlog2x<R>(c);
           ct += cd * t * t;
           cs += cd * t * t * t;
           cp += cd * t * t * t * t;
@@ -2057,13 +2138,9 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       // totals below 2^31: the largest, sum over i+j of c k^2, is at most
       // N_P (2 Ng)^2 = 6,516 x 510^2 = 1.7e9 for a 7^3 cube; above radius 3
       // (28,460 x 510^2 = 7.4e9) that one is summed in FP64, exactly
-      [[maybe_unused]] const long long ss2_lane = ss2;
-      int hi[8] = {(int)sd1, (int)sd2, (int)ss1, (int)ss2, 0, 0, 0, 0};
+      int hi[8] = {(int)sd1, (int)sd2, (int)ss1, R > 3 ? 0 : (int)ss2, (int)e2, 0, 0, 0};
       wsum8i(hi);
-      sd1 = hi[0];
-      sd2 = hi[1];
-      ss1 = hi[2];
-      ss2 = hi[3];
+      const long long Sd1 = hi[0], Sd2 = hi[1], Ss1 = hi[2], E2 = hi[4];
       double h1[8] = {dlog, slog, iv, idm, idmn, id, idn, ct};
       wsum8d(h1);
       dlog = h1[0];
@@ -2074,15 +2151,14 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       id = h1[5];
       idn = h1[6];
       ct = h1[7];
-      double h2[8] = {cs, cp, R > 3 ? (double)ss2_lane : 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+      double h2[8] = {cs, cp, R > 3 ? (double)ss2 : 0.0, hxp, plogp, 0.0, 0.0, 0.0};
       wsum8d(h2);
-      if constexpr (R > 3) ss2 = (long long)h2[2];
+      const long long Ss2 = R > 3 ? (long long)h2[2] : (long long)hi[3];
       cs = h2[0];
       cp = h2[1];
-      const long long sij = (ss2 - sd2) / 4;  // sum_ij i j P
-      const double N2 = Nd * Nd;
-      const double var = (double)(NP * S2x - S1x * S1x) / N2;
-      const double HXY = lgN - plogp / Nd;
+      const long long sij = (Ss2 - Sd2) / 4;  // sum_ij i j P
+      const double rNd = 1.0 / Nd, rN2 = rNd * rNd;  // one division; the rest multiply
+      const double HX = (nlogn - h2[3]) * rNd, HXY = (nlogn - h2[4]) * rNd;
 
       // MCC: spectral radius of B = D^-1/2 P D^-1/2 - v v^T over present levels
       double mcc = 1.0;
@@ -2159,7 +2235,6 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
         }
       }
 
-      const double rNd = 1.0 / Nd, rN2 = rNd * rNd;  // one division; the rest multiply
       if (lane == 0) {
         // a feature of this pass: its map, or one term of its mean
         auto put = [&](int k, double v) FR_INLINE {
@@ -2168,36 +2243,36 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
           else
             F[oGLCM + k] = (float)v;
         };
-        put(0, ((double)sij * rNd));
+        put(0, (double)sij * rNd);
         put(1, mu);
-        put(2, (cp * rNd));
-        put(3, (cs * rNd));
-        put(4, (ct * rNd));
-        put(5, ((double)sd2 * rNd));
+        put(2, cp * rNd);
+        put(3, cs * rNd);
+        put(4, ct * rNd);
+        put(5, (double)Sd2 * rNd);
         put(6, nlev <= 1 ? 1.0
                          : ((double)(NP * sij - S1x * S1x) / (double)(NP * S2x - S1x * S1x)));
-        put(7, ((double)sd1 * rNd));
-        put(8, (lgN - dlog * rNd));
-        put(9, ((double)(NP * sd2 - sd1 * sd1) * rN2));
-        put(10, ((double)e2 * rN2));
+        put(7, (double)Sd1 * rNd);
+        put(8, (nlogn - dlog) * rNd);
+        put(9, (double)(NP * Sd2 - Sd1 * Sd1) * rN2);
+        put(10, (double)E2 * rN2);
         put(11, HXY);
         put(12, nlev <= 1 ? 0.0 : ((HXY - 2.0 * HX) / HX));
         const double t = 1.0 - exp(-2.0 * (2.0 * HX - HXY));
         put(13, sqrt(t > 0.0 ? t : 0.0));
-        put(14, (idm * rNd));
+        put(14, idm * rNd);
         if constexpr (MODE == kAveraged) {
           if (nlev <= 1) av->mcc[pass] = 1.0;
         } else {
           put(15, mcc);
         }
-        put(16, (idmn * rNd));
-        put(17, (id * rNd));
-        put(18, (idn * rNd));
-        put(19, (iv * rNd));
-        put(20, ((double)pmax * rNd));
-        put(21, ((double)ss1 * rNd));
-        put(22, (lgN - slog * rNd));
-        put(23, var);
+        put(16, idmn * rNd);
+        put(17, id * rNd);
+        put(18, idn * rNd);
+        put(19, iv * rNd);
+        put(20, (double)pmax * rNd);
+        put(21, (double)Ss1 * rNd);
+        put(22, (nlogn - slog) * rNd);
+        put(23, (double)(NP * S2x - S1x * S1x) * rN2);
       }
     }
     if constexpr (MODE == kAveraged) {  // one flush site for the pending problems of the directions so far

@@ -79,5 +79,52 @@ __device__ inline double flog2(double x) {
   return fma(s * t, k2OverLn2, (double)e);
 }
 
+// Tables of the integer arguments that the feature sums take: a load that
+// the vector cache serves in place of the instructions of a logarithm
+// (about 28) or a reciprocal (6).
+template <int N>
+struct Table {
+  double v[N];
+};
+// log2 of c >= 1 for the table: c = m 2^e, m in [1, 2), halved above sqrt 2,
+// then the series of flog2 to s^31 (its remainder is below 1e-26).
+constexpr double table_log2(unsigned c) {
+  int e = 0;
+  while ((c >> (e + 1)) != 0u) ++e;
+  double m = (double)c / (double)(1u << e);
+  if (m > 1.4142135623730951) {
+    m *= 0.5;
+    ++e;
+  }
+  const double s = (m - 1.0) / (m + 1.0), s2 = s * s;
+  double t = 0.0;
+  for (int k = 31; k >= 1; k -= 2) t = t * s2 + 1.0 / k;
+  return (double)e + s * t * 2.8853900817779268;  // 2 / ln 2
+}
+// c log2 c for every count of a neighbourhood of radius 3 or less (the
+// largest, the co-occurrence total of a full 7^3 cube, is 6,516).
+constexpr int kXLogN = 6528;
+constexpr Table<kXLogN> make_xlog2x() {
+  Table<kXLogN> t{};
+  for (int c = 2; c < kXLogN; ++c)
+    t.v[c] = (c & 1) ? c * table_log2(c) : 2.0 * t.v[c / 2] + c;  // 2k log2 2k = 2 (k log2 k) + 2k, exact scaling
+  return t;
+}
+__device__ const Table<kXLogN> kXLog2X = make_xlog2x();
+// 1 / n^2 for levels and run, zone and dependence sizes (at most 11^3).
+constexpr int kInvSqN = 1332;
+constexpr Table<kInvSqN> make_inv_sq() {
+  Table<kInvSqN> t{};
+  for (int c = 1; c < kInvSqN; ++c) t.v[c] = 1.0 / ((double)c * c);
+  return t;
+}
+__device__ const Table<kInvSqN> kInvSq = make_inv_sq();
+// c log2 c of a count of a radius-R neighbourhood (0 for c = 0).
+template <int R>
+__device__ inline double xlog2x(uint32_t c) {
+  if constexpr (R <= 3) return kXLog2X.v[c];
+  return c < (uint32_t)kXLogN ? kXLog2X.v[c] : (double)c * flog2((double)c);
+}
+
 }  // namespace
 }  // namespace fr
