@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include <stdint.h>
 
 namespace fr {
 namespace {
@@ -21,18 +22,31 @@ __constant__ unsigned long long kLcmOver[27] = {
 constexpr double kLcm26 = 26771144400.0;
 constexpr double kRcpLcm26 = 1.0 / kLcm26;
 
-// 13 forward neighbour offsets (dx, dy, dz), one of each +/- pair; bit d of
+// 13 forward neighbour offsets (dx, dy, dz), one of each +/- pair, each the
+// larger cube index of its pair; bit d of
 // the equal-level mask is forward direction d, bit 13 + d its opposite.
+// Ordered by how many of the other opposites are neighbours of a direction's
+// opposite: the zone pass takes the first equal-level one and skips those
+// its zone already holds (kDirCover).
 __host__ __device__ constexpr int fdx(int d) {
-  return d == 0 ? 1 : d == 1 ? 0 : d == 2 ? 0 : d == 3 ? 1 : d == 4 ? -1 : d == 5 ? 1
-       : d == 6 ? -1 : d == 7 ? 0 : d == 8 ? 0 : d == 9 ? 1 : d == 10 ? -1 : d == 11 ? 1 : -1;
+  return d == 2 ? 1 : d == 5 ? 1 : d == 6 ? -1 : d == 7 ? 1 : d == 8 ? -1 : d == 9 ? 1 : d == 10 ? -1
+       : d == 11 ? 1 : d == 12 ? -1 : 0;
 }
 __host__ __device__ constexpr int fdy(int d) {
-  return d == 0 ? 0 : d == 1 ? 1 : d == 2 ? 0 : d == 3 ? 1 : d == 4 ? 1 : d == 5 ? 0
-       : d == 6 ? 0 : d == 7 ? 1 : d == 8 ? -1 : d == 9 ? 1 : d == 10 ? 1 : d == 11 ? -1 : -1;
+  return d == 1 ? 1 : d == 3 ? 1 : d == 4 ? -1 : d == 7 ? 1 : d == 8 ? 1 : d == 9 ? 1 : d == 10 ? 1
+       : d == 11 ? -1 : d == 12 ? -1 : 0;
 }
 __host__ __device__ constexpr int fdz(int d) {
-  return d == 0 ? 0 : d == 1 ? 0 : d == 2 ? 1 : d == 3 ? 0 : d == 4 ? 0 : 1;
+  return d == 0 ? 1 : d == 1 || d == 2 ? 0 : d <= 6 ? 1 : d <= 8 ? 0 : 1;
+}
+// Bit n: the opposites of directions d and n are neighbours (or the same).
+__host__ __device__ constexpr uint32_t dir_cover(int d) {
+  uint32_t m = 0;
+  for (int n = 0; n < 13; ++n) {
+    const int x = fdx(n) - fdx(d), y = fdy(n) - fdy(d), z = fdz(n) - fdz(d);
+    if (x >= -1 && x <= 1 && y >= -1 && y <= 1 && z >= -1 && z <= 1) m |= 1u << n;
+  }
+  return m;
 }
 // The same offsets as a table, for a direction known only at run time.
 __constant__ signed char kDir[13][3] = {
@@ -41,6 +55,9 @@ __constant__ signed char kDir[13][3] = {
     {fdx(6), fdy(6), fdz(6)},    {fdx(7), fdy(7), fdz(7)},    {fdx(8), fdy(8), fdz(8)},
     {fdx(9), fdy(9), fdz(9)},    {fdx(10), fdy(10), fdz(10)}, {fdx(11), fdy(11), fdz(11)},
     {fdx(12), fdy(12), fdz(12)}};
+__constant__ uint32_t kDirCover[13] = {dir_cover(0), dir_cover(1), dir_cover(2),  dir_cover(3),  dir_cover(4),
+                                       dir_cover(5), dir_cover(6), dir_cover(7),  dir_cover(8),  dir_cover(9),
+                                       dir_cover(10), dir_cover(11), dir_cover(12)};
 __host__ __device__ constexpr int ndx(int n) { return n < 13 ? fdx(n) : -fdx(n - 13); }
 __host__ __device__ constexpr int ndy(int n) { return n < 13 ? fdy(n) : -fdy(n - 13); }
 __host__ __device__ constexpr int ndz(int n) { return n < 13 ? fdz(n) : -fdz(n - 13); }

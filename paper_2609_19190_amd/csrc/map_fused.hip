@@ -17,13 +17,6 @@ union FusedSmem {
   Smem<3, LMAX, MOUT> s3;
 };
 
-template <int R, int LMAX, bool MOUT>
-__device__ FR_INLINE inline void fused_layout(Smem<R, LMAX, MOUT>& sm) {
-  if (threadIdx.x < Smem<R, LMAX, MOUT>::LVW) ((uint32_t*)sm.lflag)[threadIdx.x] = 0u;
-  for (int e = threadIdx.x; e < Smem<R, LMAX, MOUT>::PC / 4; e += 64) ((uint32_t*)sm.clp)[e] = 0u;
-  __syncthreads();
-}
-
 template <typename T, int LMAX>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LMAX == 32 ? 3 : 2))) void k_map_fused(
     const BatchJob* __restrict__ jobs, const DiscParams* __restrict__ params,
@@ -100,11 +93,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LMAX == 32 ?
       flush(true);
       if (!more) break;
       if (R == 1) {
-        if constexpr (LMAX == 32) fused_layout(sm.s1);
+        if constexpr (LMAX == 32) smem_layout(sm.s1);
       } else if (R == 2) {
-        fused_layout(sm.s2);
+        smem_layout(sm.s2);
       } else {
-        fused_layout(sm.s3);
+        smem_layout(sm.s3);
       }
       cur = R;
     }
