@@ -51,6 +51,7 @@ struct Pool {
   int64_t cap_blocks = 0;
   fr::DiscParams* params = nullptr;
   fr::DiscParams* host_params = nullptr;  // pinned
+  int32_t* counts = nullptr;              // counter block of the map passes
   float* stage = nullptr;                 // voxel-major map staging rows
   int64_t cap_stage = 0;                  // rows
   int2* over[2] = {nullptr, nullptr};     // overflow lists of the 32- and 64-level passes
@@ -75,6 +76,10 @@ fr_status pool_get(int64_t nvox, Pool** out) {
   std::lock_guard<std::mutex> lk(g_pool_mu);
   if ((int)g_pools.size() <= dev) g_pools.resize(dev + 1);
   Pool& p = g_pools[dev];
+  if (!p.counts && hipMalloc((void**)&p.counts, fr::kCountInts * sizeof(int32_t)) != hipSuccess) {
+    p.counts = nullptr;
+    return fail(FR_E_NOMEM, "hipMalloc of the pass counters failed");
+  }
   if (!p.params) {
     if (hipMalloc((void**)&p.params, sizeof(fr::DiscParams)) != hipSuccess)
       return fail(FR_E_NOMEM, "hipMalloc of the parameter block failed");
@@ -277,6 +282,7 @@ fr_status enqueue_discretise(const void* volume, int32_t dtype, int32_t nx, int3
   s.block_min = p->block_min;
   s.block_max = p->block_max;
   s.params = p->params;
+  s.counts = p->counts;
   return enqueue_discretise_into(volume, dtype, nx, ny, nz, mask, mode, value, lower, levels,
                                  p->list, s, expect_count, st);
 }
@@ -374,7 +380,8 @@ fr_status read_options(const fr_map_options* in, fr::MapOptions* o) {
 
 // Device buffers of the map passes of one call.
 struct PassBuffers {
-  fr::DiscParams* params;  // the call's parameter block (overflow counters inside)
+  fr::DiscParams* params;  // the call's parameter block
+  int32_t* counts;         // its counter block
   int2* over[2];           // overflow lists (n_items entries each)
   void* gscratch;          // generic-kernel scratch: generic_grid slices
   int generic_grid;
@@ -394,26 +401,27 @@ fr_status enqueue_map_passes(fr::MapArgs a, int32_t dtype, int32_t radius, int l
   a.items = nullptr;
   a.items_count = nullptr;
   a.over = pb.over[0];
-  a.over_count = &pb.params->n_over[0];
+  a.over_count = pb.counts + fr::kCntOver0;
   a.over_job = 0;
+  a.part_n = a.n_items;
+  a.key0 = 0;
   a.mcc = debug || !default_options(a.opt) ? nullptr : pb.mcc;  // the variants solve theirs in the kernel
-  a.mcc_cap = a.n_items;
-  a.mcc_count = pb.params->n_mcc;
+  a.mcc_count = pb.counts;
   HIP_TRY(fr::launch_map(a, dtype, radius, 32, debug, stream));
   if (radius >= 2 && lcap > 32) {
     // the 64-level instance stashes its problems with <= 32 levels in the
     // same stash (a voxel reaches one pass only) and solves wider ones
     fr::MapArgs b = a;
     b.items = pb.over[0];
-    b.items_count = &pb.params->n_over[0];
+    b.items_count = pb.counts + fr::kCntOver0;
     b.over = pb.over[1];
-    b.over_count = &pb.params->n_over[1];
+    b.over_count = pb.counts + fr::kCntOver1;
     HIP_TRY(fr::launch_map(b, dtype, radius, 64, debug, stream));
     if (lcap > 64)
-      HIP_TRY(fr::launch_map_generic(a, nullptr, nullptr, pb.over[1], &pb.params->n_over[1], 0,
+      HIP_TRY(fr::launch_map_generic(a, nullptr, nullptr, pb.over[1], pb.counts + fr::kCntOver1, a.part_n,
                                      dtype, pb.gscratch, lcap, pb.generic_grid, stream));
   }
-  if (a.mcc) HIP_TRY(fr::launch_mcc(pb.params->n_mcc, &pb.params->err, a.mcc, a.mcc_cap, radius > 3, stream));
+  if (a.mcc) HIP_TRY(fr::launch_mcc(pb.counts, &pb.params->err, a.mcc, a.part_n, radius > 3, stream));
   return FR_OK;
 }
 
@@ -529,7 +537,7 @@ fr_status map_common(const void* volume, int32_t dtype, int32_t nx, int32_t ny, 
     return st;
   if (!debug && default_options(opt) && (st = pool_mcc(p, n_items)) != FR_OK)
     return st;
-  const PassBuffers pb = {p->params, {p->over[0], p->over[1]}, p->gscratch, fr::kGenericGrid,
+  const PassBuffers pb = {p->params, p->counts, {p->over[0], p->over[1]}, p->gscratch, fr::kGenericGrid,
                           debug ? nullptr : p->mcc};
   std::pair<hipEvent_t, hipEvent_t> ev;
   if (prof && (st = prof_begin(stream, &ev)) != FR_OK) return st;
@@ -587,7 +595,8 @@ NoAllocLayout noalloc_layout(int64_t nvox, int64_t n_mask, bool staged, size_t g
 // The allocation-free entry point's scratch: one array per device that
 // loads the library, held until the process ends.  Host code uses only the
 // address hipGetSymbolAddress returns for the current device.
-static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
+// Past the documented size: the counter block of the passes.
+static __device__ __align__(256) unsigned char scratch[kNoAllocBytes + fr::kCountInts * sizeof(int32_t)];
 
 namespace {
 
@@ -764,9 +773,10 @@ fr_status fr_map_noalloc(const void* volume, int32_t dtype, int32_t nx, int32_t 
   ds.block_min = (double*)(base + L.bmin);
   ds.block_max = (double*)(base + L.bmax);
   ds.params = (fr::DiscParams*)(base + L.params);
-  // the scan kernel writes the whole parameter block (error state, counters
-  // and queues at zero) before any later kernel reads it: nothing else of
-  // the previous call's contents is read
+  ds.counts = (int32_t*)(base + kNoAllocBytes);
+  // the scan kernel writes the whole parameter block and zeroes the counters
+  // before any later kernel reads them: nothing else of the previous call's
+  // contents is read
   uint8_t* levels = base + L.levels;
   int32_t* list = (int32_t*)(base + L.list);
   if ((st = enqueue_discretise_into(volume, dtype, nx, ny, nz, mask, disc_mode, disc_value,
@@ -792,7 +802,7 @@ fr_status fr_map_noalloc(const void* volume, int32_t dtype, int32_t nx, int32_t 
   a.voxel_volume = spacing_mm[0] * spacing_mm[1] * spacing_mm[2];
   a.radius = kernel_radius;
   a.opt = opt;
-  const PassBuffers pb = {ds.params, {(int2*)(base + L.over0), (int2*)(base + L.over1)},
+  const PassBuffers pb = {ds.params, ds.counts, {(int2*)(base + L.over0), (int2*)(base + L.over1)},
                           gbytes ? (void*)(base + L.gscratch) : nullptr, kNoAllocGenericGrid,
                           nullptr};
   if ((st = enqueue_map_passes(a, dtype, kernel_radius, lcap, false, pb, stream)) != FR_OK) return st;

@@ -107,7 +107,6 @@ struct Group {
   bool need_generic = false;  // some job may hold more than 64
   int grid32 = 0, grid64 = 0;
 };
-constexpr int kGroupCounters = 4;  // two overflow counts, two work-queue heads
 
 int32_t map_count_of(uint32_t fam) {
   static const int cnt[6] = {18, 24, 16, 16, 14, 5};
@@ -143,12 +142,12 @@ struct fr_batch_s {
   int32_t* d_lists = nullptr;
   float* d_stage = nullptr;
   int2* d_tr_items = nullptr;
-  // per group: two overflow counts and two work-queue heads; then the two
-  // MCC stash counts; then per wide variant what a group has
+  // a counter block per group, one for the MCC stash, then one per wide
+  // variant
   int32_t* d_counters = nullptr;
   void* d_gscratch = nullptr;     // generic-kernel scratch
-  // MCC problems of the 32-level passes (one per fixed-radius voxel at
-  // most), solved by one k_mcc launch
+  // MCC problems of the fused passes (one per voxel of radius 1..3 at most:
+  // cap_mcc), solved by one k_mcc launch
   unsigned char* d_mcc = nullptr;
   int64_t cap_mcc = 0;
   Group groups[2];                // FR_I16, FR_F32
@@ -277,19 +276,19 @@ fr_status build_items(fr_batch_s* b) {
   return FR_OK;
 }
 
-int32_t* group_counters(fr_batch_s* b, int gi) { return b->d_counters + kGroupCounters * gi; }
-// The two MCC stash counts, after the groups' counters.
-int32_t* mcc_counts(fr_batch_s* b) { return b->d_counters + kGroupCounters * 2; }
+int32_t* group_counters(fr_batch_s* b, int gi) { return b->d_counters + fr::kCountInts * gi; }
+// The MCC stash's counters, after the groups'.
+int32_t* mcc_counts(fr_batch_s* b) { return b->d_counters + fr::kCountInts * 2; }
 // The counters of wide variant w (at most four: two raw types, radii 4, 5).
-int32_t* wide_counters(fr_batch_s* b, int w) { return b->d_counters + kGroupCounters * (2 + w) + 2; }
-constexpr int kCounters = kGroupCounters * 6 + 2;
+int32_t* wide_counters(fr_batch_s* b, int w) { return b->d_counters + fr::kCountInts * (3 + w); }
+constexpr int kCounters = fr::kCountInts * 7;
 
 // The fused first pass of group gi over n items of its list.
 fr_status enqueue_first(fr_batch_s* b, int gi, int32_t n, hipStream_t st) {
   Group& g = b->groups[gi];
   int32_t* c = group_counters(b, gi);
   BHIP(fr::launch_map_fused(b->d_jobs, b->d_params, g.d_items, n, nullptr, g.dtype, 32, g.grid32, g.d_over[0],
-                            c, c + 2, b->d_mcc, b->cap_mcc, mcc_counts(b), st));
+                            c + fr::kCntOver0, c + fr::kCntQueue0, b->d_mcc, b->cap_mcc, mcc_counts(b), st));
   return FR_OK;
 }
 
@@ -301,6 +300,7 @@ fr_status enqueue(fr_batch_s* b, hipStream_t st) {
   s.block_min = b->d_bmin;
   s.block_max = b->d_bmax;
   s.params = b->d_params;
+  s.counts = nullptr;
   BHIP(fr::launch_zero_i32(b->d_counters, kCounters, st));
   BHIP(fr::launch_discretise_batch(b->d_jobs, (int32_t)b->jobs.size(), b->d_seg_job, b->n_seg, s, st));
   fr_status e;
@@ -310,8 +310,8 @@ fr_status enqueue(fr_batch_s* b, hipStream_t st) {
     Group& g = b->groups[gi];
     if (!g.need64) continue;
     int32_t* c = group_counters(b, gi);
-    BHIP(fr::launch_map_fused(b->d_jobs, b->d_params, g.d_over[0], 0, c, g.dtype, 64, g.grid64, g.d_over[1],
-                              c + 1, c + 3, b->d_mcc, b->cap_mcc, mcc_counts(b), st));
+    BHIP(fr::launch_map_fused(b->d_jobs, b->d_params, g.d_over[0], 0, c + fr::kCntOver0, g.dtype, 64, g.grid64,
+                              g.d_over[1], c + fr::kCntOver1, c + fr::kCntQueue1, b->d_mcc, b->cap_mcc, mcc_counts(b), st));
   }
   BHIP(fr::launch_mcc(mcc_counts(b), nullptr, b->d_mcc, b->cap_mcc, false, st));
   fr::MapArgs none;
@@ -319,20 +319,22 @@ fr_status enqueue(fr_batch_s* b, hipStream_t st) {
   for (int gi = 0; gi < 2; ++gi) {  // and more than 64
     Group& g = b->groups[gi];
     if (!g.need_generic) continue;
-    BHIP(fr::launch_map_generic(none, b->d_jobs, b->d_params, g.d_over[1], group_counters(b, gi) + 1, 0,
-                                g.dtype, b->d_gscratch, b->lcap_generic, fr::kGenericGrid, st));
+    BHIP(fr::launch_map_generic(none, b->d_jobs, b->d_params, g.d_over[1],
+                                group_counters(b, gi) + fr::kCntOver1, b->cap_mcc, g.dtype, b->d_gscratch, b->lcap_generic, fr::kGenericGrid, st));
   }
   for (auto& v : b->variants) {
     if (!v.wide) continue;
     int32_t* c = wide_counters(b, v.widx);
     BHIP(fr::launch_map_batch(b->d_jobs, b->d_params, v.d_items, v.n_items, nullptr, 1, v.dtype, v.radius, 32,
-                              v.grid32, v.d_over[0], c, c + 2, nullptr, 0, nullptr, st));
+                              v.grid32, v.d_over[0], c + fr::kCntOver0, c + fr::kCntQueue0, nullptr, v.n_vox, nullptr,
+                              st));
     if (v.lcap <= 32) continue;
-    BHIP(fr::launch_map_batch(b->d_jobs, b->d_params, v.d_over[0], 0, c, 1, v.dtype, v.radius, 64, v.grid64,
-                              v.d_over[1], c + 1, c + 3, nullptr, 0, nullptr, st));
+    BHIP(fr::launch_map_batch(b->d_jobs, b->d_params, v.d_over[0], 0, c + fr::kCntOver0, 1, v.dtype, v.radius, 64,
+                              v.grid64, v.d_over[1], c + fr::kCntOver1, c + fr::kCntQueue1, nullptr, v.n_vox,
+                              nullptr, st));
     if (v.lcap <= 64) continue;
-    BHIP(fr::launch_map_generic(none, b->d_jobs, b->d_params, v.d_over[1], c + 1, 0, v.dtype, b->d_gscratch,
-                                b->lcap_generic, fr::kGenericGrid, st));
+    BHIP(fr::launch_map_generic(none, b->d_jobs, b->d_params, v.d_over[1], c + fr::kCntOver1, v.n_vox, v.dtype,
+                                b->d_gscratch, b->lcap_generic, fr::kGenericGrid, st));
   }
   BHIP(fr::launch_transpose_batch(b->d_jobs, b->d_params, b->d_tr_items, (int32_t)b->tr_items.size(),
                                   st));
@@ -476,6 +478,7 @@ fr_status fr_batch_prepare(fr_batch b, const fr_job* jobs, int32_t n_jobs) {
   drop_graph(b);
   free_workspace(b);
   b->prepared = false;
+  b->cap_mcc = 0;
   b->jobs.assign(jobs, jobs + n_jobs);
   b->bj.assign(n_jobs, fr::BatchJob{});
   int64_t seg = 0, vox = 0, mvox = 0;
@@ -513,6 +516,11 @@ fr_status fr_batch_prepare(fr_batch b, const fr_job* jobs, int32_t n_jobs) {
     Variant& v = b->variants[it->second];
     v.jobs.push_back(j);
     v.lcap = std::max(v.lcap, lcap);
+    // numbers of the job's positions: within its variant's lists (wide), or
+    // within the lists and the stash that all other jobs share
+    int64_t& base = v.wide ? v.n_vox : b->cap_mcc;
+    B.key0 = (int32_t)(base % fr::kParts);
+    if (!v.wide) b->cap_mcc += J.n_mask;
     v.n_vox += J.n_mask;
   }
   for (auto& v : b->variants) {
@@ -538,7 +546,6 @@ fr_status fr_batch_prepare(fr_batch b, const fr_job* jobs, int32_t n_jobs) {
       g.n_vox += v.n_vox;
       g.need64 = g.need64 || (v.radius >= 2 && v.lcap > 32);
       g.need_generic = g.need_generic || (v.radius >= 2 && v.lcap > 64);
-      b->cap_mcc += v.n_vox;
     }
   }
   b->n_seg = seg;
@@ -574,7 +581,8 @@ fr_status fr_batch_prepare(fr_batch b, const fr_job* jobs, int32_t n_jobs) {
   }
   for (auto& g : b->groups) {
     if (g.variants.empty()) continue;
-    if (!dal((void**)&g.d_over[0], sizeof(int2) * g.n_vox) || !dal((void**)&g.d_over[1], sizeof(int2) * g.n_vox)) {
+    if (!dal((void**)&g.d_over[0], sizeof(int2) * b->cap_mcc) ||
+        !dal((void**)&g.d_over[1], sizeof(int2) * b->cap_mcc)) {
       free_workspace(b);
       return bfail(FR_E_NOMEM, "overflow-list allocation failed");
     }

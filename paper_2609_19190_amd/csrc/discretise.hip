@@ -72,6 +72,7 @@ __global__ __launch_bounds__(kDiscThreads) void k_disc_stats(const T* __restrict
 }
 
 constexpr int kScanThreads = 1024;
+static_assert(kScanThreads == kCountInts, "the scan zeroes a counter block, one counter a thread");
 
 // Exclusive scan of the counts of segments [s0, s0 + nb), the VOI min/max
 // and the gray-level count, written to *P (one block of kScanThreads).
@@ -140,12 +141,6 @@ __device__ inline void disc_scan_range(int64_t s0, int64_t nb, const int32_t* bc
     p.xmax = mx;
     p.count = carry;
     p.err = 0;
-    p.n_over[0] = 0;
-    p.n_over[1] = 0;
-    p.queue[0] = 0;
-    p.queue[1] = 0;
-    p.n_mcc[0] = 0;
-    p.n_mcc[1] = 0;
     if (mode == 2) {  // fixed bin number: Ng given
       p.lo = mn;
       p.ng = (int32_t)value;
@@ -167,7 +162,9 @@ __global__ __launch_bounds__(kScanThreads) void k_disc_scan(int64_t nb, const in
                                                             const double* bmin,
                                                             const double* bmax, int64_t* boff,
                                                             DiscParams* P, int mode, double value,
-                                                            double lower, int64_t expect_count) {
+                                                            double lower, int64_t expect_count,
+                                                            int32_t* counts) {
+  if (counts) counts[threadIdx.x] = 0;
   disc_scan_range(0, nb, bcount, bmin, bmax, boff, P, mode, value, lower, expect_count);
 }
 
@@ -253,7 +250,9 @@ __global__ __launch_bounds__(kDiscThreads) void k_bdisc_stats(const BatchJob* __
 __global__ __launch_bounds__(kScanThreads) void k_bdisc_scan(const BatchJob* __restrict__ jobs,
                                                              const int32_t* bcount,
                                                              const double* bmin, const double* bmax,
-                                                             int64_t* boff, DiscParams* params) {
+                                                             int64_t* boff, DiscParams* params,
+                                                             int32_t* counts) {
+  if (counts) counts[threadIdx.x] = 0;  // a single job's
   const BatchJob& J = jobs[blockIdx.x];
   disc_scan_range(J.seg_base, J.nseg, bcount, bmin, bmax, boff, &params[blockIdx.x], J.mode,
                   J.value, J.lower, J.n_mask);
@@ -289,7 +288,7 @@ hipError_t launch_discretise_batch(const BatchJob* jobs, int32_t n_jobs, const i
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_bdisc_scan, dim3((unsigned)n_jobs), dim3(kScanThreads), 0, st, jobs,
-                     s.block_count, s.block_min, s.block_max, s.block_offset, s.params);
+                     s.block_count, s.block_min, s.block_max, s.block_offset, s.params, s.counts);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_bdisc_levels, dim3((unsigned)n_seg), dim3(kDiscThreads), 0, st, jobs, seg_job,
@@ -313,7 +312,7 @@ hipError_t launch_discretise(const void* vol, int dtype, int64_t nvox, const uin
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_disc_scan, dim3(1), dim3(kScanThreads), 0, st, (int64_t)s.nblocks,
                      s.block_count, s.block_min, s.block_max, s.block_offset, s.params, mode,
-                     value, lower, expect_count);
+                     value, lower, expect_count, s.counts);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (dtype == 1) {

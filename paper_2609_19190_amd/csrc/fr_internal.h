@@ -18,15 +18,26 @@ struct DiscParams {
   int64_t count;    // number of mask voxels
   int32_t ng;       // VOI gray-level count
   int32_t err;      // kJob* code: nonzero stops every later kernel of the job
-  // entries appended to the two overflow lists of a single-job map (voxels
-  // with more present levels than the 32- and 64-level instances hold) and
-  // two work-queue heads; all zeroed by the discretisation scan
-  int32_t n_over[2];
-  int32_t queue[2];
-  // MCC problems stashed by a single-job map for the MCC kernel: those with
-  // at most 16 and with 17..32 present levels
-  int32_t n_mcc[2];
 };
+
+// Lists that map kernels append to (overflow lists, the MCC stash) and work
+// queues are split in kParts partitions, one counter each on a cache line of
+// its own: returning atomics on one address complete about one per 12 ns on
+// this GPU whatever the grid, which alone had bound the map kernel of a
+// 100 k-voxel radius-2 map (1.25 -> 0.94 ms with partitions) and the 32-level
+// pass of a CT that hands every voxel on (0.70 ms of 60 k voxels).  Position m goes to partition (m + key0) mod
+// kParts, so a list of at most n positions, numbered 0 .. n - 1, has a fixed
+// place for each partition: [part_base(n, p), part_base(n, p + 1)).
+constexpr int kParts = 32;
+constexpr int kPartStride = 32;                      // ints between two counters of a kind
+constexpr int kCountInts = kParts * kPartStride;     // a counter block
+// The kinds of counter in a block: counter k of partition p is
+// block[p * kPartStride + k].
+enum { kCntNarrow = 0, kCntWide = 1, kCntOver0 = 2, kCntOver1 = 3, kCntQueue0 = 4, kCntQueue1 = 5 };
+__host__ __device__ inline int64_t part_base(int64_t n, int p) {
+  const int64_t r = n % kParts;
+  return p * (n / kParts) + (p < r ? p : r);
+}
 
 // Segment of the volume handled by one discretisation block.
 constexpr int kDiscThreads = 256;
@@ -40,6 +51,7 @@ struct DiscScratch {
   double* block_min;      // [nblocks]
   double* block_max;      // [nblocks]
   DiscParams* params;     // [1]
+  int32_t* counts;        // a counter block to zero (kCountInts), or NULL
 };
 
 // Enqueue the three discretisation kernels: block statistics, block scan +
@@ -78,12 +90,16 @@ struct MapArgs {
   int32_t count;            // maps per voxel (fr_map_count(families))
   double voxel_volume;
   int64_t nblk;             // workgroups; b takes [b n / nblk, (b + 1) n / nblk)
-  // optional item list (a previous pass's overflow): item k is position
-  // items[k].y, with *items_count entries (read on the device)
+  // positions that the partitioned lists are laid out for, and this job's
+  // first one (modulo kParts)
+  int64_t part_n;
+  int32_t key0;
+  // optional item list (a previous pass's overflow, partitioned): its
+  // entries' .y are positions; items_count: its counters
   const int2* items;
   const int32_t* items_count;
   // where a voxel with more present levels than the instance holds goes:
-  // (over_job, position) appended at over[atomicAdd(over_count, 1)]
+  // (over_job, position) appended to its partition of over
   int2* over;
   int32_t* over_count;
   int32_t over_job;
@@ -92,9 +108,9 @@ struct MapArgs {
   // optional MCC stash (the 32- and 64-level instances write each
   // neighbourhood's MCC problem of <= 32 levels there for the MCC kernel
   // instead of solving it in LDS):
-  // room for mcc_cap problems of kMccProblemBytes, counted in *mcc_count
+  // room for part_n problems of kMccProblemBytes, counted in the block
+  // mcc_count
   unsigned char* mcc;
-  int64_t mcc_cap;
   int32_t* mcc_count;
   // debug matrix dump (all null in production)
   int32_t* d_glcm;
@@ -132,7 +148,7 @@ struct BatchJob {
   int32_t seg_base, nseg;
   MapOptions opt;
   int32_t vpw;         // voxels per work item of the job (fused batch pass)
-  int32_t reserved;
+  int32_t key0;        // number of its first position in the batch's partitioned lists, modulo kParts
 };
 
 // Error codes a job can raise on the device (DiscParams::err).
@@ -146,35 +162,36 @@ hipError_t launch_discretise_batch(const BatchJob* jobs, int32_t n_jobs, const i
 // Persistent batched map kernel for one (dtype, radius) variant, radius 1..5,
 // on the instance with lmax (32 or 64) local levels: items[w] = (job, first
 // compact index), vpw voxels each (items NULL: a single job, jobs[0], item
-// w starting at voxel w * vpw); with n_items_dev set, the item count is
-// read on the device.  A voxel with more than lmax present levels is
-// appended as (job, voxel) to over[*over_count] (radius >= 2).  With queue
-// set (a zeroed counter), workgroups take items dynamically from it, so
-// kernels running side by side balance; otherwise item w goes to
-// workgroup w mod grid.  With mcc set (lmax 32), the MCC problems go to
-// that stash of mcc_cap problems (counts in mcc_count[0..1]) and
-// launch_mcc must follow.
+// w starting at voxel w * vpw); with items_count set, items is a partitioned
+// list of an earlier pass with these counters.  A voxel with more than lmax
+// present levels is appended as (job, voxel) to over, counted in over_count
+// (radius >= 2).  With queue set (zeroed counters of a block), workgroups
+// take items dynamically from its partitions; otherwise (host-made items
+// only) item w goes to workgroup w mod grid.  With mcc set (lmax 32), the
+// MCC problems go to that stash (counter block mcc_count) and launch_mcc
+// must follow.  part_n: positions the lists and the stash are laid out for.
 hipError_t launch_map_batch(const BatchJob* jobs, const DiscParams* params, const int2* items,
-                            int32_t n_items, const int32_t* n_items_dev, int32_t vpw, int dtype,
+                            int32_t n_items, const int32_t* items_count, int32_t vpw, int dtype,
                             int radius, int lmax, int grid, int2* over, int32_t* over_count,
-                            int32_t* queue, unsigned char* mcc, int64_t mcc_cap, int32_t* mcc_count,
+                            int32_t* queue, unsigned char* mcc, int64_t part_n, int32_t* mcc_count,
                             hipStream_t st);
 
 // launch_map_batch's kernels of radius 1..3 by raw type and their occupancy.
 hipError_t launch_map_batch_i16(const BatchJob* jobs, const DiscParams* params, const int2* items, int32_t n_items,
-                                const int32_t* n_items_dev, int32_t vpw, int radius, int lmax, int grid, int2* over,
-                                int32_t* over_count, int32_t* queue, unsigned char* mcc, int64_t mcc_cap,
+                                const int32_t* items_count, int32_t vpw, int radius, int lmax, int grid, int2* over,
+                                int32_t* over_count, int32_t* queue, unsigned char* mcc, int64_t part_n,
                                 int32_t* mcc_count, hipStream_t st);
 int map_batch_i16_blocks_per_cu(int radius, int lmax, bool stash);
 hipError_t launch_map_batch_f32(const BatchJob* jobs, const DiscParams* params, const int2* items, int32_t n_items,
-                                const int32_t* n_items_dev, int32_t vpw, int radius, int lmax, int grid, int2* over,
-                                int32_t* over_count, int32_t* queue, unsigned char* mcc, int64_t mcc_cap,
+                                const int32_t* items_count, int32_t vpw, int radius, int lmax, int grid, int2* over,
+                                int32_t* over_count, int32_t* queue, unsigned char* mcc, int64_t part_n,
                                 int32_t* mcc_count, hipStream_t st);
 int map_batch_f32_blocks_per_cu(int radius, int lmax, bool stash);
 // launch_map_batch's kernels of radius 4 and 5 (no stash) and their occupancy.
 hipError_t launch_map_batch_wide(const BatchJob* jobs, const DiscParams* params, const int2* items,
-                                 int32_t n_items, const int32_t* n_items_dev, int32_t vpw, int radius, int lmax,
-                                 int grid, int2* over, int32_t* over_count, int32_t* queue, hipStream_t st);
+                                 int32_t n_items, const int32_t* items_count, int32_t vpw, int radius, int lmax,
+                                 int grid, int2* over, int32_t* over_count, int32_t* queue, int64_t part_n,
+                                 hipStream_t st);
 int map_batch_wide_blocks_per_cu(int radius, int lmax);
 
 // Fused batched pass over the jobs of every fixed radius (1..3) of one raw
@@ -182,14 +199,14 @@ int map_batch_wide_blocks_per_cu(int radius, int lmax);
 // the radius), taken from a work queue.  lmax 32: items[w] = (job, first
 // compact index), jobs[job].vpw voxels each; the MCC problems go to the
 // stash (launch_mcc must follow); a neighbourhood with more than 32 present
-// levels is appended as (job, voxel) to over[*over_count].  lmax 64:
+// levels is appended as (job, voxel) to over.  lmax 64:
 // items are (job, voxel) pairs (an earlier pass's overflow, count read on
 // the device), radius 2 or 3, MCC problems with <= 32 levels stashed as
 // well, wider ones solved in the kernel; more than 64 levels go to over.  grid: resident workgroups (map_fused_blocks_per_cu).
 hipError_t launch_map_fused(const BatchJob* jobs, const DiscParams* params, const int2* items,
-                            int32_t n_items, const int32_t* n_items_dev, int dtype, int lmax,
+                            int32_t n_items, const int32_t* items_count, int dtype, int lmax,
                             int grid, int2* over, int32_t* over_count, int32_t* queue,
-                            unsigned char* mcc, int64_t mcc_cap, int32_t* mcc_count, hipStream_t st);
+                            unsigned char* mcc, int64_t part_n, int32_t* mcc_count, hipStream_t st);
 int map_fused_blocks_per_cu(int dtype, int lmax);
 
 // Generic map kernel: any radius 1..kGenericMaxRadius, up to 255 present
@@ -203,14 +220,13 @@ size_t generic_scratch_bytes(int lcap);
 // Workgroups of a generic launch (each takes one scratch slice).
 constexpr int kGenericGrid = 256;
 // Single job (a, its params and list; a.opt, a.radius and a.count set) or
-// batch (jobs != NULL: item (job, voxel)); items / n_items_dev as
-// launch_map_batch (items NULL with jobs NULL: every voxel 0 .. n_items-1
-// of the single job).  scratch holds grid slices of
-// generic_scratch_bytes(lcap); every neighbourhood mapped has at most lcap
-// present levels (lcap >= min(Ng, (2r+1)^3)).
+// batch (jobs != NULL: item (job, voxel)), over a partitioned list with the
+// counters items_count, laid out for part_n positions.  scratch holds grid
+// slices of generic_scratch_bytes(lcap); every neighbourhood mapped has at
+// most lcap present levels (lcap >= min(Ng, (2r+1)^3)).
 hipError_t launch_map_generic(const MapArgs& a, const BatchJob* jobs, const DiscParams* params,
-                              const int2* items, const int32_t* n_items_dev, int32_t n_items,
-                              int dtype, void* scratch, int lcap, int grid, hipStream_t st);
+                              const int2* items, const int32_t* items_count, int64_t part_n, int dtype,
+                              void* scratch, int lcap, int grid, hipStream_t st);
 // Resident workgroups per CU of a batched map variant (occupancy; stash:
 // the instance that stashes its MCC problems).
 int map_batch_blocks_per_cu(int dtype, int radius, int lmax, bool stash);
@@ -235,13 +251,13 @@ hipError_t launch_map_wide(const MapArgs& a, int radius, int lmax, bool debug, h
 hipError_t launch_map_variant(const MapArgs& a, int radius, int lmax, hipStream_t st);
 hipError_t launch_map_averaged(const MapArgs& a, int radius, int lmax, hipStream_t st);
 
-// The MCC of every problem in a stash of cap problems (device counts
-// n_mcc[0..1]: problems with <= 16 levels from the stash's start, wider
+// The MCC of every problem in a stash laid out for part_n positions (counter
+// block counts: problems with <= 16 levels from a partition's start, wider
 // ones from its end), written to each problem's output address; nothing
 // when *err (if err is set) holds a job error.  fine: to the finer search
 // width (the problems of radii 4 and 5).
-hipError_t launch_mcc(const int32_t* n_mcc, const int32_t* err, const unsigned char* stash,
-                      int64_t cap, bool fine, hipStream_t st);
+hipError_t launch_mcc(const int32_t* counts, const int32_t* err, const unsigned char* stash,
+                      int64_t part_n, bool fine, hipStream_t st);
 // out[k * n + m] = stage[m * kStageStride + k] for k < count, m < n (nothing
 // when params->err is set).
 hipError_t launch_transpose(const float* stage, float* out, int64_t n, int count,

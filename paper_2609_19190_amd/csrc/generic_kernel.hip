@@ -1009,8 +1009,8 @@ template <typename T>
 __global__ __launch_bounds__(NT) void k_map_generic(MapArgs one, const BatchJob* __restrict__ jobs,
                                                     const DiscParams* __restrict__ params,
                                                     const int2* __restrict__ items,
-                                                    const int32_t* __restrict__ n_items_dev,
-                                                    int32_t n_items_host, char* scratch,
+                                                    const int32_t* __restrict__ items_count,
+                                                    int64_t part_n, char* scratch,
                                                     size_t per_wg, int lcap) {
   __shared__ GSmem sm;
   const int t = threadIdx.x;
@@ -1018,11 +1018,15 @@ __global__ __launch_bounds__(NT) void k_map_generic(MapArgs one, const BatchJob*
   __syncthreads();
   const GLayout lay = glayout(lcap);
   char* slice = scratch + (size_t)blockIdx.x * per_wg;
-  const int64_t n = n_items_dev ? (int64_t)*n_items_dev : (int64_t)n_items_host;
-  const int64_t i0 = (int64_t)blockIdx.x * n / gridDim.x;
-  const int64_t i1 = ((int64_t)blockIdx.x + 1) * n / gridDim.x;
-  for (int64_t k = i0; k < i1; ++k) {
-    const int2 item = items ? items[k] : make_int2(0, (int)k);
+  // the partitions of the list over the workgroups: several workgroups to
+  // a partition, or several partitions to one
+  const int grid = (int)gridDim.x, pstep = grid < kParts ? grid : kParts;
+  for (int p = (int)blockIdx.x % pstep; p < kParts; p += pstep) {
+  const int per = grid < kParts ? 1 : (grid - p + kParts - 1) / kParts;
+  const int n = items_count[p * kPartStride];
+  const int2* list = items + part_base(part_n, p);
+  for (int k = (int)blockIdx.x / pstep; k < n; k += per) {
+    const int2 item = list[k];
     MapArgs a;
     if (jobs) {
       const DiscParams* P = &params[item.x];
@@ -1041,6 +1045,7 @@ __global__ __launch_bounds__(NT) void k_map_generic(MapArgs one, const BatchJob*
     }
     gmap_voxel<T>(sm, a, a.list[m], it, slice, lcap, lay);
   }
+  }
 }
 
 }  // namespace
@@ -1048,17 +1053,16 @@ __global__ __launch_bounds__(NT) void k_map_generic(MapArgs one, const BatchJob*
 size_t generic_scratch_bytes(int lcap) { return glayout(lcap < 1 ? 1 : lcap).total; }
 
 hipError_t launch_map_generic(const MapArgs& a, const BatchJob* jobs, const DiscParams* params,
-                              const int2* items, const int32_t* n_items_dev, int32_t n_items,
-                              int dtype, void* scratch, int lcap, int grid, hipStream_t st) {
-  if (!n_items_dev && n_items <= 0) return hipSuccess;
+                              const int2* items, const int32_t* items_count, int64_t part_n, int dtype,
+                              void* scratch, int lcap, int grid, hipStream_t st) {
   if (lcap < 1 || lcap > 255 || grid < 1) return hipErrorInvalidValue;
   const size_t scratch_per_wg = generic_scratch_bytes(lcap);
   if (dtype == 1)
     hipLaunchKernelGGL(k_map_generic<int16_t>, dim3((unsigned)grid), dim3(NT), 0, st, a, jobs, params,
-                       items, n_items_dev, n_items, (char*)scratch, scratch_per_wg, lcap);
+                       items, items_count, part_n, (char*)scratch, scratch_per_wg, lcap);
   else
     hipLaunchKernelGGL(k_map_generic<float>, dim3((unsigned)grid), dim3(NT), 0, st, a, jobs, params,
-                       items, n_items_dev, n_items, (char*)scratch, scratch_per_wg, lcap);
+                       items, items_count, part_n, (char*)scratch, scratch_per_wg, lcap);
   return hipGetLastError();
 }
 

@@ -1420,7 +1420,10 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
   }
   if constexpr (C > LMAX) {
     if (L > LMAX) {  // more present levels than these tables hold: a wider pass maps it
-      if (lane == 0) a.over[atomicAdd(a.over_count, 1)] = make_int2(a.over_job, (int)it);
+      if (lane == 0) {
+        const int p = (int)(it + a.key0) % kParts;
+        a.over[part_base(a.part_n, p) + atomicAdd(&a.over_count[p * kPartStride], 1)] = make_int2(a.over_job, (int)it);
+      }
       return;
     }
   }
@@ -2227,18 +2230,19 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
             }
           };
           if constexpr (MOUT) {
-            // problems with <= 16 levels fill the stash from its start,
-            // wider ones from its end (one problem per voxel at most, so
-            // the two never meet)
+            // problems with <= 16 levels fill the voxel's partition of the
+            // stash from its start, wider ones from its end (one problem per
+            // voxel at most, so the two never meet)
             const bool small = n <= 16;
+            const int p = (int)(it + a.key0) % kParts;
             int slot = 0;
-            if (lane == 0) slot = atomicAdd(&a.mcc_count[small ? 0 : 1], 1);
-            slot = __shfl(slot, 0);
+            if (lane == 0) slot = atomicAdd(&a.mcc_count[p * kPartStride + (small ? kCntNarrow : kCntWide)], 1);
+            slot = __builtin_amdgcn_readfirstlane(slot);
             if (small) {
-              McSmall* q = (McSmall*)a.mcc + slot;
+              McSmall* q = (McSmall*)(a.mcc + part_base(a.part_n, p) * kMccProblemBytes) + slot;
               stash(q->g, &q->dst, &q->n);
             } else {
-              McProblem* q = (McProblem*)(a.mcc + a.mcc_cap * kMccProblemBytes) - (slot + 1);
+              McProblem* q = (McProblem*)(a.mcc + part_base(a.part_n, p + 1) * kMccProblemBytes) - (slot + 1);
               stash(q->g, &q->dst, &q->n);
             }
           } else {
@@ -2363,13 +2367,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MOUT && LMAX
   smem_layout(sm);
   int ns = 0, nq = 0;  // deferred MCC problems in sm.ms and sm.mq
   bool big = false;    // a problem with > 32 levels pending
-  // balanced partition (n < 2^31): the counts differ by at most one; with
-  // an item list, n is the list's length as the previous pass left it
-  const int64_t n = a.items ? (int64_t)*a.items_count : a.n_items;
-  const int64_t i0 = (int64_t)blockIdx.x * n / a.nblk;
-  const int64_t i1 = ((int64_t)blockIdx.x + 1) * n / a.nblk;
-  for (int64_t k = i0; k < i1; ++k) {
-    const int64_t it = a.items ? (int64_t)a.items[k].y : k;
+  // balanced shares of the voxels (n < 2^31): the counts differ by at most
+  // one; of an item list, workgroup b takes every per-th entry of partition
+  // b mod kParts, as the previous pass left it (launch_i: nblk >= kParts)
+  int64_t k = (int64_t)blockIdx.x * a.n_items / a.nblk, kend = ((int64_t)blockIdx.x + 1) * a.n_items / a.nblk;
+  int64_t kstep = 1;
+  const int2* items = nullptr;
+  if (a.items) {
+    const int p = (int)blockIdx.x % kParts;
+    items = a.items + part_base(a.part_n, p);
+    kend = a.items_count[p * kPartStride];
+    k = (int)blockIdx.x / kParts;
+    kstep = (a.nblk - p + kParts - 1) / kParts;
+  }
+  for (; k < kend; k += kstep) {
+    const int64_t it = items ? (int64_t)items[k].y : k;
     const int64_t m = dbg ? a.sample[it] : it;
     if (m < 0 || m >= a.n_list) {  // out-of-range sample index: NaN maps, no matrices
       for (int q = threadIdx.x; q < 93; q += 64)
@@ -2384,7 +2396,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MOUT && LMAX
     } else if constexpr (!MOUT) {
       // one flush site (the flush code is large): after a voxel with more
       // than 32 levels, when a pool is full, and after the last voxel
-      const bool last = k + 1 == i1;
+      const bool last = k + kstep >= kend;
       const int fs = (ns == kSmallSlots<R, LMAX> || last) ? ns : 0;
       const int fq = (nq == kMcSlots<R, LMAX> || last) ? nq : 0;
       if (big || fs || fq) {
@@ -2445,7 +2457,7 @@ int resident_t() {
 template <typename T, int R, int LMAX, bool DEBUG, bool MOUT, int MODE = kPlain>
 hipError_t launch_i(MapArgs a, hipStream_t st) {
   const int resident = resident_t<T, R, LMAX, DEBUG, MOUT, MODE>();
-  a.nblk = a.items ? resident : plain_blocks(a.n_items, resident, MOUT || MODE == kAveraged ? 1 : 4);
+  a.nblk = a.items ? (resident > kParts ? resident : kParts) : plain_blocks(a.n_items, resident, MOUT || MODE == kAveraged ? 1 : 4);
   hipLaunchKernelGGL((k_map<T, R, LMAX, DEBUG, MOUT, MODE>), dim3((unsigned)a.nblk), dim3(64), 0, st, a);
   return hipGetLastError();
 }
@@ -2476,15 +2488,33 @@ hipError_t launch_v(const MapArgs& a, int radius, int lmax, hipStream_t st) {
   }
 }
 
+// The next item of a workgroup from the partitioned queue: of a host-made
+// list of n_items (item w in partition w mod kParts, so that the list's order
+// is kept across them), or of an earlier pass's partitioned list (counts).
+// p: the workgroup's partition, left: how many it has not found empty yet;
+// an exhausted one is left for the next.  -1 once all are.
+__device__ inline int64_t take_item(int32_t* queue, const int32_t* counts, int64_t part_n, int32_t n_items, int& p,
+                                    int& left) {
+  for (; left > 0; --left, p = (p + 1) % kParts) {
+    const int n = counts ? counts[p * kPartStride] : (n_items - p + kParts - 1) / kParts;
+    int q = n;
+    if (threadIdx.x == 0 &&
+        __hip_atomic_load(&queue[p * kPartStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n)
+      q = atomicAdd(&queue[p * kPartStride], 1);
+    q = __builtin_amdgcn_readfirstlane(q);
+    if (q < n) return counts ? part_base(part_n, p) + q : (int64_t)q * kParts + p;
+  }
+  return -1;
+}
+
 template <typename T, int R, int LMAX, bool MOUT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MOUT && R <= 3 ? 3 : 2))) void k_map_batch(
     const BatchJob* __restrict__ jobs, const DiscParams* __restrict__ params,
-    const int2* __restrict__ items, int32_t n_items_host, const int32_t* __restrict__ n_items_dev,
+    const int2* __restrict__ items, int32_t n_items_host, const int32_t* __restrict__ items_count,
     int32_t vpw, int2* over, int32_t* over_count, int32_t* queue, unsigned char* mcc,
-    int64_t mcc_cap, int32_t* mcc_count) {
+    int64_t part_n, int32_t* mcc_count) {
   static_assert(!MOUT || LMAX == 32, "stash only from the 32-level instance");
   __shared__ Smem<R, LMAX, MOUT> sm;
-  const int32_t n_items = n_items_dev ? *n_items_dev : n_items_host;
   smem_layout(sm);
   int ns = 0, nq = 0;  // deferred MCC problems in sm.ms and sm.mq
   bool big = false;    // a problem with > 32 levels pending
@@ -2492,19 +2522,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MOUT && R <=
   // next item of the queue (dynamic); one loop over their voxels, so that
   // the flush has a single site
   int64_t w = (int64_t)blockIdx.x - (int64_t)gridDim.x;
+  int part = (int)blockIdx.x % kParts, left = kParts;
+  bool more = true;
   int64_t m = 0, m1 = 0;
   MapArgs a;
   const BatchJob* J = nullptr;
   for (;;) {
     while (m >= m1) {  // next item of a job without error
       if (queue) {
-        int q = 0;
-        if (threadIdx.x == 0) q = atomicAdd(queue, 1);
-        w = __shfl(q, 0);
+        w = take_item(queue, items_count, part_n, n_items_host, part, left);
+        more = w >= 0;
       } else {
         w += gridDim.x;
+        more = w < n_items_host;
       }
-      if (w >= n_items) break;
+      if (!more) break;
       // no item table: one job (index 0), item w starts at voxel w * vpw
       const int2 it2 = items ? items[w] : make_int2(0, w * vpw);
       const DiscParams& P = params[it2.x];
@@ -2538,13 +2570,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MOUT && R <=
       a.radius = J->radius;
       a.opt = J->opt;
       a.mcc = mcc;
-      a.mcc_cap = mcc_cap;
+      a.part_n = part_n;
+      a.key0 = J->key0;
       a.mcc_count = mcc_count;
       m = it2.y;
       m1 = (int64_t)it2.y + vpw;
       if (m1 > J->n_mask) m1 = J->n_mask;
     }
-    const bool more = w < n_items;
     if (more) {
       map_voxel<T, R, LMAX, false, MOUT>(sm, a, a.list[m], m, ns, nq, big);
       ++m;
@@ -2565,18 +2597,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MOUT && R <=
 
 template <typename T, int R, int LMAX>
 hipError_t launch_b(const BatchJob* jobs, const DiscParams* params, const int2* items,
-                    int32_t n_items, const int32_t* n_items_dev, int32_t vpw, int grid, int2* over,
-                    int32_t* over_count, int32_t* queue, unsigned char* mcc, int64_t mcc_cap,
+                    int32_t n_items, const int32_t* items_count, int32_t vpw, int grid, int2* over,
+                    int32_t* over_count, int32_t* queue, unsigned char* mcc, int64_t part_n,
                     int32_t* mcc_count, hipStream_t st) {
   if constexpr (LMAX == 32) {
     if (mcc) {
       hipLaunchKernelGGL((k_map_batch<T, R, 32, true>), dim3((unsigned)grid), dim3(64), 0, st, jobs, params,
-                         items, n_items, n_items_dev, vpw, over, over_count, queue, mcc, mcc_cap, mcc_count);
+                         items, n_items, items_count, vpw, over, over_count, queue, mcc, part_n, mcc_count);
       return hipGetLastError();
     }
   }
   hipLaunchKernelGGL((k_map_batch<T, R, LMAX, false>), dim3((unsigned)grid), dim3(64), 0, st, jobs, params,
-                     items, n_items, n_items_dev, vpw, over, over_count, queue, nullptr, (int64_t)0,
+                     items, n_items, items_count, vpw, over, over_count, queue, nullptr, part_n,
                      nullptr);
   return hipGetLastError();
 }
@@ -2593,21 +2625,21 @@ int occ_b() {
 
 template <typename T>
 hipError_t launch_b_r(const BatchJob* jobs, const DiscParams* params, const int2* items,
-                      int32_t n_items, const int32_t* n_items_dev, int32_t vpw, int radius,
+                      int32_t n_items, const int32_t* items_count, int32_t vpw, int radius,
                       int lmax, int grid, int2* over, int32_t* over_count, int32_t* queue,
-                      unsigned char* mcc, int64_t mcc_cap, int32_t* mcc_count, hipStream_t st) {
+                      unsigned char* mcc, int64_t part_n, int32_t* mcc_count, hipStream_t st) {
   if (radius == 1)
-    return launch_b<T, 1, 32>(jobs, params, items, n_items, n_items_dev, vpw, grid, over, over_count,
-                              queue, mcc, mcc_cap, mcc_count, st);
+    return launch_b<T, 1, 32>(jobs, params, items, n_items, items_count, vpw, grid, over, over_count,
+                              queue, mcc, part_n, mcc_count, st);
   if (radius == 2)
-    return lmax <= 32 ? launch_b<T, 2, 32>(jobs, params, items, n_items, n_items_dev, vpw, grid, over,
-                                           over_count, queue, mcc, mcc_cap, mcc_count, st)
-                      : launch_b<T, 2, 64>(jobs, params, items, n_items, n_items_dev, vpw, grid, over,
-                                           over_count, queue, nullptr, 0, nullptr, st);
-  return lmax <= 32 ? launch_b<T, 3, 32>(jobs, params, items, n_items, n_items_dev, vpw, grid, over,
-                                         over_count, queue, mcc, mcc_cap, mcc_count, st)
-                    : launch_b<T, 3, 64>(jobs, params, items, n_items, n_items_dev, vpw, grid, over,
-                                         over_count, queue, nullptr, 0, nullptr, st);
+    return lmax <= 32 ? launch_b<T, 2, 32>(jobs, params, items, n_items, items_count, vpw, grid, over,
+                                           over_count, queue, mcc, part_n, mcc_count, st)
+                      : launch_b<T, 2, 64>(jobs, params, items, n_items, items_count, vpw, grid, over,
+                                           over_count, queue, nullptr, part_n, nullptr, st);
+  return lmax <= 32 ? launch_b<T, 3, 32>(jobs, params, items, n_items, items_count, vpw, grid, over,
+                                         over_count, queue, mcc, part_n, mcc_count, st)
+                    : launch_b<T, 3, 64>(jobs, params, items, n_items, items_count, vpw, grid, over,
+                                         over_count, queue, nullptr, part_n, nullptr, st);
 }
 
 template <typename T>

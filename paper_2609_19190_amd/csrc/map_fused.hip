@@ -20,12 +20,12 @@ union FusedSmem {
 template <typename T, int LMAX>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LMAX == 32 ? 3 : 2))) void k_map_fused(
     const BatchJob* __restrict__ jobs, const DiscParams* __restrict__ params,
-    const int2* __restrict__ items, int32_t n_items_host, const int32_t* __restrict__ n_items_dev,
-    int2* over, int32_t* over_count, int32_t* queue, unsigned char* mcc, int64_t mcc_cap,
+    const int2* __restrict__ items, int32_t n_items_host, const int32_t* __restrict__ items_count,
+    int2* over, int32_t* over_count, int32_t* queue, unsigned char* mcc, int64_t part_n,
     int32_t* mcc_count) {
   constexpr bool MOUT = true;  // problems with <= 32 levels go to the stash
   __shared__ FusedSmem<LMAX, MOUT> sm;
-  const int32_t n_items = n_items_dev ? *n_items_dev : n_items_host;
+  int part = (int)blockIdx.x % kParts, left = kParts;
   int cur = 0;         // radius whose layout the LDS holds (0: none yet)
   int ns = 0, nq = 0;  // deferred MCC problems (64-level form)
   bool big = false;
@@ -46,10 +46,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LMAX == 32 ?
   for (;;) {
     int R = cur;
     while (m >= m1) {  // next item of a job without error
-      int q = 0;
-      if (threadIdx.x == 0) q = atomicAdd(queue, 1);
-      const int w = __shfl(q, 0);
-      if (w >= n_items) break;
+      const int64_t w = take_item(queue, items_count, part_n, n_items_host, part, left);
+      if (w < 0) break;
       const int2 it2 = items[w];
       const DiscParams& P = params[it2.x];
       if (P.err != kJobOk) continue;
@@ -81,7 +79,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LMAX == 32 ?
       a.radius = J->radius;
       a.opt = J->opt;
       a.mcc = mcc;
-      a.mcc_cap = mcc_cap;
+      a.part_n = part_n;
+      a.key0 = J->key0;
       a.mcc_count = mcc_count;
       R = __builtin_amdgcn_readfirstlane(J->radius);
       m = it2.y;
@@ -125,25 +124,25 @@ int occ_f() {
 }  // namespace
 
 hipError_t launch_map_fused(const BatchJob* jobs, const DiscParams* params, const int2* items,
-                            int32_t n_items, const int32_t* n_items_dev, int dtype, int lmax,
+                            int32_t n_items, const int32_t* items_count, int dtype, int lmax,
                             int grid, int2* over, int32_t* over_count, int32_t* queue,
-                            unsigned char* mcc, int64_t mcc_cap, int32_t* mcc_count, hipStream_t st) {
-  if (n_items <= 0 && !n_items_dev) return hipSuccess;
+                            unsigned char* mcc, int64_t part_n, int32_t* mcc_count, hipStream_t st) {
+  if (n_items <= 0 && !items_count) return hipSuccess;
   const dim3 g((unsigned)grid), b(64);
   if (dtype == 1) {
     if (lmax <= 32)
-      hipLaunchKernelGGL((k_map_fused<int16_t, 32>), g, b, 0, st, jobs, params, items, n_items, n_items_dev,
-                         over, over_count, queue, mcc, mcc_cap, mcc_count);
+      hipLaunchKernelGGL((k_map_fused<int16_t, 32>), g, b, 0, st, jobs, params, items, n_items, items_count,
+                         over, over_count, queue, mcc, part_n, mcc_count);
     else
-      hipLaunchKernelGGL((k_map_fused<int16_t, 64>), g, b, 0, st, jobs, params, items, n_items, n_items_dev,
-                         over, over_count, queue, mcc, mcc_cap, mcc_count);
+      hipLaunchKernelGGL((k_map_fused<int16_t, 64>), g, b, 0, st, jobs, params, items, n_items, items_count,
+                         over, over_count, queue, mcc, part_n, mcc_count);
   } else {
     if (lmax <= 32)
-      hipLaunchKernelGGL((k_map_fused<float, 32>), g, b, 0, st, jobs, params, items, n_items, n_items_dev,
-                         over, over_count, queue, mcc, mcc_cap, mcc_count);
+      hipLaunchKernelGGL((k_map_fused<float, 32>), g, b, 0, st, jobs, params, items, n_items, items_count,
+                         over, over_count, queue, mcc, part_n, mcc_count);
     else
-      hipLaunchKernelGGL((k_map_fused<float, 64>), g, b, 0, st, jobs, params, items, n_items, n_items_dev,
-                         over, over_count, queue, mcc, mcc_cap, mcc_count);
+      hipLaunchKernelGGL((k_map_fused<float, 64>), g, b, 0, st, jobs, params, items, n_items, items_count,
+                         over, over_count, queue, mcc, part_n, mcc_count);
   }
   return hipGetLastError();
 }

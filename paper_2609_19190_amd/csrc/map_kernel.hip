@@ -9,20 +9,24 @@ namespace {
 // result goes to its problem's output address.  A problem's result depends
 // only on the problem, as in the in-kernel flush.
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_mcc(
-    const int32_t* __restrict__ n_mcc, const int32_t* __restrict__ err,
-    const unsigned char* __restrict__ stash, int64_t cap, bool fine) {
+    const int32_t* __restrict__ counts, const int32_t* __restrict__ err,
+    const unsigned char* __restrict__ stash, int64_t part_n, bool fine) {
   if (err && *err != kJobOk) return;
-  const int nn = n_mcc[0], nw = n_mcc[1];
+  // workgroup b takes every per-th group of partition b mod kParts
+  const int p = (int)blockIdx.x % kParts, per = ((int)gridDim.x - p + kParts - 1) / kParts;
+  const int nn = counts[p * kPartStride + kCntNarrow], nw = counts[p * kPartStride + kCntWide];
+  const unsigned char* first = stash + part_base(part_n, p) * kMccProblemBytes;
+  const unsigned char* past = stash + part_base(part_n, p + 1) * kMccProblemBytes;
   const int gn = (nn + 3) / 4, gw = (nw + 3) / 4;
-  for (int g = blockIdx.x; g < gn + gw; g += gridDim.x) {
+  for (int g = (int)blockIdx.x / kParts; g < gn + gw; g += per) {
     if (g < gn) {
       const int c = min(4, nn - 4 * g);
-      mcc_narrow((const McSmall*)stash + 4 * g, (1u << c) - 1u, fine);
+      mcc_narrow((const McSmall*)first + 4 * g, (1u << c) - 1u, fine);
     } else {
       // wide problem k is the (k + 1)-th entry from the end: slot s of the
       // group's window is problem k0 + c - 1 - s
       const int k0 = 4 * (g - gn), c = min(4, nw - k0);
-      const McProblem* win = (const McProblem*)(stash + cap * kMccProblemBytes) - (k0 + c);
+      const McProblem* win = (const McProblem*)past - (k0 + c);
       mcc_wide(win, (1u << c) - 1u, fine);
     }
   }
@@ -79,8 +83,8 @@ hipError_t launch_transpose_batch(const BatchJob* jobs, const DiscParams* params
   return hipGetLastError();
 }
 
-hipError_t launch_mcc(const int32_t* n_mcc, const int32_t* err, const unsigned char* stash,
-                      int64_t cap, bool fine, hipStream_t st) {
+hipError_t launch_mcc(const int32_t* counts, const int32_t* err, const unsigned char* stash,
+                      int64_t part_n, bool fine, hipStream_t st) {
   static int grid = 0;  // resident workgroups of k_mcc: a persistent grid
   if (grid == 0) {
     int dev = 0, cus = 0, per_cu = 0;
@@ -92,8 +96,9 @@ hipError_t launch_mcc(const int32_t* n_mcc, const int32_t* err, const unsigned c
       per_cu = 1;
     }
     grid = (per_cu > 0 ? per_cu : 1) * (cus > 0 ? cus : 1);
+    if (grid < kParts) grid = kParts;
   }
-  hipLaunchKernelGGL(k_mcc, dim3((unsigned)grid), dim3(64), 0, st, n_mcc, err, stash, cap, fine);
+  hipLaunchKernelGGL(k_mcc, dim3((unsigned)grid), dim3(64), 0, st, counts, err, stash, part_n, fine);
   return hipGetLastError();
 }
 
@@ -112,17 +117,17 @@ hipError_t launch_map(const MapArgs& a, int dtype, int radius, int lmax, bool de
 }
 
 hipError_t launch_map_batch(const BatchJob* jobs, const DiscParams* params, const int2* items,
-                            int32_t n_items, const int32_t* n_items_dev, int32_t vpw, int dtype,
+                            int32_t n_items, const int32_t* items_count, int32_t vpw, int dtype,
                             int radius, int lmax, int grid, int2* over, int32_t* over_count,
-                            int32_t* queue, unsigned char* mcc, int64_t mcc_cap, int32_t* mcc_count,
+                            int32_t* queue, unsigned char* mcc, int64_t part_n, int32_t* mcc_count,
                             hipStream_t st) {
-  if (n_items <= 0 && !n_items_dev) return hipSuccess;
+  if (n_items <= 0 && !items_count) return hipSuccess;
   if (radius > 3)  // no stashing instances: the problems are solved in the kernel
-    return launch_map_batch_wide(jobs, params, items, n_items, n_items_dev, vpw, radius, lmax, grid, over,
-                                 over_count, queue, st);
+    return launch_map_batch_wide(jobs, params, items, n_items, items_count, vpw, radius, lmax, grid, over,
+                                 over_count, queue, part_n, st);
   auto f = dtype == 1 ? launch_map_batch_i16 : launch_map_batch_f32;
-  return f(jobs, params, items, n_items, n_items_dev, vpw, radius, lmax, grid, over, over_count, queue, mcc,
-           mcc_cap, mcc_count, st);
+  return f(jobs, params, items, n_items, items_count, vpw, radius, lmax, grid, over, over_count, queue, mcc,
+           part_n, mcc_count, st);
 }
 
 int map_batch_blocks_per_cu(int dtype, int radius, int lmax, bool stash) {

@@ -273,6 +273,7 @@ struct Slot {
   hipEvent_t ev = nullptr;
   fr::BatchJob* h_job = nullptr;     // pinned upload of the job record
   fr::DiscParams* h_params = nullptr;  // pinned read-back of the job status
+  int32_t* counts = nullptr;           // device counter block of the job's passes
   int64_t ticket = -1;
 };
 
@@ -340,6 +341,7 @@ hipError_t launch_job(fr_server_s* s, SJob& J, Slot& sl) {
   sc.block_min = (double*)(blk + L.bmin);
   sc.block_max = (double*)(blk + L.bmax);
   sc.params = dpar;
+  sc.counts = sl.counts;
   if ((e = fr::launch_discretise_batch(djob, 1, nullptr, B.nseg, sc, sl.st)) != hipSuccess) return e;
   int2* over0 = (int2*)(blk + L.over0);
   int2* over1 = (int2*)(blk + L.over1);
@@ -354,21 +356,23 @@ hipError_t launch_job(fr_server_s* s, SJob& J, Slot& sl) {
     // MCC kernel would take every CU for its short run and stall the jobs
     // beside it (measured: served throughput fell below the plain path's).
     if ((e = fr::launch_map_batch(djob, dpar, nullptr, n_items, nullptr, vpw, B.dtype, B.radius, klmax,
-                                  n_items, over0, &dpar->n_over[0], nullptr, nullptr, 0, nullptr,
+                                  n_items, over0, sl.counts + fr::kCntOver0, nullptr, nullptr, B.n_mask, nullptr,
                                   sl.st)) != hipSuccess)
       return e;
     if (B.radius >= 2 && klmax == 32 && B.lcap > 32) {
       const int grid64 = s->n_cu * fr::map_batch_blocks_per_cu(B.dtype, B.radius, 64, false);
       // a persistent grid over a list known only on the device: a work queue,
       // so jobs running beside it do not leave it a long tail
-      if ((e = fr::launch_map_batch(djob, dpar, over0, 0, &dpar->n_over[0], 1, B.dtype, B.radius, 64,
-                                    grid64, over1, &dpar->n_over[1], &dpar->queue[1], nullptr, 0, nullptr,
+      if ((e = fr::launch_map_batch(djob, dpar, over0, 0, sl.counts + fr::kCntOver0, 1, B.dtype, B.radius, 64,
+                                    grid64, over1, sl.counts + fr::kCntOver1, sl.counts + fr::kCntQueue1, nullptr,
+                                    B.n_mask, nullptr,
                                     sl.st)) != hipSuccess)
         return e;
     }
     if (needs_generic(B)) {
       const int list = klmax == 32 ? 1 : 0;
-      if ((e = fr::launch_map_generic(none, djob, dpar, list ? over1 : over0, &dpar->n_over[list], 0,
+      if ((e = fr::launch_map_generic(none, djob, dpar, list ? over1 : over0,
+                                      sl.counts + (list ? fr::kCntOver1 : fr::kCntOver0), B.n_mask,
                                       B.dtype, blk + L.gscratch, B.lcap, kServeGenericGrid,
                                       sl.st)) != hipSuccess)
         return e;
@@ -491,6 +495,7 @@ void free_server(fr_server_s* s) {
     if (sl.st) (void)hipStreamDestroy(sl.st);
     if (sl.h_job) (void)hipHostFree(sl.h_job);
     if (sl.h_params) (void)hipHostFree(sl.h_params);
+    if (sl.counts) (void)hipFree(sl.counts);
   }
   if (s->base) (void)hipFree(s->base);
   delete s;
@@ -527,7 +532,8 @@ fr_status fr_server_create(const fr_server_config* cfg, fr_server* out) {
     if (hipStreamCreateWithFlags(&sl.st, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&sl.ev, hipEventDisableTiming) != hipSuccess ||
         hipHostMalloc((void**)&sl.h_job, sizeof(fr::BatchJob), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void**)&sl.h_params, sizeof(fr::DiscParams), hipHostMallocDefault) != hipSuccess) {
+        hipHostMalloc((void**)&sl.h_params, sizeof(fr::DiscParams), hipHostMallocDefault) != hipSuccess ||
+        hipMalloc((void**)&sl.counts, fr::kCountInts * sizeof(int32_t)) != hipSuccess) {
       free_server(s);
       return sfail(FR_E_DEVICE, "slot streams/events/pinned memory could not be created");
     }
