@@ -23,32 +23,35 @@ constexpr double kLcm26 = 26771144400.0;
 constexpr double kRcpLcm26 = 1.0 / kLcm26;
 
 // 13 forward neighbour offsets (dx, dy, dz), one of each +/- pair, each the
-// larger cube index of its pair; bit d of
-// the equal-level mask is forward direction d, bit 13 + d its opposite.
-// Ordered by how many of the other opposites are neighbours of a direction's
-// opposite: the zone pass takes the first equal-level one and skips those
-// its zone already holds (kDirCover).
-__host__ __device__ constexpr int fdx(int d) {
-  return d == 2 ? 1 : d == 5 ? 1 : d == 6 ? -1 : d == 7 ? 1 : d == 8 ? -1 : d == 9 ? 1 : d == 10 ? -1
-       : d == 11 ? 1 : d == 12 ? -1 : 0;
+// larger cube index of its pair.
+// Directions 0..11 are dx = d / 4 - 1 on the forward rows (dy, dz) = (0, 1),
+// (1, 0), (1, 1), (-1, 1); direction 12 is (1, 0, 0).
+__host__ __device__ constexpr int fdx(int d) { return d == 12 ? 1 : d / 4 - 1; }
+__host__ __device__ constexpr int fdy(int d) { return d == 12 || d % 4 == 0 ? 0 : d % 4 == 3 ? -1 : 1; }
+__host__ __device__ constexpr int fdz(int d) { return d == 12 || d % 4 == 1 ? 0 : 1; }
+// The equal-level mask of a voxel: byte dx + 1 (bits 0..23) holds the eight
+// neighbour rows, bit r < 4 the row opposite to forward row r, bit 4 + r
+// forward row r; the voxel's own row has bit 27 (dx = -1) and 31 (dx = 1).
+constexpr uint32_t kFwdBits = 0x80f0f0f0u, kBackBits = 0x080f0f0fu;
+__host__ __device__ constexpr int fwd_bit(int d) { return d == 12 ? 31 : 8 * (d / 4) + 4 + d % 4; }
+__host__ __device__ constexpr int back_bit(int d) { return d == 12 ? 27 : 8 * (2 - d / 4) + d % 4; }
+// The backward bits with the dx = 0 byte first, so that the lowest set bit
+// is the neighbour that most of the others are neighbours of: bit position
+// of direction d's opposite in that order.
+__host__ __device__ constexpr int zone_bit(int d) {
+  return d == 12 ? 27 : (d / 4 == 1 ? 0 : d / 4 == 2 ? 8 : 16) + d % 4;
 }
-__host__ __device__ constexpr int fdy(int d) {
-  return d == 1 ? 1 : d == 3 ? 1 : d == 4 ? -1 : d == 7 ? 1 : d == 8 ? 1 : d == 9 ? 1 : d == 10 ? 1
-       : d == 11 ? -1 : d == 12 ? -1 : 0;
-}
-__host__ __device__ constexpr int fdz(int d) {
-  return d == 0 ? 1 : d == 1 || d == 2 ? 0 : d <= 6 ? 1 : d <= 8 ? 0 : 1;
-}
-// Bit n: the opposites of directions d and n are neighbours (or the same).
+// Zone bits of the opposites that are neighbours of direction d's opposite
+// (or are it).
 __host__ __device__ constexpr uint32_t dir_cover(int d) {
   uint32_t m = 0;
   for (int n = 0; n < 13; ++n) {
     const int x = fdx(n) - fdx(d), y = fdy(n) - fdy(d), z = fdz(n) - fdz(d);
-    if (x >= -1 && x <= 1 && y >= -1 && y <= 1 && z >= -1 && z <= 1) m |= 1u << n;
+    if (x >= -1 && x <= 1 && y >= -1 && y <= 1 && z >= -1 && z <= 1) m |= 1u << zone_bit(n);
   }
   return m;
 }
-// The same offsets as a table, for a direction known only at run time.
+// The same as tables, for a direction known only at run time.
 __constant__ signed char kDir[13][3] = {
     {fdx(0), fdy(0), fdz(0)},    {fdx(1), fdy(1), fdz(1)},    {fdx(2), fdy(2), fdz(2)},
     {fdx(3), fdy(3), fdz(3)},    {fdx(4), fdy(4), fdz(4)},    {fdx(5), fdy(5), fdz(5)},
