@@ -72,6 +72,13 @@ __device__ inline double frcp(double x) {
   return fma(fma(-x, r0, 1.0), r0, r0);
 }
 
+// sqrt(x) of a positive normal x from the hardware reciprocal square root
+// and one Newton step (relative error ~1e-16).
+__device__ inline double fsqrt(double x) {
+  const double r = __builtin_amdgcn_rsq(x), g = x * r;
+  return fma(g, fma(-0.5 * r, g, 0.5), g);
+}
+
 // log2 of a positive finite normal x, for the entropy terms: x = m 2^e with
 // m in [1/sqrt 2, sqrt 2), ln m = 2 atanh(s), s = (m - 1) / (m + 1) (|s| <=
 // 0.1716), by the odd series of atanh to s^15.  The first omitted term,
