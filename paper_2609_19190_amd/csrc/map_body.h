@@ -769,20 +769,17 @@ __device__ FR_INLINE inline void mcc_narrow(const P* slots, unsigned mask, bool 
     const double alpha = a2 == 0.0 ? 0.0 : -copysign(fsqrt(a2), x0);
     const double beta = a2 == 0.0 ? 0.0 : frcp(a2 - x0 * alpha);  // 2 / v.v
     const double vi = j == k + 1 ? x0 - alpha : xi;
-    double pj = 0.0;
-    static_for<k + 1, 16>([&](auto ic) FR_INLINE {
-      constexpr int i = decltype(ic)::value;
-      pj += col[i] * rbc<i>(vi);
-    });
-    pj *= beta;  // p = beta T v
+    // rows in blocks of eight, the finished ones (v_i = q_i = 0) along
+    double pp[4] = {0.0, 0.0, 0.0, 0.0};
+    if constexpr (k < 7) mv8<false>(pp, vi, &col[0]);
+    mv8<true>(pp, vi, &col[8]);
+    const double pj = ((pp[0] + pp[1]) + (pp[2] + pp[3])) * beta;  // p = beta T v
     const double Kc = 0.5 * beta * rsum(vi * pj);
-    const double qj = pj - Kc * vi;
-    if (j > k) {  // T -= v q^T + q v^T
-      static_for<k + 1, 16>([&](auto ic) FR_INLINE {
-        constexpr int i = decltype(ic)::value;
-        col[i] -= rbc<i>(vi) * qj + rbc<i>(qj) * vi;
-      });
-    }
+    // 0 on the finished columns (whose v is 0 too): they stay unchanged
+    const double qj = j > k ? pj - Kc * vi : 0.0;
+    const double nv = -vi, nq = -qj;
+    if constexpr (k < 7) up8<false>(&col[0], vi, qj, nv, nq);  // T -= v q^T + q v^T
+    up8<true>(&col[8], vi, qj, nv, nq);
     if (j == k) e_lane = alpha;  // also the last step k = n - 2 (a sign flip)
   });
   double d = 0.0;
@@ -854,41 +851,34 @@ __device__ FR_INLINE inline void mcc_wide(const McProblem* slots, unsigned mask,
     constexpr int K0 = decltype(k0c)::value, K1 = decltype(k1c)::value;
 #pragma unroll 1
     for (int k = K0; k < K1 && k < kend; ++k) {
-      double ckA = 0.0, ckB = 0.0;  // row k of the lane's columns
+      // row k of the lane's columns and its entry k + 1 (a branch, not
+      // selects: the empty statement keeps the moves inside it)
+      double ckA = 0.0, ckB = 0.0, x0 = 0.0;
       static_for<K0, K1>([&](auto cc) FR_INLINE {
         constexpr int c = decltype(cc)::value;
         if (k == c) {
           ckA = cA[c];
           ckB = cB[c];
+          x0 = c + 1 < 16 ? rbc<(c + 1) & 15>(ckA) : rbc<(c + 1) & 15>(ckB);
+          asm volatile("" : "+v"(ckA), "+v"(ckB), "+v"(x0));
         }
       });
       // column k below the diagonal; by symmetry B[i][k] = cA[k] of lane i
       const double xA = (j > k && j < n) ? ckA : 0.0;
       const double xB = (jb > k && jb < n) ? ckB : 0.0;
       const double a2 = rsum(xA * xA + xB * xB);
-      const double x0 = rsum((j == k + 1 ? xA : 0.0) + (jb == k + 1 ? xB : 0.0));
       const double alpha = a2 == 0.0 ? 0.0 : -copysign(fsqrt(a2), x0);
       const double beta = a2 == 0.0 ? 0.0 : frcp(a2 - x0 * alpha);  // 2 / v.v
       const double vA = j == k + 1 ? x0 - alpha : xA;
       const double vB = jb == k + 1 ? x0 - alpha : xB;
-      // rows from K0 + 1 on, in blocks of eight behind one uniform branch
-      // each (block b only if 8 b < nmax: rows past every problem's n hold
-      // zeros); two partial sums per column for latency
+      // rows from K0 on, in blocks of eight behind one uniform branch each
+      // (block b only if 8 b < nmax: rows past every problem's n hold zeros,
+      // as v and q of the finished rows); two partial sums per column for
+      // latency
       double pA2[2] = {0.0, 0.0}, pB2[2] = {0.0, 0.0};
-      static_for<(K0 + 1) / 8, 4>([&](auto bc) FR_INLINE {
+      static_for<K0 / 8, 4>([&](auto bc) FR_INLINE {
         constexpr int b = decltype(bc)::value;
-        if (8 * b < nmax) {
-          if constexpr (8 * b >= K0 + 1) {
-            mv8w<(b & 1) != 0>(pA2, pB2, b < 2 ? vA : vB, &cA[8 * b], &cB[8 * b]);
-          } else {
-            static_for<K0 + 1, 8 * b + 8>([&](auto ic) FR_INLINE {
-              constexpr int i = decltype(ic)::value;
-              const double vi = i < 16 ? rbc<i & 15>(vA) : rbc<i & 15>(vB);
-              pA2[i & 1] = fma(cA[i], vi, pA2[i & 1]);
-              pB2[i & 1] = fma(cB[i], vi, pB2[i & 1]);
-            });
-          }
-        }
+        if (8 * b < nmax) mv8w<(b & 1) != 0>(pA2, pB2, b < 2 ? vA : vB, &cA[8 * b], &cB[8 * b]);
       });
       const double pA = (pA2[0] + pA2[1]) * beta;  // p = beta T v
       const double pB = (pB2[0] + pB2[1]) * beta;
@@ -897,21 +887,10 @@ __device__ FR_INLINE inline void mcc_wide(const McProblem* slots, unsigned mask,
       // v is 0 too), so the update leaves those unchanged
       const double qA = j > k ? pA - Kc * vA : 0.0, qB = jb > k ? pB - Kc * vB : 0.0;
       const double nvA = -vA, nvB = -vB, nqA = -qA, nqB = -qB;
-      static_for<(K0 + 1) / 8, 4>([&](auto bc) FR_INLINE {  // T -= v q^T + q v^T
+      static_for<K0 / 8, 4>([&](auto bc) FR_INLINE {  // T -= v q^T + q v^T
         constexpr int b = decltype(bc)::value;
-        if (8 * b < nmax) {
-          if constexpr (8 * b >= K0 + 1) {
-            up8w<(b & 1) != 0>(&cA[8 * b], &cB[8 * b], b < 2 ? vA : vB, b < 2 ? qA : qB, nvA, nvB, nqA, nqB);
-          } else {
-            static_for<K0 + 1, 8 * b + 8>([&](auto ic) FR_INLINE {
-              constexpr int i = decltype(ic)::value;
-              const double vi = i < 16 ? rbc<i & 15>(vA) : rbc<i & 15>(vB);
-              const double qi = i < 16 ? rbc<i & 15>(qA) : rbc<i & 15>(qB);
-              cA[i] = fma(-vi, qA, fma(-qi, vA, cA[i]));
-              cB[i] = fma(-vi, qB, fma(-qi, vB, cB[i]));
-            });
-          }
-        }
+        if (8 * b < nmax)
+          up8w<(b & 1) != 0>(&cA[8 * b], &cB[8 * b], b < 2 ? vA : vB, b < 2 ? qA : qB, nvA, nvB, nqA, nqB);
       });
       if (j == k) eA = alpha;  // also the last step k = n - 2 (a sign flip)
       if (jb == k) eB = alpha;
@@ -999,7 +978,10 @@ __device__ FR_INLINE inline void mcc_big(Smem<R, LMAX, MOUT>& sm) {
       double ck = 0.0;  // row k of the lane's column
       static_for<K0, K1>([&](auto cc) FR_INLINE {
         constexpr int c = decltype(cc)::value;
-        ck = k == c ? col[c] : ck;
+        if (k == c) {  // a branch, as in mcc_wide
+          ck = col[c];
+          asm volatile("" : "+v"(ck));
+        }
       });
       // column k below the diagonal; by symmetry B[i][k] = col[k] of lane i
       const double x = lane > k ? ck : 0.0;
@@ -1012,22 +994,14 @@ __device__ FR_INLINE inline void mcc_big(Smem<R, LMAX, MOUT>& sm) {
       hv[lane] = v;
       __syncthreads();
       static_for<0, 4>([&](auto mc) FR_INLINE { vr[decltype(mc)::value] = hv[16 * decltype(mc)::value + ln]; });
-      // rows from K0 + 1 on, in blocks of eight behind one uniform branch
-      // each (block b only if 8 b < n); rows past n inside a block hold
-      // zeros and have v_i = q_i = 0.  Four independent sums for latency.
+      // rows from K0 on, in blocks of eight behind one uniform branch each
+      // (block b only if 8 b < n); rows past n inside a block hold zeros,
+      // and v_i = q_i = 0 there and in the finished rows.  Four independent
+      // sums for latency.
       double pp[4] = {0.0, 0.0, 0.0, 0.0};
-      static_for<(K0 + 1) / 8, 8>([&](auto bc) FR_INLINE {
+      static_for<K0 / 8, 8>([&](auto bc) FR_INLINE {
         constexpr int b = decltype(bc)::value;
-        if (8 * b < n) {
-          if constexpr (8 * b >= K0 + 1) {
-            mv8<(b & 1) != 0>(pp, vr[b >> 1], &col[8 * b]);
-          } else {
-            static_for<K0 + 1, 8 * b + 8>([&](auto ic) FR_INLINE {
-              constexpr int i = decltype(ic)::value;
-              pp[i & 3] = fma(col[i], rbc<i & 15>(vr[i >> 4]), pp[i & 3]);
-            });
-          }
-        }
+        if (8 * b < n) mv8<(b & 1) != 0>(pp, vr[b >> 1], &col[8 * b]);
       });
       double p = (pp[0] + pp[1]) + (pp[2] + pp[3]);
       p *= beta;  // p = beta T v
@@ -1038,18 +1012,9 @@ __device__ FR_INLINE inline void mcc_big(Smem<R, LMAX, MOUT>& sm) {
       __syncthreads();
       static_for<0, 4>([&](auto mc) FR_INLINE { qr[decltype(mc)::value] = hq[16 * decltype(mc)::value + ln]; });
       const double nv = -v, nq = -q;
-      static_for<(K0 + 1) / 8, 8>([&](auto bc) FR_INLINE {  // T -= v q^T + q v^T
+      static_for<K0 / 8, 8>([&](auto bc) FR_INLINE {  // T -= v q^T + q v^T
         constexpr int b = decltype(bc)::value;
-        if (8 * b < n) {
-          if constexpr (8 * b >= K0 + 1) {
-            up8<(b & 1) != 0>(&col[8 * b], vr[b >> 1], qr[b >> 1], nv, nq);
-          } else {
-            static_for<K0 + 1, 8 * b + 8>([&](auto ic) FR_INLINE {
-              constexpr int i = decltype(ic)::value;
-              col[i] = fma(-rbc<i & 15>(vr[i >> 4]), q, fma(-rbc<i & 15>(qr[i >> 4]), v, col[i]));
-            });
-          }
-        }
+        if (8 * b < n) up8<(b & 1) != 0>(&col[8 * b], vr[b >> 1], qr[b >> 1], nv, nq);
       });
       if (lane == k) e_lane = alpha;  // also the last step k = n - 2 (a sign flip)
     }
