@@ -144,12 +144,30 @@ struct Smem {
   static constexpr int SX = (SQ + 3) / 4 * 4;                     // bytes of a padded cube row
   static constexpr int PC = SQ * SQ * SX + 4;                     // 8-byte reads end past the last row
   uint8_t cl[CP];        // compact level + 1 per cube position (0: not in V)
-  // the same in a cube with a zero border of 1, rows from 4-byte boundaries
-  alignas(4) uint8_t clp[PC];
-  // per position of the cube and of its border rows: the level values of the
-  // position and its two neighbours along x, summed, times 32, plus how
-  // many of the three are in V
-  uint16_t cw[SQ * SQ * S];
+  // The regions below are shared by what lives at different times, because
+  // LDS sets the occupancy at radius 3: 13.2 -> 10.7 KB is 15 workgroups a
+  // CU instead of 12 (14.3 -> 12.2 ms for 1 M voxels).
+  // One region (nb) in turn holds
+  //   the same in a cube with a zero border of 1, rows from 4-byte
+  //   boundaries (clp), and per position of the cube and of its border rows
+  //   the level values of the position and its two neighbours along x,
+  //   summed, times 32, plus how many of the three are in V (cw);
+  //   after the counting pass, the zone pass's edge list (16-bit entries, at
+  //   most three a voxel); the list of runs; the zone sizes at roots and
+  //   the zones per size (zcnt, zps: 16-bit, packed); this voxel's maps,
+  //   over the zone sizes or behind both.
+  static constexpr int CWB = 2 * SQ * SQ * S;  // bytes of cw
+  static constexpr int kZoneBytes = CP * 4;    // of zcnt and zps
+  static constexpr int kFeatAt = CP * 2 >= 384 ? 0 : kZoneBytes;
+  static constexpr int cmax(int a, int b) { return a > b ? a : b; }
+  static constexpr int NB = (cmax(cmax(PC + CWB, 6 * C), cmax(kZoneBytes, kFeatAt + 384)) + 15) / 16 * 16;
+  alignas(16) uint8_t nb[NB];
+  __device__ uint8_t* clp() { return nb; }
+  __device__ uint16_t* cw() { return (uint16_t*)(nb + PC); }
+  __device__ uint16_t* list() { return (uint16_t*)nb; }
+  __device__ uint32_t* zcnt() { return (uint32_t*)nb; }
+  __device__ uint32_t* zps() { return (uint32_t*)nb + CP / 2; }
+  __device__ float* feat() { return (float*)(nb + kFeatAt); }
   // level values 1..255; at most LMAX of them present in one neighbourhood
   // (a neighbourhood with more is handed to a wider instance)
   static constexpr int LV = 256;
@@ -157,18 +175,14 @@ struct Smem {
   // per bit of the equal-level mask: what the zone pass covers with that
   // neighbour (dir_cover; zone bits), its distance in the cube (zone bits),
   // and the distance of a forward bit
-  uint32_t zcov[28];
-  uint8_t zoff[28], foff[32];
-  uint8_t lflag[LV];     // level present in V
+  // (entries that are no bit of theirs hold 0)
+  uint32_t zcov[32];
+  uint8_t zoff[32], foff[32];
   uint8_t lval[LMAX];    // compact index -> level
   uint32_t hist[LMAX];   // level histogram
   uint32_t pxc[LMAX];    // GLCM row sums
-  float fo[kNFO];        // the first-order maps, taken before the tables fill
-  // this voxel's maps: a member, or (radius 3 with 32 levels, where LDS
-  // decides the occupancy) the zone-size table, free once the zones are
-  // counted and out of reach of the overlays b and c below
-  static constexpr bool kFeatInZcnt = R == 3 && LMAX == 32;
-  float feat_m[kFeatInZcnt ? 1 : 96];
+  // maps taken before the others: first order, GLDM, NGTDM
+  float early[kNFO + kNGLDM + kNNGTDM];
   McSlots<McProblem, MOUT ? 0 : kMcSlots<R, LMAX>> mq;  // deferred MCC problems
   McSlots<McSmall, MOUT ? 0 : kSmallSlots<R, LMAX>> ms;  // deferred MCC problems, <= 16 levels
   // The counting tables (a), the GLCM feature histograms (c) and the MCC
@@ -181,18 +195,21 @@ struct Smem {
       // equal-level masks; then the zone hash (kHashInSame)
       alignas(16) uint32_t same[CP];
       uint32_t parent[CP]; // raw values to sort; zone forest; the list of its roots
-      alignas(16) uint32_t gldm[LMAX * kGldmWords];  // 16-bit counts, packed, kGldmWords words a level
-      uint32_t dpl[28];                  // voxels per dependence
-      uint32_t ngn[LMAX];
-      unsigned long long ngS[LMAX];
-      uint32_t zpl[LMAX];
-      // what follows first holds the zone pass's edge list (16-bit entries,
-      // at most three a voxel), then is cleared together
-      alignas(16) uint32_t glrlm[LMAX * S];
-      uint32_t zcnt[CP / 2];  // zone sizes at roots (16-bit, packed)
-      uint32_t zps[CP / 2];   // zones per size (16-bit, packed)
-      uint32_t hash_m[kHashInSame ? 1 : HT + HT / 2];
-      uint32_t edge_pad[R == 4 ? 64 : R == 5 ? 320 : 1];
+      // GLDM and NGTDM counts; once their maps are taken, the runs, the
+      // zones per level and (kHashInSame false) the zone hash
+      union {
+        struct {
+          alignas(16) uint32_t gldm[LMAX * kGldmWords];  // 16-bit counts, packed, kGldmWords words a level
+          uint32_t dpl[28];                  // voxels per dependence
+          uint32_t ngn[LMAX];
+          unsigned long long ngS[LMAX];
+        };
+        struct {
+          alignas(16) uint32_t glrlm[LMAX * S];
+          uint32_t zpl[LMAX];
+          uint32_t hash_m[kHashInSame ? 1 : HT + HT / 2];
+        };
+      };
     } a;
     struct C {
       uint32_t glcm[kGlcmWords];  // a.glcm
@@ -208,7 +225,6 @@ struct Smem {
       int big_n;
     } b;
   } u;
-  __device__ float* feat() { return kFeatInZcnt ? (float*)u.a.zcnt : feat_m; }
   // zone hash: keys, then zones per (level, size) key (16-bit, packed)
   __device__ uint32_t* hkey() { return kHashInSame ? u.a.same : u.a.hash_m; }
   __device__ uint32_t* hcnt() { return hkey() + HT; }
@@ -220,9 +236,12 @@ template <int R, int LMAX, bool MOUT>
 __device__ FR_INLINE inline void smem_layout(Smem<R, LMAX, MOUT>& sm) {
   using SM = Smem<R, LMAX, MOUT>;
   const int lane = threadIdx.x;
-  if (lane < SM::LVW) ((uint32_t*)sm.lflag)[lane] = 0u;
-  for (int e = lane; e < SM::PC / 4; e += 64) ((uint32_t*)sm.clp)[e] = 0u;
-  for (int e = lane; e < SM::SQ * SM::SQ * SM::S; e += 64) sm.cw[e] = 0;
+  if (lane < 32) {
+    sm.zcov[lane] = 0u;
+    sm.zoff[lane] = 0;
+    sm.foff[lane] = 0;
+  }
+  __syncthreads();
   if (lane < 13) {
     const int off = (kDir[lane][2] * SM::S + kDir[lane][1]) * SM::S + kDir[lane][0];
     sm.zcov[zone_bit(lane)] = kDirCover[lane];
@@ -1342,19 +1361,24 @@ constexpr bool kFineMcc = R > 3 || MODE != kPlain;
 
 // The 16 GLRLM maps of the counts glrlm [L][S] (compact level, run length
 // - 1).  Rows by lane (LevelRow): the sums over a level's lengths first,
-// the level's powers once a row; a column that no level has is skipped.
+// the level's powers once a row; the tables' loads together.
 template <int R, int LMAX, typename O>
 __device__ FR_INLINE inline void runs_features(const uint32_t* glrlm, const LevelRow<LMAX>& lr, int L, int lane,
                                                double units, O* f) {
   constexpr int S = 2 * R + 1, H = LevelRow<LMAX>::H, NT = (S + H - 1) / H;
   RowSums rs = {};
   long long gln = 0, rln = 0;
+  uint32_t cs[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     const int j = t * H + lr.part;
-    const uint32_t c = lr.ok && j < S ? glrlm[lr.l * S + j] : 0u;
-    if (__ballot(c != 0u) == 0ull) continue;
-    row_add<R>(rs, c, (uint32_t)j + 1u);
+    cs[t] = lr.ok && j < S ? glrlm[lr.l * S + j] : 0u;
+  }
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int j = t * H + lr.part;
+    const uint32_t c = cs[t];
+    row_add<R>(rs, c, (uint32_t)(j < S ? j : 0) + 1u);
     // the length's total over the levels: in the last lane of each half
     // wave (H 2, one column per half) or of the wave
     int v = (int)c;
@@ -1393,6 +1417,9 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
   // ---- gather the cube ------------------------------------------------
   // the raw values (xq) and levels (gl) stay in registers until the
   // first-order maps are done; the sums for the moments are taken here
+  uint8_t* lflag = reinterpret_cast<uint8_t*>(sm.u.a.glcm);  // level present in V (before the counts)
+  clear16(lflag, SM::LV, lane);
+  clear16(sm.nb, SM::PC + SM::CWB, lane);
   int K = 0;
   float xq[NIT];
   double s1 = 0.0, s2 = 0.0;
@@ -1420,7 +1447,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
   for (int q = 0; q < NIT; ++q) {
     const int g = gl[q];
     const float xr = g ? xl[q] : INFINITY;
-    if (g) sm.lflag[g] = 1;
+    if (g) lflag[g] = 1;
     xq[q] = xr;
     if (fFO && g) {
       const double xd = (double)xr;
@@ -1436,7 +1463,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
   uint8_t* lmap = reinterpret_cast<uint8_t*>(sm.u.a.same);  // level -> compact index
   static_assert(sizeof(SM::U::A::same) >= (size_t)SM::LV, "the level map fits the masks' place");
   {
-    const uint32_t fw = lane < SM::LVW ? ((const uint32_t*)sm.lflag)[lane] : 0u;
+    const uint32_t fw = lane < SM::LVW ? ((const uint32_t*)lflag)[lane] : 0u;
     const int f0 = (fw & 0xffu) != 0, f1 = (fw & 0xff00u) != 0, f2 = (fw & 0xff0000u) != 0,
               f3 = (fw & 0xff000000u) != 0;
     int pre = wscan_excl(f0 + f1 + f2 + f3, lane, &L);
@@ -1444,7 +1471,6 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     if (f1) { lmap[4 * lane + 1] = (uint8_t)pre; sm.lval[pre++] = (uint8_t)(4 * lane + 1); }
     if (f2) { lmap[4 * lane + 2] = (uint8_t)pre; sm.lval[pre++] = (uint8_t)(4 * lane + 2); }
     if (f3) { lmap[4 * lane + 3] = (uint8_t)pre; sm.lval[pre++] = (uint8_t)(4 * lane + 3); }
-    if (lane < SM::LVW) ((uint32_t*)sm.lflag)[lane] = 0u;  // ready for the next voxel
   }
   if constexpr (C > LMAX) {
     if (L > LMAX) {  // more present levels than these tables hold: a wider pass maps it
@@ -1459,7 +1485,6 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
   clear16(sm.u.a.glcm, SM::glcm_words(L) * 4, lane);
   static_assert(offsetof(typename SM::U::A, same) % 16 == 0 && (SM::kGlcmWords * 4 + 15) / 16 * 16 <= (int)offsetof(typename SM::U::A, same),
                 "clearing the counts stays clear of the level map");
-  if (!fGLSZM) clear16(sm.u.a.glrlm, L * S * 4, lane);
   clear16(sm.u.a.gldm, L * SM::kGldmWords * 4, lane);
   if (lane < 28) sm.u.a.dpl[lane] = 0;
   if (lane < L) {
@@ -1467,7 +1492,6 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     sm.pxc[lane] = 0;
     sm.u.a.ngn[lane] = 0;
     sm.u.a.ngS[lane] = 0ull;
-    sm.u.a.zpl[lane] = 0;
   }
   __syncthreads();
 
@@ -1496,8 +1520,8 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       const int x = c % S, y = (c / S) % S, z = c / (S * S);
       const int row = (z + 1) * SM::SQ + (y + 1);
       const uint32_t left = lev[c], right = lev[c + 2];
-      sm.clp[row * SM::SX + (x + 1)] = (uint8_t)l1;
-      sm.cw[row * S + x] = (uint16_t)((x > 0 ? left : 0u) + (g ? g * 32 + 1 : 0) + (x < S - 1 ? right : 0u));
+      sm.clp()[row * SM::SX + (x + 1)] = (uint8_t)l1;
+      sm.cw()[row * S + x] = (uint16_t)((x > 0 ? left : 0u) + (g ? g * 32 + 1 : 0) + (x < S - 1 ? right : 0u));
     }
   }
   __syncthreads();
@@ -1658,7 +1682,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     }
     const bool flat = (mn == mx);
     if (lane == 0) {
-      float* f = sm.fo;
+      float* f = sm.early;
       f[0] = (float)S2;
       f[1] = (float)(a.voxel_volume * S2);
       f[2] = (float)ent;
@@ -1691,21 +1715,15 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
   // 6.0 k VALU instructions a voxel at radius 3 (16.6 -> 14.9 ms for 1 M
   // voxels), 4.0 k -> 3.7 k at radius 2.
   constexpr int SQ = SM::SQ;
-  uint16_t* elist = reinterpret_cast<uint16_t*>(sm.u.a.glrlm);
-  int n_edge = 0;
-  using UA = typename SM::U::A;
-  static_assert(sizeof(UA) - offsetof(UA, glrlm) >= 6u * C, "the edge list holds three edges a voxel");
-  static_assert(C <= 2048, "an edge is a cube index of 11 bits and a zone bit of 5");
 #pragma unroll 1
   for (int q = 0; q < NIT; ++q) {
     const int c = lane + 64 * q;
     const uint32_t l1 = (c < C) ? sm.cl[c] : 0u;
-    uint32_t back = 0;
     if (l1) {
       const int x = c % S, y = (c / S) % S, z = c / (S * S);
       const int row0 = (z + 1) * SQ + (y + 1);
-      const uint32_t* words = reinterpret_cast<const uint32_t*>(&sm.clp[row0 * SM::SX + (x & ~3)]);
-      const uint16_t* sums = &sm.cw[row0 * S + x];
+      const uint32_t* words = reinterpret_cast<const uint32_t*>(&sm.clp()[row0 * SM::SX + (x & ~3)]);
+      const uint16_t* sums = &sm.cw()[row0 * S + x];
       uint32_t rw[9], wsum = 0;
 #pragma unroll
       for (int r = 0; r < 9; ++r) {  // rows opposite to the forward ones, forward rows, the own one
@@ -1723,17 +1741,6 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       const int l = (int)l1 - 1, g = sm.lval[l];
       const int cnt = (int)(wsum & 31u) - 1, lsum = (int)(wsum >> 5) - g;
       sm.u.a.same[c] = same;
-      if (fGLSZM) {  // the first equal-level neighbour before c is its parent
-        // the backward bits, dx = 0 first (zone bits)
-        back = __builtin_amdgcn_perm(0u, same & kBackBits, 0x03020001u);
-        uint32_t par = (uint32_t)c;
-        if (back) {
-          const int b = __ffs(back) - 1;
-          par -= sm.zoff[b];
-          back &= ~sm.zcov[b];
-        }
-        sm.u.a.parent[c] = par;
-      }
       if (MODE == kPlain && fGLCM) {
         if constexpr (SM::kFullGlcm) {
           uint32_t* row = &sm.u.a.glcm[(l >> 1) * SM::kRowWords];
@@ -1775,16 +1782,6 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
         atomicAdd(&sm.u.a.ngS[l], (unsigned long long)(dd < 0 ? -dd : dd) * kLcmOver[cnt]);
       }
     }
-    // the neighbours that no earlier one taken is a neighbour of: edges for
-    // the zone pass (at most three more: four of the half neighbourhood are
-    // pairwise no neighbours)
-    for (uint64_t m; (m = __ballot(back != 0u)) != 0ull; n_edge += __popcll(m)) {
-      if (back) {
-        const int b = __ffs(back) - 1;
-        elist[n_edge + below(m)] = (uint16_t)(c | b << 11);
-        back &= ~sm.zcov[b];
-      }
-    }
   }
   __syncthreads();
 
@@ -1818,214 +1815,9 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     if (fGLCM) count_pairs(0, 13);
   }
 
-  // ---- zones: union of the listed edges -------------------------------
-  // parent[c] <= c names a voxel of c's zone: a forest whose roots are the
-  // zones' smallest cube indices once every edge's ends share a root.  An
-  // edge lowers the parent of its larger end; an end that had another
-  // parent goes on with that one, so no connection is lost.  A pass of
-  // minimum labels over all 26 neighbours, repeated until nothing changed
-  // (about four times), had been 14 % of the kernel's VALU instructions and
-  // half its LDS ones; with the runs below counted by kind: 10.8 k -> 7.9 k
-  // VALU and 1,346 -> 790 LDS instructions a voxel, 20.9 -> 16.7 ms for
-  // 1 M voxels of radius 3.
-  if (fGLSZM) {
-    uint32_t* parent = sm.u.a.parent;
-    for (int e0 = 0; e0 < n_edge; e0 += 64) {
-      if (e0 + lane < n_edge) {
-        const uint32_t w = elist[e0 + lane];
-        uint32_t u = w & 0x7ffu, v = u - sm.zoff[w >> 11];
-        while (u != v) {
-          const uint32_t hi = max(u, v), lo = min(u, v);
-          const uint32_t old = atomicMin(&parent[hi], lo);
-          if (old == hi) break;
-          u = old;
-          v = lo;
-        }
-      }
-    }
-    __syncthreads();
-    clear16(sm.u.a.glrlm, (int)(offsetof(UA, edge_pad) - offsetof(UA, glrlm)), lane);
-    __syncthreads();
-  }
-
-  // ---- runs and zone sizes --------------------------------------------
-#pragma unroll 1
-  for (int q = 0; q < NIT; ++q) {
-    const int c = lane + 64 * q;
-    const int l1 = (c < C) ? sm.cl[c] : 0;
-    if (l1) {
-      const uint32_t same = sm.u.a.same[c];
-      if (MODE != kAveraged && fGLRLM) {
-        const int l = l1 - 1;
-        uint32_t* row = &sm.u.a.glrlm[l * S];
-        // a run of direction d starts here when the backward neighbour is
-        // not of this level; runs of one voxel (most of them, in images with
-        // noise) are counted together, the others walked
-        // (the backward bits moved to their opposites: bytes 0 and 2 swapped)
-        const uint32_t starts = ~(__builtin_amdgcn_perm(0u, same, 0x03000102u) << 4) & kFwdBits;
-        uint32_t act = starts & same;
-        const int single = __popc(starts & ~same);
-        if (single) atomicAdd(&row[0], (uint32_t)single);
-        if (__ballot(__popc(act) > kRunBits) == 0ull) {  // a few: one direction after another
-          while (act) {
-            const int d = __ffs(act) - 1;
-            act &= act - 1u;
-            const uint32_t step = sm.foff[d];
-            uint32_t u = (uint32_t)c + step;
-            int len = 1;
-            while ((sm.u.a.same[u] >> d) & 1u) {
-              u += step;
-              ++len;
-            }
-            atomicAdd(&row[len], 1u);
-          }
-        } else {
-          // many (smooth images): the runs of all 13 directions walked
-          // together, one step of each per round (13 independent LDS reads
-          // in flight).  step[d]: positions walked so far; the position
-          // reached is c + step[d] * (forward offset of d, positive), its
-          // byte address one multiply-add
-          const uint32_t walk = act;
-          uint32_t step[13];
-#pragma unroll
-          for (int d = 0; d < 13; ++d) step[d] = 0u;
-          const char* sb0 = reinterpret_cast<const char*>(sm.u.a.same) + 4 * c;
-          while (act) {
-            uint32_t sv[13];
-#pragma unroll
-            for (int d = 0; d < 13; ++d) step[d] += (act >> fwd_bit(d)) & 1u;
-#pragma unroll
-            for (int d = 0; d < 13; ++d)
-              sv[d] = *reinterpret_cast<const uint32_t*>(
-                  sb0 + step[d] * (uint32_t)(4 * ((fdz(d) * S + fdy(d)) * S + fdx(d))));
-            uint32_t go = 0;
-#pragma unroll
-            for (int d = 0; d < 13; ++d) go |= sv[d] & (1u << fwd_bit(d));
-            act &= go;
-          }
-#pragma unroll
-          for (int d = 0; d < 13; ++d)
-            if ((walk >> fwd_bit(d)) & 1u) atomicAdd(&row[step[d]], 1u);
-        }
-      }
-      if (fGLSZM) {
-        uint32_t r = sm.u.a.parent[c];
-        for (uint32_t up; (up = sm.u.a.parent[r]) != r;) r = up;
-        gadd(sm.u.a.zcnt, (int)r, 1u);
-      }
-    }
-  }
   const LevelRow<LMAX> lrow(sm.lval, L, lane);
-  // GLRLM averaged over the directions: each direction's runs counted and
-  // reduced in turn; lane k < 16 keeps the sum of feature k
-  double rl_acc = 0.0;
-  if constexpr (MODE == kAveraged) {
-    if (fGLRLM) {
-#pragma unroll 1
-      for (int d = 0; d < 13; ++d) {
-        __syncthreads();
-        for (int e = lane; e < L * S; e += 64) sm.u.a.glrlm[e] = 0;
-        __syncthreads();
-        const int step = (kDir[d][2] * S + kDir[d][1]) * S + kDir[d][0];
-#pragma unroll 1
-        for (int q = 0; q < NIT; ++q) {
-          const int c = lane + 64 * q;
-          const int l1 = (c < C) ? sm.cl[c] : 0;
-          if (!l1) continue;
-          uint32_t sb = sm.u.a.same[c];
-          if ((sb >> back_bit(d)) & 1u) continue;  // not the start of a run
-          int len = 0, u = c;
-          while ((sb >> fwd_bit(d)) & 1u) {
-            u += step;
-            sb = sm.u.a.same[u];
-            ++len;
-          }
-          atomicAdd(&sm.u.a.glrlm[(l1 - 1) * S + len], 1u);
-        }
-        __syncthreads();
-        if (dbg)
-          for (int e = lane; e < L * S; e += 64)
-            a.d_glrlm[it * a.ng * S + (int64_t)(sm.lval[e / S] - 1) * S + e % S] += (int32_t)sm.u.a.glrlm[e];
-        double f[16];
-        runs_features<R>(sm.u.a.glrlm, lrow, L, lane, (double)K, f);
-        double own = 0.0;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) own = lane == k ? f[k] : own;
-        rl_acc += own;
-      }
-    }
-  }
-  __syncthreads();
-  if constexpr (SM::kHashInSame) {  // the masks are no longer read
-    if (fGLSZM) {
-      static_assert(sizeof(UA::same) >= 6u * HT, "the hash fits the masks' place");
-      clear16(sm.u.a.same, 6 * HT, lane);
-    }
-  }
-
-  // ---- zones: per root ------------------------------------------------
-  Emph ez = {};
-  if (fGLSZM) {
-    // the roots compacted in place (a round writes below the positions that
-    // later rounds read)
-    int n_root = 0;
-#pragma unroll 1
-    for (int q = 0; q < NIT; ++q) {
-      const int c = lane + 64 * q;
-      const bool root = c < C && sm.cl[c] && sm.u.a.parent[c] == (uint32_t)c;
-      const uint64_t m = __ballot(root);
-      if (root)
-        sm.u.a.parent[n_root + below(m)] = (uint32_t)c;
-      n_root += __popcll(m);
-    }
-    __syncthreads();
-#pragma unroll 1
-    for (int k0 = 0; k0 < n_root; k0 += 64) {
-      if (k0 + lane < n_root) {
-        const int c = (int)sm.u.a.parent[k0 + lane];
-        const int l = (int)sm.cl[c] - 1, g = sm.lval[l];
-        const int s = (int)gget(sm.u.a.zcnt, c);
-        emph_add(ez, 1, g, s);  // c log2 c = 0 for c = 1; the entropy comes from the hash
-        atomicAdd(&sm.u.a.zpl[l], 1u);
-        gadd(sm.u.a.zps, s - 1, 1u);
-        const uint32_t key = ((uint32_t)l << 16 | (uint32_t)s) + 1u;
-        // multiplicative hash: the product's high bits mix level and size
-        uint32_t h = (key * 2654435761u) >> (32 - __builtin_ctz((unsigned)HT));
-        while (true) {
-          const uint32_t old = atomicCAS(&sm.hkey()[h], 0u, key);
-          if (old == 0u || old == key) {
-            gadd(sm.hcnt(), (int)h, 1u);
-            break;
-          }
-          h = (h + 1) & (HT - 1);
-        }
-        if (dbg) {
-          const int64_t base = it * (int64_t)a.ng * C;
-          atomicAdd(&a.d_glszm[base + (int64_t)(g - 1) * C + (s - 1)], 1);
-        }
-      }
-    }
-  }
-  __syncthreads();
-
-  // adds this pass's co-occurrence counts to the dense table (lane e mod 64
-  // owns entry e in every pass)
-  auto dump_glcm = [&]() FR_INLINE {
-    const int ng = a.ng;
-    for (int e = lane; e < L * L; e += 64) {
-      const int l = e / L, m = e % L;
-      a.d_glcm[it * ng * ng + (int64_t)(sm.lval[l] - 1) * ng + (sm.lval[m] - 1)] += (int32_t)gsym<SM>(sm.u.a.glcm, l, m);
-    }
-  };
   if (dbg) {
     const int ng = a.ng;
-    if constexpr (MODE != kAveraged) {
-      dump_glcm();
-      for (int e = lane; e < L * S; e += 64) {
-        const int l = e / S, j = e % S;
-        a.d_glrlm[it * ng * S + (int64_t)(sm.lval[l] - 1) * S + j] = (int32_t)sm.u.a.glrlm[e];
-      }
-    }
     for (int e = lane; e < L * 27; e += 64) {
       const int l = e / 27, j = e % 27;
       a.d_gldm[it * ng * 27 + (int64_t)(sm.lval[l] - 1) * 27 + j] = (int32_t)gget(sm.u.a.gldm, l * (2 * SM::kGldmWords) + j);
@@ -2038,73 +1830,30 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     }
   }
 
-  // map offsets of the families in the output
-  int off = 0;
-  const int oFO = off;    off += fFO ? kNFO : 0;
-  const int oGLCM = off;  off += fGLCM ? kNGLCM : 0;
-  const int oGLRLM = off; off += fGLRLM ? kNGLRLM : 0;
-  const int oGLSZM = off; off += fGLSZM ? kNGLSZM : 0;
-  const int oGLDM = off;  off += fGLDM ? kNGLDM : 0;
-  const int oNGTDM = off; off += fNGTDM ? kNNGTDM : 0;
-  const int count = off;
-  float* F = sm.feat();
-  if constexpr (SM::kFeatInZcnt) {
-    using U = typename SM::U;
-    static_assert(offsetof(typename U::A, zcnt) >= sizeof(typename U::B) &&
-                      offsetof(typename U::A, zcnt) >= sizeof(typename U::C) &&
-                      sizeof(U::A::zcnt) >= 96 * sizeof(float),
-                  "the maps overlay the zone sizes");
-  }
-  if (fFO && lane < kNFO) F[oFO + lane] = sm.fo[lane];
-
-  // ---- GLRLM ----------------------------------------------------------
-  if (fGLRLM) {
-    if constexpr (MODE == kAveraged) {
-      if (lane < 16) F[oGLRLM + lane] = (float)(rl_acc / 13.0);
-    } else {
-      float f[16];
-      runs_features<R>(sm.u.a.glrlm, lrow, L, lane, 13.0 * Kd, f);
-      if (lane < 16) F[oGLRLM + lane] = f[lane];
-    }
-  }
-
-  // ---- GLSZM ----------------------------------------------------------
-  if (fGLSZM) {
-    double hl = 0.0;
-    uint32_t nzb = 0;  // bit t: slot lane + 64 t holds a key (HT <= 256)
-    for (int t = 0; lane + 64 * t < HT; ++t) nzb |= (gget(sm.hcnt(), lane + 64 * t) != 0u) << t;
-    while (nzb) {
-      hl += xlog2x<R>(gget(sm.hcnt(), lane + 64 * (__ffs(nzb) - 1)));
-      nzb &= nzb - 1;
-    }
-    ez.clogc = hl;  // zones count once each; the entropy term comes from the hash
-    long long gln = 0, szn = 0;
-    if (lane < L) {
-      const long long t = sm.u.a.zpl[lane];
-      gln = t * t;
-    }
-    for (int s = lane; s < C; s += 64) {
-      const long long t = gget(sm.u.a.zps, s);
-      szn += t * t;
-    }
-    emph_reduce(ez, gln, szn);
-    float f[16];
-    emph16(ez, gln, szn, Kd, xlog2x<R>((uint32_t)ez.n), f);
-    if (lane < 16) F[oGLSZM + lane] = f[lane];
-  }
-
   // ---- GLDM -----------------------------------------------------------
   if (fGLDM) {
     // rows by lane, as the runs; two dependences a word
     constexpr int H = LevelRow<LMAX>::H, NT = (14 + H - 1) / H;
     RowSums rs = {};
+    uint32_t cs[NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int w = t * H + lrow.part;
-      const uint32_t c = lrow.ok ? sm.u.a.gldm[lrow.l * SM::kGldmWords + w] : 0u;
-      if (__ballot(c != 0u) == 0ull) continue;
-      row_add<R>(rs, c & 0xffffu, 2u * w + 1u);
-      row_add<R>(rs, c >> 16, 2u * w + 2u);
+    for (int t = 0; t < NT; ++t)
+      cs[t] = lrow.ok ? sm.u.a.gldm[lrow.l * SM::kGldmWords + t * H + lrow.part] : 0u;
+    auto add = [&](int t) FR_INLINE {
+      const uint32_t w = (uint32_t)(t * H + lrow.part);
+      row_add<R>(rs, cs[t] & 0xffffu, 2u * w + 1u);
+      row_add<R>(rs, cs[t] >> 16, 2u * w + 2u);
+    };
+    // up to 8 (of 27) equal neighbours together, more if any level has them
+    constexpr int T0 = 4 / H;
+    uint32_t rest = 0;
+#pragma unroll
+    for (int t = T0; t < NT; ++t) rest |= cs[t];
+#pragma unroll
+    for (int t = 0; t < T0; ++t) add(t);
+    if (__ballot(rest != 0u) != 0ull) {
+#pragma unroll
+      for (int t = T0; t < NT; ++t) add(t);
     }
     Emph ed = {};
     emph_rows(ed, rs, lrow);
@@ -2121,7 +1870,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     const double N = (double)ed.n;
     const double rN = 1.0 / N, rN2 = rN * rN;  // one division; the rest multiply
     if (lane == 0) {
-      float* f = F + oGLDM;
+      float* f = sm.early + kNFO;
       f[0] = (float)(ed.invj2 * rN);
       f[1] = (float)((double)ed.sj2 * rN);
       f[2] = (float)((double)gln * rN);
@@ -2200,7 +1949,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     wsum8d(rd);
     const long long Nvc = ri[0];
     if (Nvc == 0) {
-      if (lane < kNNGTDM) F[oNGTDM + lane] = NAN;
+      if (lane < kNNGTDM) sm.early[kNFO + kNGLDM + lane] = NAN;
     } else {
       const long long Ngp = ri[1], A1 = ri[2], A2 = ri[3];
       const long long Sn1 = ri[4], Sn2 = ri[5];
@@ -2211,7 +1960,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       bden = ri[6];
       cplx = rd[2];
       if (lane == 0) {
-        float* f = F + oNGTDM;
+        float* f = sm.early + kNFO + kNGLDM;
         // sum_ij p_i p_j (i-j)^2 = 2 Var_p(i);  sum_ij (p_i+p_j)(i-j)^2 =
         // 2 sum_i p_i (Ngp i^2 - 2 i A1 + A2)
         const double c1 = 2.0 * (double)(Nvc * Sn2 - Sn1 * Sn1) / (Nd * Nd);
@@ -2223,6 +1972,406 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
         f[4] = any_s ? (float)(strn / ssum) : 0.f;
       }
     }
+  }
+
+  // the place of those counts is the runs' and zones' now
+  __syncthreads();
+  clear16(sm.u.a.glrlm, L * S * 4, lane);
+  if (lane < L) sm.u.a.zpl[lane] = 0;
+  if constexpr (!SM::kHashInSame) {
+    for (int e = lane; e < HT + HT / 2; e += 64) sm.u.a.hash_m[e] = 0;
+  }
+  __syncthreads();
+
+  // ---- zones: union of the listed edges -------------------------------
+  // parent[c] <= c names a voxel of c's zone: a forest whose roots are the
+  // zones' smallest cube indices once every edge's ends share a root.  An
+  // edge lowers the parent of its larger end; an end that had another
+  // parent goes on with that one, so no connection is lost.  A pass of
+  // minimum labels over all 26 neighbours, repeated until nothing changed
+  // (about four times), had been 14 % of the kernel's VALU instructions and
+  // half its LDS ones; with the runs below counted by kind: 10.8 k -> 7.9 k
+  // VALU and 1,346 -> 790 LDS instructions a voxel, 20.9 -> 16.7 ms for
+  // 1 M voxels of radius 3.
+  //
+  // This pass and the following ones take QB positions a lane at a time,
+  // their LDS reads issued together (14.9 -> 14.3 ms for 1 M voxels of
+  // radius 3).
+  using UA = typename SM::U::A;
+  constexpr int QB = NIT < 6 ? NIT : 6;
+  uint16_t* elist = sm.list();
+  static_assert(SM::NB >= 6 * C, "the edge list holds three edges a voxel");
+  static_assert(C <= 2048, "an entry is a cube index of 11 bits and a mask bit of 5");
+  // levels (compact + 1) and masks of positions 64 (q0 + k) + lane, 0 where
+  // there is no member
+  auto load_masks = [&](int q0, uint32_t(&l1)[QB], uint32_t(&same)[QB]) FR_INLINE {
+#pragma unroll
+    for (int k = 0; k < QB; ++k) {
+      const int c = lane + 64 * (q0 + k), cc = min(c, CP - 1);
+      l1[k] = c < C ? sm.cl[cc] : 0u;
+      same[k] = sm.u.a.same[cc];
+    }
+#pragma unroll
+    for (int k = 0; k < QB; ++k) same[k] = l1[k] ? same[k] : 0u;
+  };
+  if (fGLSZM) {
+    uint32_t* parent = sm.u.a.parent;
+    int n_edge = 0;
+#pragma unroll 1
+    for (int q0 = 0; q0 < NIT; q0 += QB) {
+      uint32_t l1[QB], back[QB], cov[QB];
+      load_masks(q0, l1, back);
+      // the first equal-level neighbour before c is its parent (backward
+      // bits, dx = 0 first: zone bits); no bit: entry 31, 0
+#pragma unroll
+      for (int k = 0; k < QB; ++k) {
+        back[k] = __builtin_amdgcn_perm(0u, back[k] & kBackBits, 0x03020001u);
+        const int b = (__ffs(back[k]) - 1) & 31, c = lane + 64 * (q0 + k);
+        cov[k] = sm.zcov[b];
+        const uint32_t off = sm.zoff[b];
+        if (l1[k]) parent[c] = (uint32_t)c - off;
+      }
+      // the neighbours that no earlier one taken is a neighbour of: edges
+      // (at most three more: four of the half neighbourhood are pairwise
+      // no neighbours)
+      for (;;) {
+        bool any = false;
+#pragma unroll
+        for (int k = 0; k < QB; ++k) {
+          back[k] &= ~cov[k];
+          const uint64_t m = __ballot(back[k] != 0u);
+          const int b = (__ffs(back[k]) - 1) & 31;
+          cov[k] = sm.zcov[b];
+          if (back[k]) elist[n_edge + below(m)] = (uint16_t)((lane + 64 * (q0 + k)) | b << 11);
+          n_edge += __popcll(m);
+          any |= m != 0ull;
+        }
+        if (!any) break;
+      }
+    }
+    __syncthreads();
+    for (int e0 = 0; e0 < n_edge; e0 += 64) {
+      if (e0 + lane < n_edge) {
+        const uint32_t w = elist[e0 + lane];
+        uint32_t u = w & 0x7ffu, v = u - sm.zoff[w >> 11];
+        while (u != v) {
+          const uint32_t hi = max(u, v), lo = min(u, v);
+          const uint32_t old = atomicMin(&parent[hi], lo);
+          if (old == hi) break;
+          u = old;
+          v = lo;
+        }
+      }
+    }
+    __syncthreads();
+  }
+
+  // ---- runs -----------------------------------------------------------
+  // A run of direction d starts where the backward neighbour is not of this
+  // level.  Runs of one voxel (most of them, in images with noise) are
+  // counted together; the longer ones are listed and walked, one a lane, or,
+  // where a position starts many (smooth images), walked all directions
+  // together.
+  if (MODE != kAveraged && fGLRLM) {
+    uint16_t* rlist = sm.list();
+    constexpr int kCap = SM::NB / 2;
+    static_assert(kCap >= 64 * QB, "a round of run starts fits the list");
+    int n_run = 0;
+#pragma unroll 1
+    for (int q0 = 0; q0 < NIT; q0 += QB) {
+      uint32_t l1[QB], act[QB];
+      load_masks(q0, l1, act);
+      bool many = false;
+#pragma unroll
+      for (int k = 0; k < QB; ++k) {
+        const uint32_t same = act[k];
+        // (the backward bits moved to their opposites: bytes 0 and 2 swapped)
+        const uint32_t starts = ~(__builtin_amdgcn_perm(0u, same, 0x03000102u) << 4) & kFwdBits;
+        act[k] = starts & same;
+        const int single = __popc(starts & ~same);
+        if (l1[k] && single) atomicAdd(&sm.u.a.glrlm[((int)l1[k] - 1) * S], (uint32_t)single);
+        many |= __popc(act[k]) > kRunBits;
+      }
+      if (__ballot(many) != 0ull) {
+#pragma unroll 1
+        for (int q = q0; q < q0 + QB && q < NIT; ++q) {
+          const int c = lane + 64 * q;
+          const int lq = c < C ? sm.cl[c] : 0;
+          if (!lq) continue;
+          uint32_t* row = &sm.u.a.glrlm[(lq - 1) * S];
+          const uint32_t same = sm.u.a.same[c];
+          const uint32_t walk = same & ~(__builtin_amdgcn_perm(0u, same, 0x03000102u) << 4) & kFwdBits;
+          // one step of each run per round (13 independent LDS reads in
+          // flight).  step[d]: positions walked so far; the position reached
+          // is c + step[d] * (forward offset of d, positive), its byte
+          // address one multiply-add
+          uint32_t go = walk, step[13];
+#pragma unroll
+          for (int d = 0; d < 13; ++d) step[d] = 0u;
+          const char* sb0 = reinterpret_cast<const char*>(sm.u.a.same) + 4 * c;
+          while (go) {
+            uint32_t sv[13];
+#pragma unroll
+            for (int d = 0; d < 13; ++d) step[d] += (go >> fwd_bit(d)) & 1u;
+#pragma unroll
+            for (int d = 0; d < 13; ++d)
+              sv[d] = *reinterpret_cast<const uint32_t*>(
+                  sb0 + step[d] * (uint32_t)(4 * ((fdz(d) * S + fdy(d)) * S + fdx(d))));
+            uint32_t on = 0;
+#pragma unroll
+            for (int d = 0; d < 13; ++d) on |= sv[d] & (1u << fwd_bit(d));
+            go &= on;
+          }
+#pragma unroll
+          for (int d = 0; d < 13; ++d)
+            if ((walk >> fwd_bit(d)) & 1u) atomicAdd(&row[step[d]], 1u);
+        }
+        continue;
+      }
+      for (bool any = true; any;) {  // one run of every position a round
+        any = false;
+#pragma unroll
+        for (int k = 0; k < QB; ++k) {
+          const uint64_t m = __ballot(act[k] != 0u);
+          if (act[k]) rlist[n_run + below(m)] = (uint16_t)((lane + 64 * (q0 + k)) | (__ffs(act[k]) - 1) << 11);
+          act[k] &= act[k] - 1u;
+          n_run += __popcll(m);
+          any |= m != 0ull;
+        }
+        if (n_run > 0 && (n_run > kCap - 64 * QB || (!any && q0 + QB >= NIT))) {
+          __syncthreads();
+          for (int e0 = 0; e0 < n_run; e0 += 64) {
+            if (e0 + lane < n_run) {
+              const uint32_t w = rlist[e0 + lane];
+              const int c = (int)(w & 0x7ffu), b = (int)(w >> 11);
+              const uint32_t step = sm.foff[b];
+              uint32_t* row = &sm.u.a.glrlm[((int)sm.cl[c] - 1) * S];
+              uint32_t u = (uint32_t)c + step;
+              int len = 1;
+              while ((sm.u.a.same[u] >> b) & 1u) {
+                u += step;
+                ++len;
+              }
+              atomicAdd(&row[len], 1u);
+            }
+          }
+          __syncthreads();
+          n_run = 0;
+        }
+      }
+    }
+    if (n_run > 0) {  // the last chunk's runs were walked all together: the listed ones before it remain
+      __syncthreads();
+      for (int e0 = 0; e0 < n_run; e0 += 64) {
+        if (e0 + lane < n_run) {
+          const uint32_t w = rlist[e0 + lane];
+          const int c = (int)(w & 0x7ffu), b = (int)(w >> 11);
+          const uint32_t step = sm.foff[b];
+          uint32_t u = (uint32_t)c + step;
+          int len = 1;
+          while ((sm.u.a.same[u] >> b) & 1u) {
+            u += step;
+            ++len;
+          }
+          atomicAdd(&sm.u.a.glrlm[((int)sm.cl[c] - 1) * S + len], 1u);
+        }
+      }
+    }
+    __syncthreads();
+  }
+  // GLRLM averaged over the directions: each direction's runs counted and
+  // reduced in turn; lane k < 16 keeps the sum of feature k
+  double rl_acc = 0.0;
+  if constexpr (MODE == kAveraged) {
+    if (fGLRLM) {
+#pragma unroll 1
+      for (int d = 0; d < 13; ++d) {
+        __syncthreads();
+        for (int e = lane; e < L * S; e += 64) sm.u.a.glrlm[e] = 0;
+        __syncthreads();
+        const int step = (kDir[d][2] * S + kDir[d][1]) * S + kDir[d][0];
+#pragma unroll 1
+        for (int q = 0; q < NIT; ++q) {
+          const int c = lane + 64 * q;
+          const int l1 = (c < C) ? sm.cl[c] : 0;
+          if (!l1) continue;
+          uint32_t sb = sm.u.a.same[c];
+          if ((sb >> back_bit(d)) & 1u) continue;  // not the start of a run
+          int len = 0, u = c;
+          while ((sb >> fwd_bit(d)) & 1u) {
+            u += step;
+            sb = sm.u.a.same[u];
+            ++len;
+          }
+          atomicAdd(&sm.u.a.glrlm[(l1 - 1) * S + len], 1u);
+        }
+        __syncthreads();
+        if (dbg)
+          for (int e = lane; e < L * S; e += 64)
+            a.d_glrlm[it * a.ng * S + (int64_t)(sm.lval[e / S] - 1) * S + e % S] += (int32_t)sm.u.a.glrlm[e];
+        double f[16];
+        runs_features<R>(sm.u.a.glrlm, lrow, L, lane, (double)K, f);
+        double own = 0.0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) own = lane == k ? f[k] : own;
+        rl_acc += own;
+      }
+    }
+  }
+  __syncthreads();
+
+  // ---- zone sizes, then the zones, a lane each ------------------------
+  Emph ez = {};
+  if (fGLSZM) {
+    // the run list's place and the hash; the masks are no longer read
+    clear16(sm.zcnt(), SM::kZoneBytes, lane);
+    if constexpr (SM::kHashInSame) {
+      static_assert(sizeof(UA::same) >= 6u * HT, "the hash fits the masks' place");
+      clear16(sm.u.a.same, 6 * HT, lane);
+    }
+    __syncthreads();
+    uint32_t* parent = sm.u.a.parent;
+    uint64_t roots[NIT];
+#pragma unroll
+    for (int q0 = 0; q0 < NIT; q0 += QB) {
+      uint32_t l1[QB], r[QB];
+#pragma unroll
+      for (int k = 0; k < QB && q0 + k < NIT; ++k) {
+        const int c = lane + 64 * (q0 + k);
+        l1[k] = c < C ? sm.cl[c] : 0u;
+        r[k] = parent[c];
+      }
+#pragma unroll
+      for (int k = 0; k < QB && q0 + k < NIT; ++k) {
+        const uint32_t c = (uint32_t)(lane + 64 * (q0 + k));
+        roots[q0 + k] = __ballot(l1[k] && r[k] == c);
+        r[k] = l1[k] ? r[k] : c;
+      }
+      for (bool moved = true; moved;) {
+        uint32_t up[QB];
+        moved = false;
+#pragma unroll
+        for (int k = 0; k < QB && q0 + k < NIT; ++k) up[k] = parent[r[k]];
+#pragma unroll
+        for (int k = 0; k < QB && q0 + k < NIT; ++k) {
+          moved |= l1[k] && up[k] != r[k];
+          r[k] = l1[k] ? up[k] : r[k];
+        }
+        moved = __ballot(moved) != 0ull;
+      }
+#pragma unroll
+      for (int k = 0; k < QB && q0 + k < NIT; ++k)
+        if (l1[k]) gadd(sm.zcnt(), (int)r[k], 1u);
+    }
+    __syncthreads();
+    // the roots listed in place of the forest
+    int n_root = 0;
+#pragma unroll
+    for (int q = 0; q < NIT; ++q) {
+      if ((roots[q] >> lane) & 1ull) parent[n_root + below(roots[q])] = (uint32_t)(lane + 64 * q);
+      n_root += __popcll(roots[q]);
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int k0 = 0; k0 < n_root; k0 += 64) {
+      if (k0 + lane < n_root) {
+        const int c = (int)parent[k0 + lane];
+        const int l = (int)sm.cl[c] - 1, g = sm.lval[l];
+        const int s = (int)gget(sm.zcnt(), c);
+        emph_add(ez, 1, g, s);  // c log2 c = 0 for c = 1; the entropy comes from the hash
+        atomicAdd(&sm.u.a.zpl[l], 1u);
+        gadd(sm.zps(), s - 1, 1u);
+        const uint32_t key = ((uint32_t)l << 16 | (uint32_t)s) + 1u;
+        // multiplicative hash: the product's high bits mix level and size
+        uint32_t h = (key * 2654435761u) >> (32 - __builtin_ctz((unsigned)HT));
+        while (true) {
+          const uint32_t old = atomicCAS(&sm.hkey()[h], 0u, key);
+          if (old == 0u || old == key) {
+            gadd(sm.hcnt(), (int)h, 1u);
+            break;
+          }
+          h = (h + 1) & (HT - 1);
+        }
+        if (dbg) {
+          const int64_t base = it * (int64_t)a.ng * C;
+          atomicAdd(&a.d_glszm[base + (int64_t)(g - 1) * C + (s - 1)], 1);
+        }
+      }
+    }
+  }
+  __syncthreads();
+
+  // adds this pass's co-occurrence counts to the dense table (lane e mod 64
+  // owns entry e in every pass)
+  auto dump_glcm = [&]() FR_INLINE {
+    const int ng = a.ng;
+    for (int e = lane; e < L * L; e += 64) {
+      const int l = e / L, m = e % L;
+      a.d_glcm[it * ng * ng + (int64_t)(sm.lval[l] - 1) * ng + (sm.lval[m] - 1)] += (int32_t)gsym<SM>(sm.u.a.glcm, l, m);
+    }
+  };
+  if (dbg) {
+    const int ng = a.ng;
+    if constexpr (MODE != kAveraged) {
+      dump_glcm();
+      for (int e = lane; e < L * S; e += 64) {
+        const int l = e / S, j = e % S;
+        a.d_glrlm[it * ng * S + (int64_t)(sm.lval[l] - 1) * S + j] = (int32_t)sm.u.a.glrlm[e];
+      }
+    }
+  }
+
+  // map offsets of the families in the output
+  int off = 0;
+  const int oFO = off;    off += fFO ? kNFO : 0;
+  const int oGLCM = off;  off += fGLCM ? kNGLCM : 0;
+  const int oGLRLM = off; off += fGLRLM ? kNGLRLM : 0;
+  const int oGLSZM = off; off += fGLSZM ? kNGLSZM : 0;
+  const int oGLDM = off;  off += fGLDM ? kNGLDM : 0;
+  const int oNGTDM = off; off += fNGTDM ? kNNGTDM : 0;
+  const int count = off;
+  float* F = sm.feat();
+  if (fFO && lane < kNFO) F[oFO + lane] = sm.early[lane];
+  if (fGLDM && lane < kNGLDM) F[oGLDM + lane] = sm.early[kNFO + lane];
+  if (fNGTDM && lane < kNNGTDM) F[oNGTDM + lane] = sm.early[kNFO + kNGLDM + lane];
+
+  // ---- GLRLM ----------------------------------------------------------
+  if (fGLRLM) {
+    if constexpr (MODE == kAveraged) {
+      if (lane < 16) F[oGLRLM + lane] = (float)(rl_acc / 13.0);
+    } else {
+      float f[16];
+      runs_features<R>(sm.u.a.glrlm, lrow, L, lane, 13.0 * Kd, f);
+      if (lane == 0)
+        for (int k = 0; k < 16; ++k) F[oGLRLM + k] = f[k];
+    }
+  }
+
+  // ---- GLSZM ----------------------------------------------------------
+  if (fGLSZM) {
+    double hl = 0.0;
+#pragma unroll
+    for (int t = 0; t < HT / 2; t += 64) {  // two counts a word; 0 log 0 = 0
+      const uint32_t w = t + lane < HT / 2 ? sm.hcnt()[t + lane] : 0u;
+      hl += xlog2x<R>(w & 0xffffu) + xlog2x<R>(w >> 16);
+    }
+    ez.clogc = hl;  // zones count once each; the entropy term comes from the hash
+    long long gln = 0;
+    if (lane < L) {
+      const long long t = sm.u.a.zpl[lane];
+      gln = t * t;
+    }
+    uint32_t szs = 0;  // total at most C^2 = 1.8e6
+    for (int e = lane; e < CP / 2; e += 64) {
+      const uint32_t w = sm.zps()[e];
+      szs += __umul24(w & 0xffffu, w & 0xffffu) + __umul24(w >> 16, w >> 16);
+    }
+    long long szn = szs;
+    emph_reduce(ez, gln, szn);
+    float f[16];
+    emph16(ez, gln, szn, Kd, xlog2x<R>((uint32_t)ez.n), f);
+    if (lane == 0)
+      for (int k = 0; k < 16; ++k) F[oGLSZM + k] = f[k];
   }
 
   // ---- GLCM (last: its eigen work space overlays the tables above) -----
