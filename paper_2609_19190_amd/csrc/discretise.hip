@@ -9,8 +9,9 @@
 //   k_disc_levels  level of every voxel (0 outside the mask) and the
 //                  raster-ordered list of mask voxels (compact index ->
 //                  linear index), each segment writing at its scanned offset
-// Loads are lane-interleaved inside a segment (element j*256 + t), so every
-// wavefront load and store is contiguous.
+// (one launch, k_disc_small, up to 65,536 voxels).  A segment's loads are
+// lane-interleaved groups of four voxels, all in flight before the first is
+// used.
 #include <math.h>
 
 #include "fr_internal.h"
@@ -18,48 +19,157 @@
 namespace fr {
 namespace {
 
+// A thread takes groups of four consecutive voxels: 16-byte (float) or 8-byte
+// (int16) volume loads and 4-byte mask loads and level stores, where the
+// pointers are aligned to them (a sub-volume need not be), otherwise voxel
+// by voxel; likewise past the last whole group.
+constexpr int kGroup = 4;
+template <typename T>
+__device__ inline bool aligned4(const T* vol, const uint8_t* mask, const uint8_t* levels) {
+  return (((uintptr_t)vol & (kGroup * sizeof(T) - 1)) | ((uintptr_t)mask & (kGroup - 1)) |
+          ((uintptr_t)levels & (kGroup - 1))) == 0;
+}
+// Voxels i .. i + 3: values x and a bit per mask voxel.
+template <typename T>
+__device__ inline uint32_t load4(const T* __restrict__ vol, const uint8_t* __restrict__ mask, int64_t i, int64_t n,
+                                 bool vec, T (&x)[kGroup]) {
+  uint32_t in = 0;
+  if (vec && i + kGroup <= n) {
+    struct alignas(kGroup * sizeof(T)) V {
+      T v[kGroup];
+    };
+    const V v = *(const V*)(vol + i);
+    const uint32_t m = *(const uint32_t*)(mask + i);
+#pragma unroll
+    for (int e = 0; e < kGroup; ++e) {
+      x[e] = v.v[e];
+      in |= (uint32_t)(((m >> (8 * e)) & 0xffu) != 0u) << e;
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < kGroup; ++e) {
+      x[e] = 0;
+      if (i + e < n) {
+        x[e] = vol[i + e];
+        in |= (uint32_t)(mask[i + e] != 0) << e;
+      }
+    }
+  }
+  return in;
+}
+__device__ inline void store4(uint8_t* levels, int64_t i, int64_t n, bool vec, const int (&g)[kGroup]) {
+  if (vec && i + kGroup <= n) {
+    *(uint32_t*)(levels + i) = (uint32_t)g[0] | (uint32_t)g[1] << 8 | (uint32_t)g[2] << 16 | (uint32_t)g[3] << 24;
+  } else {
+#pragma unroll
+    for (int e = 0; e < kGroup; ++e)
+      if (i + e < n) levels[i + e] = (uint8_t)g[e];
+  }
+}
+// Level of a VOI value (FP64, contraction off: see fr.h).
+__device__ inline int level_of(double x, int mode, double value, double xmin, double lo, double range, int ng) {
+#pragma clang fp contract(off)
+  int g = 1;
+  if (mode == 2) {
+    if (range > 0.0) {
+      const double t = x - xmin;
+      const double q = ((double)ng * t) / range;
+      g = (int)floor(q) + 1;
+      if (g > ng) g = ng;
+    }
+  } else {
+    const double t = x - lo;
+    double gg = floor(t / value) + 1.0;
+    if (gg < 1.0) gg = 1.0;
+    if (gg > 255.0) gg = 255.0;
+    g = (int)gg;
+  }
+  return g;
+}
+// Mask voxels of lower lanes in a group per lane.
+__device__ inline int group_prefix(uint32_t in) {
+  int before = 0;
+#pragma unroll
+  for (int e = 0; e < kGroup; ++e) {
+    const uint64_t b = __ballot((in >> e) & 1u);
+    before += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+  }
+  return before;
+}
+// The parameter block of a VOI of count voxels in [mn, mx].
+__device__ inline DiscParams disc_params(double mn, double mx, long long count, int mode, double value, double lower,
+                                         int64_t expect_count) {
+  DiscParams p;
+  p.xmin = mn;
+  p.xmax = mx;
+  p.count = count;
+  p.err = 0;
+  if (mode == 2) {  // fixed bin number: Ng given
+    p.lo = mn;
+    p.ng = (int32_t)value;
+  } else {  // fixed bin width: Ng = level of the VOI maximum
+#pragma clang fp contract(off)
+    p.lo = isfinite(lower) ? lower : mn;
+    const double qmax = floor((mx - p.lo) / value) + 1.0;
+    if (!(qmax <= 255.0)) p.err = kJobNgRange;
+    p.ng = qmax < 1.0 ? 1 : (qmax > 255.0 ? 255 : (int32_t)qmax);
+  }
+  if (count == 0) p.err = kJobEmpty;
+  if (p.err == 0 && expect_count >= 0 && count != expect_count) p.err = kJobCount;
+  return p;
+}
+
+constexpr int kDiscGroups = kDiscPerThread / kGroup;  // of a thread in a segment
+
 // Mask count, min and max of one 4096-voxel segment, written at `slot`.
 template <typename T>
 __device__ inline void disc_stats_seg(const T* __restrict__ vol, const uint8_t* __restrict__ mask,
                                       int64_t n, int64_t seg, int64_t slot, int32_t* bcount,
                                       double* bmin, double* bmax) {
   const int64_t base = seg * kDiscSeg;
+  const bool vec = aligned4(vol, mask, (const uint8_t*)nullptr);
   int cnt = 0;
-  double mn = INFINITY, mx = -INFINITY;
+  float fmn = INFINITY, fmx = -INFINITY;  // exact for both raw types
+  T x[kDiscGroups][kGroup];
+  uint32_t in[kDiscGroups];
 #pragma unroll
-  for (int j = 0; j < kDiscPerThread; ++j) {
-    const int64_t i = base + j * kDiscThreads + threadIdx.x;
-    if (i < n && mask[i]) {
-      const double x = (double)vol[i];
-      cnt++;
-      mn = fmin(mn, x);
-      mx = fmax(mx, x);
+  for (int j = 0; j < kDiscGroups; ++j)
+    in[j] = load4(vol, mask, base + (int64_t)(j * kDiscThreads + threadIdx.x) * kGroup, n, vec, x[j]);
+#pragma unroll
+  for (int j = 0; j < kDiscGroups; ++j) {
+    cnt += __popc(in[j]);
+#pragma unroll
+    for (int e = 0; e < kGroup; ++e) {
+      if ((in[j] >> e) & 1u) {
+        fmn = fminf(fmn, (float)x[j][e]);
+        fmx = fmaxf(fmx, (float)x[j][e]);
+      }
     }
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     cnt += __shfl_xor(cnt, o);
-    mn = fmin(mn, __shfl_xor(mn, o));
-    mx = fmax(mx, __shfl_xor(mx, o));
+    fmn = fminf(fmn, __shfl_xor(fmn, o));
+    fmx = fmaxf(fmx, __shfl_xor(fmx, o));
   }
   __shared__ int sc[kDiscThreads / 64];
-  __shared__ double smn[kDiscThreads / 64], smx[kDiscThreads / 64];
+  __shared__ float smn[kDiscThreads / 64], smx[kDiscThreads / 64];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   if (lane == 0) {
     sc[w] = cnt;
-    smn[w] = mn;
-    smx[w] = mx;
+    smn[w] = fmn;
+    smx[w] = fmx;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int q = 1; q < kDiscThreads / 64; ++q) {
       cnt += sc[q];
-      mn = fmin(mn, smn[q]);
-      mx = fmax(mx, smx[q]);
+      fmn = fminf(fmn, smn[q]);
+      fmx = fmaxf(fmx, smx[q]);
     }
     bcount[slot] = cnt;
-    bmin[slot] = mn;
-    bmax[slot] = mx;
+    bmin[slot] = (double)fmn;
+    bmax[slot] = (double)fmx;
   }
 }
 
@@ -71,8 +181,14 @@ __global__ __launch_bounds__(kDiscThreads) void k_disc_stats(const T* __restrict
   disc_stats_seg(vol, mask, n, blockIdx.x, blockIdx.x, bcount, bmin, bmax);
 }
 
-constexpr int kScanThreads = 1024;
-static_assert(kScanThreads == kCountInts, "the scan zeroes a counter block, one counter a thread");
+// Four waves: a wider block finds room late where other jobs' map kernels
+// fill the CUs (at 1,024 threads a served job's scan waited 215 us on
+// average for a start).
+constexpr int kScanThreads = 256;
+__device__ inline void zero_counts(int32_t* counts, int threads) {
+  if (counts)
+    for (int k = (int)threadIdx.x; k < kCountInts; k += threads) counts[k] = 0;
+}
 
 // Exclusive scan of the counts of segments [s0, s0 + nb), the VOI min/max
 // and the gray-level count, written to *P (one block of kScanThreads).
@@ -136,24 +252,7 @@ __device__ inline void disc_scan_range(int64_t s0, int64_t nb, const int32_t* bc
       mn = fmin(mn, wmn[q]);
       mx = fmax(mx, wmx[q]);
     }
-    DiscParams p;
-    p.xmin = mn;
-    p.xmax = mx;
-    p.count = carry;
-    p.err = 0;
-    if (mode == 2) {  // fixed bin number: Ng given
-      p.lo = mn;
-      p.ng = (int32_t)value;
-    } else {  // fixed bin width: Ng = level of the VOI maximum
-#pragma clang fp contract(off)
-      p.lo = isfinite(lower) ? lower : mn;
-      const double qmax = floor((mx - p.lo) / value) + 1.0;
-      if (!(qmax <= 255.0)) p.err = kJobNgRange;
-      p.ng = qmax < 1.0 ? 1 : (qmax > 255.0 ? 255 : (int32_t)qmax);
-    }
-    if (carry == 0) p.err = kJobEmpty;
-    if (p.err == 0 && expect_count >= 0 && carry != expect_count) p.err = kJobCount;
-    *P = p;
+    *P = disc_params(mn, mx, carry, mode, value, lower, expect_count);
   }
 }
 
@@ -164,7 +263,7 @@ __global__ __launch_bounds__(kScanThreads) void k_disc_scan(int64_t nb, const in
                                                             DiscParams* P, int mode, double value,
                                                             double lower, int64_t expect_count,
                                                             int32_t* counts) {
-  if (counts) counts[threadIdx.x] = 0;
+  zero_counts(counts, kScanThreads);
   disc_scan_range(0, nb, bcount, bmin, bmax, boff, P, mode, value, lower, expect_count);
 }
 
@@ -175,54 +274,155 @@ __device__ inline void disc_levels_seg(const T* __restrict__ vol, const uint8_t*
                                        int64_t n, int64_t seg, int64_t off,
                                        const DiscParams* P, int mode, double value,
                                        uint8_t* levels, int32_t* list) {
-#pragma clang fp contract(off)
-  __shared__ int wcnt[kDiscThreads / 64];
+  __shared__ int wcnt[kDiscGroups][kDiscThreads / 64];
   const double xmin = P->xmin, lo = P->lo;
   const double range = P->xmax - P->xmin;
   const int ng = P->ng;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   const int64_t base = seg * kDiscSeg;
+  const bool vec = aligned4(vol, mask, levels);
+  T x[kDiscGroups][kGroup];
+  uint32_t in[kDiscGroups];
+  int before[kDiscGroups];
+#pragma unroll
+  for (int j = 0; j < kDiscGroups; ++j)
+    in[j] = load4(vol, mask, base + (int64_t)(j * kDiscThreads + threadIdx.x) * kGroup, n, vec, x[j]);
+#pragma unroll
+  for (int j = 0; j < kDiscGroups; ++j) {
+    before[j] = group_prefix(in[j]);
+    if (lane == 63) wcnt[j][w] = before[j] + __popc(in[j]);
+  }
+  __syncthreads();
   int64_t pos = off;
-  for (int j = 0; j < kDiscPerThread; ++j) {
-    const int64_t i = base + j * kDiscThreads + threadIdx.x;
-    const bool in = i < n && mask[i] != 0;
-    int g = 0;
-    if (in) {
-      const double x = (double)vol[i];
-      if (mode == 2) {
-        g = 1;
-        if (range > 0.0) {
-          const double t = x - xmin;
-          const double q = ((double)ng * t) / range;
-          g = (int)floor(q) + 1;
-          if (g > ng) g = ng;
-        }
-      } else {
-        const double t = x - lo;
-        double gg = floor(t / value) + 1.0;
-        if (gg < 1.0) gg = 1.0;
-        if (gg > 255.0) gg = 255.0;
-        g = (int)gg;
-      }
-    }
-    if (i < n) levels[i] = (uint8_t)g;
-    const uint64_t b = __ballot(in);
-    if (lane == 0) wcnt[w] = __popcll(b);
-    __syncthreads();
-    int before = 0, total = 0;
+  // a call whose mask count disagrees with n_mask stops here: its list may
+  // have no room for every mask voxel
+  const bool listed = P->err != kJobCount;
+#pragma unroll
+  for (int j = 0; j < kDiscGroups; ++j) {
+    const int64_t i = base + (int64_t)(j * kDiscThreads + threadIdx.x) * kGroup;
+    int head = 0, total = 0;
 #pragma unroll
     for (int q = 0; q < kDiscThreads / 64; ++q) {
-      const int c = wcnt[q];
-      before += (q < w) ? c : 0;
+      const int c = wcnt[j][q];
+      head += (q < w) ? c : 0;
       total += c;
     }
-    if (in) list[pos + before + __popcll(b & below)] = (int32_t)i;
+    int64_t at = pos + head + before[j];
     pos += total;
-    __syncthreads();
+    int g[kGroup];
+#pragma unroll
+    for (int e = 0; e < kGroup; ++e) {
+      g[e] = 0;
+      if ((in[j] >> e) & 1u) {
+        g[e] = level_of((double)x[j][e], mode, value, xmin, lo, range, ng);
+        if (listed) list[at++] = (int32_t)(i + e);
+      }
+    }
+    store4(levels, i, n, vec, g);
   }
 }
 
+// The whole discretisation of a small volume in one workgroup: its values
+// stay in registers between the statistics and the levels.  Three launches
+// of a few microseconds each become one (with the maps written directly, a
+// call of 2,145 mask voxels in 24 k: 52.6 -> 35.3 us, of 1,537 in 8 k: 84 ->
+// 63 us); beyond kDiscSmall voxels one CU's bandwidth costs more than the
+// launches.
+constexpr int kSmallThreads = 1024, kSmallGroups = 16;
+constexpr int64_t kDiscSmall = (int64_t)kSmallThreads * kSmallGroups * kGroup;  // 65,536
+template <typename T>
+__global__ __launch_bounds__(kSmallThreads) void k_disc_small(const T* __restrict__ vol,
+                                                              const uint8_t* __restrict__ mask, int64_t n, int mode,
+                                                              double value, double lower, int64_t expect_count,
+                                                              uint8_t* levels, int32_t* list, DiscParams* P,
+                                                              int32_t* counts) {
+  constexpr int W = kSmallThreads / 64;
+  __shared__ int wcnt[kSmallGroups][W];
+  __shared__ float smn[W], smx[W];
+  __shared__ int total;
+  zero_counts(counts, kSmallThreads);
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  const bool vec = aligned4(vol, mask, levels);
+  const int groups = (int)((n + kSmallThreads * kGroup - 1) / (kSmallThreads * kGroup));
+  T x[kSmallGroups][kGroup];
+  uint32_t in[kSmallGroups];
+#pragma unroll
+  for (int j = 0; j < kSmallGroups; ++j) {
+    in[j] = 0;
+    if (j < groups) in[j] = load4(vol, mask, (int64_t)(j * kSmallThreads + t) * kGroup, n, vec, x[j]);
+  }
+  float fmn = INFINITY, fmx = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < kSmallGroups; ++j) {
+    if (j >= groups) continue;
+#pragma unroll
+    for (int e = 0; e < kGroup; ++e) {
+      if ((in[j] >> e) & 1u) {
+        fmn = fminf(fmn, (float)x[j][e]);
+        fmx = fmaxf(fmx, (float)x[j][e]);
+      }
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    fmn = fminf(fmn, __shfl_xor(fmn, o));
+    fmx = fmaxf(fmx, __shfl_xor(fmx, o));
+  }
+  if (lane == 0) {
+    smn[w] = fmn;
+    smx[w] = fmx;
+  }
+  int before[kSmallGroups];
+#pragma unroll
+  for (int j = 0; j < kSmallGroups; ++j) {
+    before[j] = 0;
+    if (j < groups) before[j] = group_prefix(in[j]);
+    if (lane == 63) wcnt[j][w] = before[j] + __popc(in[j]);
+  }
+  __syncthreads();
+  if (w == 0) {  // exclusive scan of the 256 wave counts, group by group, four a lane
+    int* c = &wcnt[0][0] + 4 * lane;
+    const int c0 = c[0], c1 = c[1], c2 = c[2], sum = c0 + c1 + c2 + c[3];
+    int inc = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(inc, o);
+      if (lane >= o) inc += y;
+    }
+    c[0] = inc - sum;
+    c[1] = inc - sum + c0;
+    c[2] = inc - sum + c0 + c1;
+    c[3] = inc - sum + c0 + c1 + c2;
+    if (lane == 63) total = inc;
+  }
+  __syncthreads();
+  fmn = smn[0];
+  fmx = smx[0];
+#pragma unroll
+  for (int q = 1; q < W; ++q) {
+    fmn = fminf(fmn, smn[q]);
+    fmx = fmaxf(fmx, smx[q]);
+  }
+  const DiscParams p = disc_params((double)fmn, (double)fmx, total, mode, value, lower, expect_count);
+  if (t == 0) *P = p;
+  const double range = p.xmax - p.xmin;
+#pragma unroll
+  for (int j = 0; j < kSmallGroups; ++j) {
+    if (j >= groups) continue;
+    const int64_t i = (int64_t)(j * kSmallThreads + t) * kGroup;
+    int at = wcnt[j][w] + before[j];
+    int g[kGroup];
+#pragma unroll
+    for (int e = 0; e < kGroup; ++e) {
+      g[e] = 0;
+      if ((in[j] >> e) & 1u) {
+        g[e] = level_of((double)x[j][e], mode, value, p.xmin, p.lo, range, p.ng);
+        if (p.err != kJobCount) list[at++] = (int32_t)(i + e);
+      }
+    }
+    store4(levels, i, n, vec, g);
+  }
+}
 
 template <typename T>
 __global__ __launch_bounds__(kDiscThreads) void k_disc_levels(const T* __restrict__ vol,
@@ -252,7 +452,7 @@ __global__ __launch_bounds__(kScanThreads) void k_bdisc_scan(const BatchJob* __r
                                                              const double* bmin, const double* bmax,
                                                              int64_t* boff, DiscParams* params,
                                                              int32_t* counts) {
-  if (counts) counts[threadIdx.x] = 0;  // a single job's
+  zero_counts(counts, kScanThreads);  // a single job's
   const BatchJob& J = jobs[blockIdx.x];
   disc_scan_range(J.seg_base, J.nseg, bcount, bmin, bmax, boff, &params[blockIdx.x], J.mode,
                   J.value, J.lower, J.n_mask);
@@ -300,6 +500,15 @@ hipError_t launch_discretise(const void* vol, int dtype, int64_t nvox, const uin
                              int mode, double value, double lower, uint8_t* levels,
                              int32_t* list, const DiscScratch& s, int64_t expect_count,
                              hipStream_t st) {
+  if (nvox <= kDiscSmall) {
+    if (dtype == 1)
+      hipLaunchKernelGGL(k_disc_small<int16_t>, dim3(1), dim3(kSmallThreads), 0, st, (const int16_t*)vol, mask, nvox,
+                         mode, value, lower, expect_count, levels, list, s.params, s.counts);
+    else
+      hipLaunchKernelGGL(k_disc_small<float>, dim3(1), dim3(kSmallThreads), 0, st, (const float*)vol, mask, nvox,
+                         mode, value, lower, expect_count, levels, list, s.params, s.counts);
+    return hipGetLastError();
+  }
   const dim3 grid((unsigned)s.nblocks), block(kDiscThreads);
   if (dtype == 1) {
     hipLaunchKernelGGL(k_disc_stats<int16_t>, grid, block, 0, st, (const int16_t*)vol, mask,

@@ -33,45 +33,51 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
 }
 
 // Tile transpose of the staging rows: 64 voxels x up to 96 maps per block
-// through LDS, so both the row reads and the per-map writes (64 consecutive
-// floats) are contiguous.
+// through LDS, so both the row reads (16 bytes a lane, all of a thread's in
+// flight together) and the per-map writes (64 consecutive floats) are
+// contiguous.
+__device__ inline void transpose_tile(const float* __restrict__ stage, float* __restrict__ out, int64_t n, int64_t m0,
+                                      int count) {
+  __shared__ float tile[64][kStageStride + 1];
+  constexpr int Q = kStageStride / 4, PER = 64 * Q / 256;
+  const int t = threadIdx.x;
+  float4 r[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int e = t + 256 * i, v = e / Q, k = 4 * (e % Q);
+    r[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (m0 + v < n && k < count) r[i] = *(const float4*)(stage + (m0 + v) * kStageStride + k);
+  }
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int e = t + 256 * i, v = e / Q, k = 4 * (e % Q);
+    tile[v][k] = r[i].x;
+    tile[v][k + 1] = r[i].y;
+    tile[v][k + 2] = r[i].z;
+    tile[v][k + 3] = r[i].w;
+  }
+  __syncthreads();
+  const int v = t % 64;
+  if (m0 + v < n) {
+#pragma unroll 4
+    for (int k = t / 64; k < count; k += 4) out[(int64_t)k * n + m0 + v] = tile[v][k];
+  }
+}
+
 __global__ __launch_bounds__(256) void k_transpose(const float* __restrict__ stage,
                                                    float* __restrict__ out, int64_t n,
                                                    int count, const DiscParams* __restrict__ params) {
-  __shared__ float tile[64][kStageStride + 1];
   if (params->err != kJobOk) return;
-  const int64_t m0 = (int64_t)blockIdx.x * 64;
-  const int t = threadIdx.x;
-  for (int e = t; e < 64 * kStageStride; e += 256) {
-    const int v = e / kStageStride, k = e % kStageStride;
-    if (m0 + v < n && k < count) tile[v][k] = stage[(m0 + v) * kStageStride + k];
-  }
-  __syncthreads();
-  for (int e = t; e < 64 * count; e += 256) {
-    const int k = e / 64, v = e % 64;
-    if (m0 + v < n) out[(int64_t)k * n + m0 + v] = tile[v][k];
-  }
+  transpose_tile(stage, out, n, (int64_t)blockIdx.x * 64, count);
 }
 
 __global__ __launch_bounds__(256) void k_transpose_batch(const BatchJob* __restrict__ jobs,
                                                          const DiscParams* __restrict__ params,
                                                          const int2* __restrict__ items) {
-  __shared__ float tile[64][kStageStride + 1];
   const int2 it2 = items ? items[blockIdx.x] : make_int2(0, (int)blockIdx.x * 64);
   const BatchJob& J = jobs[it2.x];
   if (params[it2.x].err != kJobOk) return;
-  const int64_t n = J.n_mask, m0 = it2.y;
-  const int count = J.count;
-  const int t = threadIdx.x;
-  for (int e = t; e < 64 * kStageStride; e += 256) {
-    const int v = e / kStageStride, k = e % kStageStride;
-    if (m0 + v < n && k < count) tile[v][k] = J.stage[(m0 + v) * kStageStride + k];
-  }
-  __syncthreads();
-  for (int e = t; e < 64 * count; e += 256) {
-    const int k = e / 64, v = e % 64;
-    if (m0 + v < n) J.out[(int64_t)k * n + m0 + v] = tile[v][k];
-  }
+  transpose_tile(J.stage, J.out, J.n_mask, it2.y, J.count);
 }
 
 }  // namespace

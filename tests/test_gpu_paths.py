@@ -1,0 +1,121 @@
+"""GPU parity where a call's route changes with its size, alignment or data:
+the one-launch discretisation (up to 65,536 voxels) and the three kernels
+beyond, whole and partial groups of four voxels, pointers off the vector
+alignment; maps written directly (up to 4,096 voxels) and through staging
+rows; the allocation-free entry point with and without room for the MCC
+stash; and the order statistics over every size of the sorted subset.
+"""
+import numpy as np
+import pytest
+
+from helpers import format_report, parity_report, to_dev
+from oracle import oracle as O
+from paper_2609_19190_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_19190_amd import binding
+    binding.lib()
+    return binding
+
+
+def shifted(x, by):
+    """x on the device, `by` elements past an aligned address."""
+    import torch
+    buf = torch.empty(x.size + by, dtype=torch.from_numpy(x).dtype, device="cuda:0")
+    buf[by:] = torch.from_numpy(x.reshape(-1)).to("cuda:0")
+    return buf[by:].reshape(x.shape)
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (1, 1, 3), (3, 5, 7), (16, 64, 64), (16, 64, 65), (17, 61, 63),
+                                   (33, 45, 47), (64, 64, 16)])
+@pytest.mark.parametrize("dt,mode,value,lower", [(np.float32, O.FBN, 32, float("nan")),
+                                                 (np.int16, O.FBW, 25.0, -200.0)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_discretise_sizes_and_alignment(B, shape, dt, mode, value, lower, off):
+    import torch
+    rng = np.random.default_rng(shape[2] + off)
+    vol = synth.ct_mixture(rng, shape) if dt == np.int16 else rng.gamma(2.0, 1.5, size=shape).astype(np.float32)
+    mask = (rng.random(shape) < 0.6).astype(np.uint8) * 3
+    mask.reshape(-1)[-1] = 1  # at least one, the last
+    levels = shifted(np.full(shape, 77, np.uint8), off)
+    lev, ng, xmin, xmax, n = B.fr_discretise(shifted(vol, off), shifted(mask, off), mode, value, lower,
+                                             levels=levels)
+    olev, ong, oxmin, oxmax = O.discretise(vol, mask, mode, value, lower)
+    torch.cuda.synchronize()
+    assert (ng, xmin, xmax, n) == (ong, oxmin, oxmax, int(np.count_nonzero(mask)))
+    assert np.array_equal(lev.cpu().numpy(), olev)
+
+
+@pytest.mark.parametrize("n_mask", [1, 4095, 4096, 4097, 20000])
+def test_direct_and_staged_output(B, n_mask):
+    import torch
+    rng = np.random.default_rng(n_mask)
+    shape = (26, 30, 34)
+    vol = rng.gamma(2.0, 1.5, size=shape).astype(np.float32)
+    mask = np.zeros(shape, np.uint8)
+    mask.reshape(-1)[rng.choice(mask.size, n_mask, replace=False)] = 1
+    case = synth.Case("route", vol, mask, (1.0, 1.0, 1.0), O.FBN, 12.0, float("nan"), 1, 63)
+    v, m = to_dev(case)
+    args = (v, m, case.spacing, case.mode, case.value, case.lower, 1, 63, n_mask)
+    out = B.fr_map(*args)
+    B.fr_map_check()
+    gpu = out.cpu().numpy()
+    ok, rows = parity_report(gpu, O.spatial_map(case), O.map_names(63))
+    assert ok, format_report(rows, only_bad=True)
+    na = torch.empty_like(out)
+    B.fr_map_noalloc(*args, na)
+    B.fr_map_check()
+    assert np.array_equal(na.cpu().numpy().view(np.uint32), gpu.view(np.uint32))
+
+
+def test_noalloc_with_and_without_room_for_the_stash(B):
+    import torch
+    # about 1,500 bytes a voxel with the stash: the second does not fit 64 MiB with it
+    for n in (40000, 60000):
+        shape = (40, 45, 50)
+        rng = np.random.default_rng(n)
+        vol = rng.gamma(2.0, 1.5, size=shape).astype(np.float32)
+        mask = np.zeros(shape, np.uint8)
+        mask.reshape(-1)[:n] = 1
+        v, m = to_dev(synth.Case("stash", vol, mask, (1.0, 1.0, 1.0), O.FBN, 24.0, float("nan"), 1, 2))
+        args = (v, m, (1.0, 1.0, 1.0), O.FBN, 24.0, float("nan"), 1, 2, n)
+        ref = B.fr_map(*args)
+        out = torch.empty_like(ref)
+        B.fr_map_noalloc(*args, out)
+        B.fr_map_check()
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), ref.cpu().numpy().view(np.uint32))
+
+
+def test_count_mismatch_is_reported_on_both_discretisations(B):
+    import torch
+    for shape in ((16, 32, 32), (32, 64, 64)):
+        vol = torch.rand(shape, device="cuda:0")
+        mask = torch.ones(shape, dtype=torch.uint8, device="cuda:0")
+        out = torch.full((18, 10), 5.0, device="cuda:0")
+        for f in (B.fr_map, B.fr_map_noalloc):
+            f(vol, mask, (1, 1, 1), O.FBN, 8, float("nan"), 1, 1, 10, out)
+            rc, _ = B.fr_map_status()
+            assert rc == B.FR_E_ARG
+            assert bool((out == 5.0).all())
+
+
+@pytest.mark.parametrize("radius", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("bins", [1, 2, 4, 9, 40])
+def test_order_statistics_by_level_subset(B, radius, bins):
+    """Continuous values, so that ranks inside a level matter; a heavy tail
+    puts most of V into a few levels."""
+    case = synth.random_case(900 + 7 * bins + radius, shape=(11, 12, 13), dtype=np.float32, radius=radius,
+                             mode=O.FBN, value=bins, families=1, mask_fill=0.9)
+    case.volume = (case.volume ** 2).astype(np.float32)
+    v, m = to_dev(case)
+    gpu = B.fr_map(v, m, case.spacing, case.mode, case.value, case.lower, radius, 1, case.n_mask)
+    B.fr_map_check()
+    ok, rows = parity_report(gpu.cpu().numpy(), O.spatial_map(case), O.map_names(1))
+    assert ok, format_report(rows, only_bad=True)
