@@ -2663,13 +2663,14 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
 
 // MOUT: the MCC problems with <= 32 levels go to the stash of a.mcc, so the
 // kernel needs no LDS slots for them; the 32-level instance then holds no
-// MCC code at all and needs far fewer registers (three waves per SIMD),
-// while the 64-level one still solves its wider problems itself.
-// Four waves per SIMD below radius 3 (128 VGPRs, no spills): latency of the
-// zone and run walks binds there; 100 k voxels, radius 2: 1.18 -> 1.08 ms.
-// Three at radius 3, where the tables in LDS allow no more.
+// MCC code at all and needs far fewer registers, while the 64-level one
+// still solves its wider problems itself.  Five waves per SIMD below radius
+// 3 (96 VGPRs, a few of them spilled): the latency of the zone and run
+// walks shows there; 100 k voxels at radius 2 take 0.90 ms, 0.95 with four
+// waves.  At radius 3 the tables in LDS allow fifteen waves per CU and the
+// instructions issue without gaps: a tighter bound only spills.
 template <typename T, int R, int LMAX, bool DEBUG, bool MOUT, int MODE = kPlain>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MOUT && LMAX == 32 && R <= 3 ? (R <= 2 ? 4 : 3) : 2))) void k_map(MapArgs arg) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MOUT && LMAX == 32 && R <= 3 ? (R <= 2 ? 5 : 3) : 2))) void k_map(MapArgs arg) {
   static_assert(!MOUT || (!DEBUG && MODE == kPlain), "stash only from production instances");
   __shared__ Smem<R, LMAX, MOUT> sm;
   __shared__ std::conditional_t<MODE == kAveraged, AvgMem, char> av;

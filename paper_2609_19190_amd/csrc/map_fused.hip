@@ -8,7 +8,9 @@ namespace {
 // persistent kernel.  The LDS holds one radius's layout at a time (a union
 // of the three); a workgroup switches layout when its next item's job has
 // another radius (items come grouped by radius, so rarely), after flushing
-// the MCC problems stashed in the old layout (64-level form).
+// the MCC problems stashed in the old layout (64-level form).  The 32-level
+// form asks for four waves per SIMD (128 VGPRs, none spilled): its LDS
+// allows fifteen waves per CU, three per SIMD left a fifth of them out.
 struct FusedNone {};
 template <int LMAX, bool MOUT>
 union FusedSmem {
@@ -18,7 +20,7 @@ union FusedSmem {
 };
 
 template <typename T, int LMAX>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LMAX == 32 ? 3 : 2))) void k_map_fused(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LMAX == 32 ? 4 : 2))) void k_map_fused(
     const BatchJob* __restrict__ jobs, const DiscParams* __restrict__ params,
     const int2* __restrict__ items, int32_t n_items_host, const int32_t* __restrict__ items_count,
     int2* over, int32_t* over_count, int32_t* queue, unsigned char* mcc, int64_t part_n,
