@@ -1144,9 +1144,9 @@ __device__ inline float xor_lane(float x, int lane) {
   } else if constexpr (M == 2) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(b, 0x4e, 0xf, 0xf, false));
   } else if constexpr (M == 4) {
-    const int r4 = __builtin_amdgcn_mov_dpp(b, 0x124, 0xf, 0xf, false);   // row_ror:4 (lane - 4)
-    const int r12 = __builtin_amdgcn_mov_dpp(b, 0x12c, 0xf, 0xf, false);  // row_ror:12 (lane + 4)
-    return __int_as_float((lane & 4) ? r4 : r12);
+    // row_ror:12 (lane + 4), then row_ror:4 (lane - 4) into banks 1 and 3
+    const int r12 = __builtin_amdgcn_mov_dpp(b, 0x12c, 0xf, 0xf, false);
+    return __int_as_float(__builtin_amdgcn_update_dpp(r12, b, 0x124, 0xf, 0xa, false));
   } else if constexpr (M == 8) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(b, 0x128, 0xf, 0xf, false));  // row_ror:8
   } else if constexpr (M == 16) {
@@ -1158,6 +1158,20 @@ __device__ inline float xor_lane(float x, int lane) {
     static_assert(M == 32, "xor_lane: M in 1..32");
     const auto r = __builtin_amdgcn_permlane32_swap(b, b, false, false);  // halves, likewise
     return __int_as_float((lane & 32) ? r[0] : r[1]);
+  }
+}
+// The smaller (lim = -inf) or larger (+inf) of x and its value in lane ^ M;
+// no NaN.  A swap of a register with itself leaves both in every lane.
+template <int M>
+__device__ inline float med_lane(float x, int lane, float lim) {
+  if constexpr (M == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
+    return __builtin_amdgcn_fmed3f(__int_as_float(r[0]), __int_as_float(r[1]), lim);
+  } else if constexpr (M == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
+    return __builtin_amdgcn_fmed3f(__int_as_float(r[0]), __int_as_float(r[1]), lim);
+  } else {
+    return __builtin_amdgcn_fmed3f(x, xor_lane<M>(x, lane), lim);
   }
 }
 
@@ -1182,8 +1196,12 @@ __device__ inline void sort_regs(const float (&in)[NIN], float* srt, int lane) {
         const float lim = keep_lo ? -INFINITY : INFINITY;
 #pragma unroll
         for (int r = 0; r < NPL; ++r) {
-          const float y = xor_lane<m>(v[r], lane);
-          v[r] = MED ? __builtin_amdgcn_fmed3f(v[r], y, lim) : keep_lo ? fminf(v[r], y) : fmaxf(v[r], y);
+          if constexpr (MED) {
+            v[r] = med_lane<m>(v[r], lane, lim);
+          } else {
+            const float y = xor_lane<m>(v[r], lane);
+            v[r] = keep_lo ? fminf(v[r], y) : fmaxf(v[r], y);
+          }
         }
       } else {
 #pragma unroll
@@ -1336,14 +1354,14 @@ __device__ inline uint32_t row_total(uint32_t n) {
 template <typename O>
 __device__ inline void emph16(const Emph& a, long long gln, long long rln, double units, double nlogn, O* f) {
   const double N = (double)a.n;
-  const double rN = 1.0 / N, rN2 = rN * rN;  // one division; the rest multiply
+  const double rN = frcp(N), rN2 = rN * rN;  // one reciprocal; the rest multiply
   f[0] = (O)(a.invj2 * rN);
   f[1] = (O)((double)a.sj2 * rN);
   f[2] = (O)((double)gln * rN);
   f[3] = (O)((double)gln * rN2);
   f[4] = (O)((double)rln * rN);
   f[5] = (O)((double)rln * rN2);
-  f[6] = (O)(N / units);
+  f[6] = (O)fdiv(N, units);
   f[7] = (O)((double)(a.n * a.si2 - a.si * a.si) * rN2);
   f[8] = (O)((double)(a.n * a.sj2 - a.sj * a.sj) * rN2);
   f[9] = (O)((nlogn - a.clogc) * rN);  // nlogn = N log2 N
@@ -1426,18 +1444,27 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
   // every load of the cube first (levels and raw values of the positions
   // inside the image, whatever their level), so that they are all in
   // flight together instead of one round trip per position
+  // The coordinates come from a table, and one comparison a byte (7 bits a
+  // coordinate, the top one for the sign) tests them against the part of the
+  // cube that lies inside the image.
   int gl[NIT];
   float xl[NIT];
+  {
+    constexpr uint32_t kTop = 0x808080u;
+    auto first = [](int at) FR_INLINE { return (uint32_t)max(0, R - at); };
+    auto last = [](int at, int n) FR_INLINE { return (uint32_t)min(S - 1, n - 1 - at + R); };
+    const uint32_t lo = first(cx) | first(cy) << 8 | first(cz) << 16;
+    const uint32_t hi = last(cx, nx) | last(cy, ny) << 8 | last(cz, nz) << 16 | kTop;
+    // an image holds less than 2^31 voxels: the index is exact modulo 2^32
+    const uint32_t unx = (uint32_t)nx, unxy = unx * (uint32_t)ny;
+    const uint32_t corner = (uint32_t)lin - (uint32_t)R * (unxy + unx + 1u);
 #pragma unroll
-  for (int q = 0; q < NIT; ++q) {
-    const int c = lane + 64 * q;
-    gl[q] = 0;
-    xl[q] = INFINITY;
-    if (c < C) {
-      const int x = c % S, y = (c / S) % S, z = c / (S * S);
-      const int gx = cx + x - R, gy = cy + y - R, gz = cz + z - R;
-      if (gx >= 0 && gx < nx && gy >= 0 && gy < ny && gz >= 0 && gz < nz) {
-        const int64_t gi = ((int64_t)gz * ny + gy) * nx + gx;
+    for (int q = 0; q < NIT; ++q) {
+      const uint32_t pos = kPos<R>.v[lane + 64 * q];
+      gl[q] = 0;
+      xl[q] = INFINITY;
+      if (((((pos | kTop) - lo) & (hi - (pos & 0xffffffu))) & kTop) == kTop) {
+        const uint32_t gi = corner + ((pos >> 16) & 0xffu) * unxy + ((pos >> 8) & 0xffu) * unx + (pos & 0xffu);
         gl[q] = a.levels[gi];
         xl[q] = raw_at<T>(a, gi);
       }
@@ -1449,10 +1476,10 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     const float xr = g ? xl[q] : INFINITY;
     if (g) lflag[g] = 1;
     xq[q] = xr;
-    if (fFO && g) {
-      const double xd = (double)xr;
+    if (fFO) {
+      const double xd = (double)(g ? xl[q] : 0.f);
       s1 += xd;
-      s2 += xd * xd;
+      s2 = fma(xd, xd, s2);
     }
     K += __popcll(__ballot(g != 0));
   }
@@ -1501,7 +1528,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
 #pragma unroll
   for (int q = 0; q < NIT; ++q) {
     const int c = lane + 64 * q;
-    lev[c + 1] = (uint16_t)(gl[q] ? gl[q] * 32 + 1 : 0);
+    lev[c + 1] = (uint16_t)(gl[q] * 32 + min(gl[q], 1));
   }
   __syncthreads();
 #pragma unroll
@@ -1517,11 +1544,11 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     gl[q] = l1;
     sm.cl[c] = (uint8_t)l1;
     if (c < C) {
-      const int x = c % S, y = (c / S) % S, z = c / (S * S);
-      const int row = (z + 1) * SM::SQ + (y + 1);
+      const uint32_t pos = kPos<R>.v[c];
+      const int x = (int)(pos & 0xffu), row = (int)(pos >> 24);
       const uint32_t left = lev[c], right = lev[c + 2];
       sm.clp()[row * SM::SX + (x + 1)] = (uint8_t)l1;
-      sm.cw()[row * S + x] = (uint16_t)((x > 0 ? left : 0u) + (g ? g * 32 + 1 : 0) + (x < S - 1 ? right : 0u));
+      sm.cw()[row * S + x] = (uint16_t)((x > 0 ? left : 0u) + (g * 32 + min(g, 1)) + (x < S - 1 ? right : 0u));
     }
   }
   __syncthreads();
@@ -1534,7 +1561,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
   // 1,000 VALU instructions a voxel at radius 3, this is about 300.)
   const double Kd = (double)K;
   if (fFO) {
-    const double rKd = 1.0 / Kd;  // one division; the rest multiply
+    const double rKd = frcp(Kd);  // one reciprocal; the rest multiply
     float* srt = reinterpret_cast<float*>(sm.u.a.parent);
     const double rank[5] = {(double)(K - 1) * 0.10, (double)(K - 1) * 0.25, (double)(K - 1) * 0.50,
                             (double)(K - 1) * 0.75, (double)(K - 1) * 0.90};
@@ -1620,8 +1647,8 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
         gl[q] = c < K;
       }
     }
-    const float mnf = part ? wfold_f(lo, [](float x, float y) { return fminf(x, y); }) : srt[0];
-    const float mxf = part ? wfold_f(hi, [](float x, float y) { return fmaxf(x, y); }) : srt[K - 1];
+    const float mnf = part ? wfold_f(lo, [](float x, float y) { return __builtin_amdgcn_fmed3f(x, y, -INFINITY); }) : srt[0];
+    const float mxf = part ? wfold_f(hi, [](float x, float y) { return __builtin_amdgcn_fmed3f(x, y, INFINITY); }) : srt[K - 1];
     double pct[5];
 #pragma unroll
     for (int k = 0; k < 5; ++k) {  // (the second statistic equals the first where there is none)
@@ -1669,7 +1696,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     rn = r2[5];
     double rmad = NAN;
     if (rn > 0.0) {
-      const double rrn = 1.0 / rn, rmu = rs * rrn;
+      const double rrn = frcp(rn), rmu = rs * rrn;
       double acc = 0.0;
 #pragma unroll
       for (int q = 0; q < NIT; ++q) {
@@ -1696,9 +1723,9 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       f[10] = (float)(mx - mn);
       f[11] = (float)mad;
       f[12] = (float)rmad;
-      f[13] = (float)sqrt(S2 * rKd);
-      f[14] = flat ? 0.f : (float)(m3 / (m2 * sqrt(m2)));  // m2^1.5
-      f[15] = flat ? 0.f : (float)(m4 / (m2 * m2) - 3.0);
+      f[13] = (float)(S2 > 0.0 && S2 < (double)INFINITY ? fsqrt(S2 * rKd) : S2);
+      f[14] = flat ? 0.f : (float)fdiv(m3, m2 * fsqrt(m2));  // m2^1.5
+      f[15] = flat ? 0.f : (float)(fdiv(m4, m2 * m2) - 3.0);
       f[16] = (float)m2;
       f[17] = (float)uni;
     }
@@ -1720,8 +1747,8 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     const int c = lane + 64 * q;
     const uint32_t l1 = (c < C) ? sm.cl[c] : 0u;
     if (l1) {
-      const int x = c % S, y = (c / S) % S, z = c / (S * S);
-      const int row0 = (z + 1) * SQ + (y + 1);
+      const uint32_t pos = kPos<R>.v[c];
+      const int x = (int)(pos & 0xffu), row0 = (int)(pos >> 24);
       const uint32_t* words = reinterpret_cast<const uint32_t*>(&sm.clp()[row0 * SM::SX + (x & ~3)]);
       const uint16_t* sums = &sm.cw()[row0 * S + x];
       uint32_t rw[9], wsum = 0;
@@ -1868,7 +1895,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     }
     emph_reduce(ed, gln, dn);
     const double N = (double)ed.n;
-    const double rN = 1.0 / N, rN2 = rN * rN;  // one division; the rest multiply
+    const double rN = frcp(N), rN2 = rN * rN;  // one reciprocal; the rest multiply
     if (lane == 0) {
       float* f = sm.early + kNFO;
       f[0] = (float)(ed.invj2 * rN);
@@ -1924,10 +1951,8 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       for (int e0 = 0; e0 < npair; e0 += 64) {
         const int e = e0 + lane;
         if (e < npair) {
-          int jc = (int)((1.0f + __builtin_amdgcn_sqrtf(8.0f * (float)e + 1.0f)) * 0.5f);
-          jc += (jc + 1) * jc / 2 <= e;  // exact: largest jc with jc (jc - 1) / 2 <= e
-          jc -= jc * (jc - 1) / 2 > e;
-          const int i = e - jc * (jc - 1) / 2;
+          const uint32_t rc = kTri.v[e];
+          const int i = (int)(rc & 0xffu), jc = (int)(rc >> 8) + 1;
           // counts <= (2r+1)^3 and levels <= 255: the products fit in 32 bits
           const int ni = (int)sm.u.a.ngn[i], nj = (int)sm.u.a.ngn[jc];
           if (ni && nj) {
@@ -1955,7 +1980,8 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       const long long Sn1 = ri[4], Sn2 = ri[5];
       const double ssum = rd[0];
       const double Nd = (double)Nvc;
-      const double psum = rd[1] / Nd;  // sum_i p_i s_i
+      const double rNd = frcp(Nd);      // one reciprocal; the rest multiply
+      const double psum = rd[1] * rNd;  // sum_i p_i s_i
       const bool any_s = __ballot(anys) != 0ull;
       bden = ri[6];
       cplx = rd[2];
@@ -1963,13 +1989,13 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
         float* f = sm.early + kNFO + kNGLDM;
         // sum_ij p_i p_j (i-j)^2 = 2 Var_p(i);  sum_ij (p_i+p_j)(i-j)^2 =
         // 2 sum_i p_i (Ngp i^2 - 2 i A1 + A2)
-        const double c1 = 2.0 * (double)(Nvc * Sn2 - Sn1 * Sn1) / (Nd * Nd);
-        const double strn = 2.0 * (double)(Ngp * Sn2 - 2 * A1 * Sn1 + A2 * Nvc) / Nd;
-        f[0] = any_s ? (float)(1.0 / psum) : 1e6f;
-        f[1] = Ngp <= 1 ? 0.f : (float)(c1 / (double)(Ngp * (Ngp - 1)) * (ssum / Nd));
-        f[2] = bden == 0 ? 0.f : (float)(psum / ((double)bden / Nd));
-        f[3] = (float)(cplx / Nd);
-        f[4] = any_s ? (float)(strn / ssum) : 0.f;
+        const double c1 = 2.0 * (double)(Nvc * Sn2 - Sn1 * Sn1) * (rNd * rNd);
+        const double strn = 2.0 * (double)(Ngp * Sn2 - 2 * A1 * Sn1 + A2 * Nvc) * rNd;
+        f[0] = any_s ? (float)frcp(psum) : 1e6f;
+        f[1] = Ngp <= 1 ? 0.f : (float)(fdiv(c1, (double)(Ngp * (Ngp - 1))) * (ssum * rNd));
+        f[2] = bden == 0 ? 0.f : (float)fdiv(rd[1], (double)bden);
+        f[3] = (float)(cplx * rNd);
+        f[4] = any_s ? (float)fdiv(strn, ssum) : 0.f;
       }
     }
   }
@@ -2419,6 +2445,45 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       const int nlev = __popcll(presb);
       const double Nd = (double)NP;
       const double nlogn = xlog2x<R>((uint32_t)NP);
+      // MCC: spectral radius of B = D^-1/2 P D^-1/2 - v v^T over present
+      // levels.  The place of a problem with up to 32 levels, which a flush
+      // (or the MCC kernel) computes four at a time
+      const bool defer = nlev > 1 && nlev <= 32;
+      uint16_t* gq = nullptr;
+      float** dq = nullptr;
+      int* nqp = nullptr;
+      if (defer) {
+        if constexpr (MOUT) {
+          // problems with <= 16 levels fill the voxel's partition of the
+          // stash from its start, wider ones from its end (one problem per
+          // voxel at most, so the two never meet)
+          const bool small = nlev <= 16;
+          const int p = (int)(it + a.key0) % kParts;
+          int slot = 0;
+          if (lane == 0) slot = atomicAdd(&a.mcc_count[p * kPartStride + (small ? kCntNarrow : kCntWide)], 1);
+          slot = __builtin_amdgcn_readfirstlane(slot);
+          if (small) {
+            McSmall* q = (McSmall*)(a.mcc + part_base(a.part_n, p) * kMccProblemBytes) + slot;
+            gq = q->g, dq = &q->dst, nqp = &q->n;
+          } else {
+            McProblem* q = (McProblem*)(a.mcc + part_base(a.part_n, p + 1) * kMccProblemBytes) - (slot + 1);
+            gq = q->g, dq = &q->dst, nqp = &q->n;
+          }
+        } else {
+          bool to_small = false;
+          if constexpr (kSmallSlots<R, LMAX> > 0) to_small = nlev <= 16;
+          if (to_small) {
+            if constexpr (kSmallSlots<R, LMAX> > 0) gq = sm.ms.s[ns].g, dq = &sm.ms.s[ns].dst, nqp = &sm.ms.s[ns].n;
+            ++ns;
+          } else {
+            gq = sm.mq.s[nq].g, dq = &sm.mq.s[nq].dst, nqp = &sm.mq.s[nq].n;
+            ++nq;
+          }
+        }
+      }
+      // every level has a pair (all but isolated ones do): the problem's
+      // entries are those of the pass below, in its order
+      const bool whole = defer && nlev == L;
       // entries of the upper triangle (r <= c), one per lane, enumerated
       // compactly (e = c (c + 1) / 2 + r); an entry off the diagonal stands
       // for the two symmetric ones (weight 2)
@@ -2429,11 +2494,10 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       for (int e0 = 0; e0 < ntri; e0 += 64) {
         const int e = e0 + lane;
         if (e < ntri) {
-          int c = (int)((__builtin_amdgcn_sqrtf(8.0f * (float)e + 1.0f) - 1.0f) * 0.5f);
-          c += (c + 1) * (c + 2) / 2 <= e;  // exact floor of the root
-          c -= c * (c + 1) / 2 > e;
-          const int r = e - c * (c + 1) / 2;
+          const uint32_t rc = kTri.v[e];
+          const int r = (int)(rc & 0xffu), c = (int)(rc >> 8);
           const uint32_t P = gsym<SM>(sm.u.a.glcm, r, c);
+          if (whole) gq[e] = (uint16_t)P;
           if (P) {
             const uint32_t w = r == c ? 1u : 2u;
             e2 += __umul24(w * P, P);
@@ -2448,12 +2512,13 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       pmax = wmaxu(pmax);
       __syncthreads();
       const int ng = a.ng;
-      const double mu = (double)S1x / Nd;
+      const double rNd = frcp(Nd), rN2 = rNd * rNd;  // one reciprocal; the rest multiply
+      const double mu = (double)S1x * rNd;
       uint32_t sd1 = 0, sd2 = 0, ss1 = 0;
       std::conditional_t<(R > 3), double, uint32_t> ss2 = 0;
       double dlog = 0, slog = 0, iv = 0, idm = 0, idmn = 0, id = 0, idn = 0, ct = 0, cs = 0, cp = 0;
       const double ngd = (double)ng;
-      const double rng = 1.0 / ngd, rng2 = rng * rng;
+      const double rng = frcp(ngd), rng2 = rng * rng;
       for (int k = lane; k < ng; k += 64) {
         const uint32_t c = sm.u.c.pd[k];
         if (c) {
@@ -2507,73 +2572,43 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       cs = h2[0];
       cp = h2[1];
       const long long sij = (Ss2 - Sd2) / 4;  // sum_ij i j P
-      const double rNd = 1.0 / Nd, rN2 = rNd * rNd;  // one division; the rest multiply
       const double HX = (nlogn - h2[3]) * rNd, HXY = (nlogn - h2[4]) * rNd;
 
-      // MCC: spectral radius of B = D^-1/2 P D^-1/2 - v v^T over present levels
       double mcc = 1.0;
-      bool deferred = false;
       if (nlev > 1) {
-        const int n = nlev;
-        if (lane < L && rowc > 0) {
-          const int pos = __popcll(presb & ((lane == 0) ? 0ull : (~0ull >> (64 - lane))));
-          sm.u.b.pl[pos] = lane;
+        mcc = NAN;
+        if (!whole) {
+          if (lane < L && rowc > 0) {
+            const int pos = __popcll(presb & ((lane == 0) ? 0ull : (~0ull >> (64 - lane))));
+            sm.u.b.pl[pos] = lane;
+          }
+          __syncthreads();
         }
-        __syncthreads();
-        if (n <= 32) {  // stash the problem; a flush (or the MCC kernel) computes four at once
-          // upper triangle, column c of the lower half-wave and column
-          // n - 1 - c of the upper one per pass
-          auto stash = [&](uint16_t* gq, float** dq, int* nqp) FR_INLINE {
-            const int l = lane & 31;
+        if (defer) {
+          if (!whole) {
+            // upper triangle, column c of the lower half-wave and column
+            // n - 1 - c of the upper one per pass
+            const int l = lane & 31, n = nlev;
             const int plr = l < n ? sm.u.b.pl[l] : 0;
             for (int c0 = 0; 2 * c0 < n; ++c0) {
               const int c = lane < 32 ? c0 : n - 1 - c0;
               if (l <= c && (lane < 32 || c > c0))
                 gq[c * (c + 1) / 2 + l] = (uint16_t)gsym<SM>(sm.u.a.glcm, plr, sm.u.b.pl[c]);
             }
-            if (lane == 0) {
-              *nqp = n;
-              if constexpr (MODE == kAveraged)
-                *dq = (float*)&av->mcc[pass];
-              else
-                *dq = a.stage ? a.stage + it * kStageStride + (oGLCM + 15)
-                            : a.out + (int64_t)(oGLCM + 15) * a.n_out + it;
-            }
-          };
-          if constexpr (MOUT) {
-            // problems with <= 16 levels fill the voxel's partition of the
-            // stash from its start, wider ones from its end (one problem per
-            // voxel at most, so the two never meet)
-            const bool small = n <= 16;
-            const int p = (int)(it + a.key0) % kParts;
-            int slot = 0;
-            if (lane == 0) slot = atomicAdd(&a.mcc_count[p * kPartStride + (small ? kCntNarrow : kCntWide)], 1);
-            slot = __builtin_amdgcn_readfirstlane(slot);
-            if (small) {
-              McSmall* q = (McSmall*)(a.mcc + part_base(a.part_n, p) * kMccProblemBytes) + slot;
-              stash(q->g, &q->dst, &q->n);
-            } else {
-              McProblem* q = (McProblem*)(a.mcc + part_base(a.part_n, p + 1) * kMccProblemBytes) - (slot + 1);
-              stash(q->g, &q->dst, &q->n);
-            }
-          } else {
-            bool to_small = false;
-            if constexpr (kSmallSlots<R, LMAX> > 0) to_small = n <= 16;
-            if (to_small) {
-              if constexpr (kSmallSlots<R, LMAX> > 0) stash(sm.ms.s[ns].g, &sm.ms.s[ns].dst, &sm.ms.s[ns].n);
-              ++ns;
-            } else {
-              stash(sm.mq.s[nq].g, &sm.mq.s[nq].dst, &sm.mq.s[nq].n);
-              ++nq;
-            }
           }
-          deferred = true;
-          mcc = NAN;
+          if (lane == 0) {
+            *nqp = nlev;
+            if constexpr (MODE == kAveraged)
+              *dq = (float*)&av->mcc[pass];
+            else
+              *dq = a.stage ? a.stage + it * kStageStride + (oGLCM + 15)
+                            : a.out + (int64_t)(oGLCM + 15) * a.n_out + it;
+          }
         }
         if constexpr (LMAX > 32) {
-          if (!deferred) {  // > 32 levels: computed at the flush after this voxel
+          if (!defer) {  // > 32 levels: computed at the flush after this voxel
             if (lane == 0) {
-              sm.u.b.big_n = n;
+              sm.u.b.big_n = nlev;
               if constexpr (MODE == kAveraged)
                 sm.u.b.big_dst = (float*)&av->mcc[pass];
               else
@@ -2581,7 +2616,6 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
                                        : a.out + (int64_t)(oGLCM + 15) * a.n_out + it;
             }
             big = true;
-            mcc = NAN;
           }
         }
       }
@@ -2601,15 +2635,15 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
         put(4, ct * rNd);
         put(5, (double)Sd2 * rNd);
         put(6, nlev <= 1 ? 1.0
-                         : ((double)(NP * sij - S1x * S1x) / (double)(NP * S2x - S1x * S1x)));
+                         : fdiv((double)(NP * sij - S1x * S1x), (double)(NP * S2x - S1x * S1x)));
         put(7, (double)Sd1 * rNd);
         put(8, (nlogn - dlog) * rNd);
         put(9, (double)(NP * Sd2 - Sd1 * Sd1) * rN2);
         put(10, (double)E2 * rN2);
         put(11, HXY);
-        put(12, nlev <= 1 ? 0.0 : ((HXY - 2.0 * HX) / HX));
+        put(12, nlev <= 1 ? 0.0 : fdiv(HXY - 2.0 * HX, HX));
         const double t = 1.0 - exp(-2.0 * (2.0 * HX - HXY));
-        put(13, sqrt(t > 0.0 ? t : 0.0));
+        put(13, t > 0.0 ? fsqrt(t) : 0.0);
         put(14, idm * rNd);
         if constexpr (MODE == kAveraged) {
           if (nlev <= 1) av->mcc[pass] = 1.0;
@@ -2667,10 +2701,10 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
 // still solves its wider problems itself.  Five waves per SIMD below radius
 // 3 (96 VGPRs, a few of them spilled): the latency of the zone and run
 // walks shows there; 100 k voxels at radius 2 take 0.90 ms, 0.95 with four
-// waves.  At radius 3 the tables in LDS allow fifteen waves per CU and the
-// instructions issue without gaps: a tighter bound only spills.
+// waves.  Four at radius 3 (128 VGPRs, none spilled), where the tables in
+// LDS allow fifteen waves per CU: 1 M voxels take 11.4 ms, 12.2 with three.
 template <typename T, int R, int LMAX, bool DEBUG, bool MOUT, int MODE = kPlain>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MOUT && LMAX == 32 && R <= 3 ? (R <= 2 ? 5 : 3) : 2))) void k_map(MapArgs arg) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MOUT && LMAX == 32 && R <= 3 ? (R <= 2 ? 5 : 4) : 2))) void k_map(MapArgs arg) {
   static_assert(!MOUT || (!DEBUG && MODE == kPlain), "stash only from production instances");
   __shared__ Smem<R, LMAX, MOUT> sm;
   __shared__ std::conditional_t<MODE == kAveraged, AvgMem, char> av;
