@@ -273,7 +273,7 @@ fr_status enqueue_discretise_into(const void* volume, int32_t dtype, int32_t nx,
 
 fr_status enqueue_discretise(const void* volume, int32_t dtype, int32_t nx, int32_t ny, int32_t nz,
                              const uint8_t* mask, int32_t mode, double value, double lower,
-                             uint8_t* levels, Pool* p, int64_t expect_count, hipStream_t st) {
+                             uint8_t* levels, int32_t* list, Pool* p, int64_t expect_count, hipStream_t st) {
   const int64_t n = (int64_t)nx * ny * nz;
   fr::DiscScratch s;
   s.nblocks = (n + fr::kDiscSeg - 1) / fr::kDiscSeg;
@@ -284,7 +284,7 @@ fr_status enqueue_discretise(const void* volume, int32_t dtype, int32_t nx, int3
   s.params = p->params;
   s.counts = p->counts;
   return enqueue_discretise_into(volume, dtype, nx, ny, nz, mask, mode, value, lower, levels,
-                                 p->list, s, expect_count, st);
+                                 list, s, expect_count, st);
 }
 
 // The status a device parameter block reports (message in fr_last_error).
@@ -309,11 +309,12 @@ fr_status read_params(Pool* p, hipStream_t st, fr::DiscParams* out) {
   return FR_OK;
 }
 
-// Discretise and wait for the parameters (fr_discretise, fr_map_matrices).
+// Discretise and wait for the parameters (fr_discretise, which needs no list
+// of the mask voxels, and fr_map_matrices).
 fr_status run_discretise(const void* volume, int32_t dtype, int32_t nx, int32_t ny, int32_t nz,
                          const uint8_t* mask, int32_t mode, double value, double lower,
-                         uint8_t* levels, Pool* p, hipStream_t st, fr::DiscParams* out) {
-  fr_status e = enqueue_discretise(volume, dtype, nx, ny, nz, mask, mode, value, lower, levels, p, -1, st);
+                         uint8_t* levels, int32_t* list, Pool* p, hipStream_t st, fr::DiscParams* out) {
+  fr_status e = enqueue_discretise(volume, dtype, nx, ny, nz, mask, mode, value, lower, levels, list, p, -1, st);
   if (e != FR_OK) return e;
   if ((e = read_params(p, st, out)) != FR_OK) return e;
   if (out->count == 0) return fail(FR_E_EMPTY_MASK, "the mask holds no voxel");
@@ -479,7 +480,7 @@ fr_status map_common(const void* volume, int32_t dtype, int32_t nx, int32_t ny, 
     // the dense tables are sized by the caller's Ng: check it before mapping
     fr::DiscParams dp;
     if ((st = run_discretise(volume, dtype, nx, ny, nz, mask, disc_mode, disc_value, disc_lower,
-                             p->levels, p, stream, &dp)) != FR_OK)
+                             p->levels, p->list, p, stream, &dp)) != FR_OK)
       return st;
     if (dp.count != n_mask)
       return fail(FR_E_ARG, "n_mask %lld does not match the %lld mask voxels", (long long)n_mask,
@@ -498,7 +499,7 @@ fr_status map_common(const void* volume, int32_t dtype, int32_t nx, int32_t ny, 
     // no host synchronisation: the mask count and Ng are checked on the
     // device, and every later kernel stops on an error (fr_map_status)
     if ((st = enqueue_discretise(volume, dtype, nx, ny, nz, mask, disc_mode, disc_value, disc_lower,
-                                 p->levels, p, n_mask, stream)) != FR_OK)
+                                 p->levels, p->list, p, n_mask, stream)) != FR_OK)
       return st;
   }
 
@@ -645,7 +646,7 @@ fr_status fr_discretise(const void* volume, int32_t dtype, int32_t nx, int32_t n
   Pool* p = nullptr;
   if ((st = pool_get((int64_t)nx * ny * nz, &p)) != FR_OK) return st;
   fr::DiscParams dp;
-  st = run_discretise(volume, dtype, nx, ny, nz, mask, disc_mode, disc_value, disc_lower, levels, p,
+  st = run_discretise(volume, dtype, nx, ny, nz, mask, disc_mode, disc_value, disc_lower, levels, nullptr, p,
                       (hipStream_t)hip_stream, &dp);
   if (st != FR_OK) return st;
   if (ng) *ng = dp.ng;

@@ -9,6 +9,7 @@
 //   k_disc_levels  level of every voxel (0 outside the mask) and the
 //                  raster-ordered list of mask voxels (compact index ->
 //                  linear index), each segment writing at its scanned offset
+//                  (no list where the levels alone are asked for)
 // (one launch, k_disc_small, up to 65,536 voxels).  A segment's loads are
 // lane-interleaved groups of four voxels, all in flight before the first is
 // used.
@@ -192,7 +193,10 @@ __device__ inline void zero_counts(int32_t* counts, int threads) {
 
 // Exclusive scan of the counts of segments [s0, s0 + nb), the VOI min/max
 // and the gray-level count, written to *P (one block of kScanThreads).
-// expect_count >= 0 adds the check of the mask-voxel count.
+// expect_count >= 0 adds the check of the mask-voxel count.  A thread takes
+// a run of consecutive segments, so that their loads are in flight together
+// and the block scans once: one load after another sets the time, not their
+// number (2,048 segments: 6.0 -> 4.3 us).
 __device__ inline void disc_scan_range(int64_t s0, int64_t nb, const int32_t* bcount_all,
                                        const double* bmin_all, const double* bmax_all,
                                        int64_t* boff_all, DiscParams* P, int mode, double value,
@@ -203,39 +207,35 @@ __device__ inline void disc_scan_range(int64_t s0, int64_t nb, const int32_t* bc
   int64_t* boff = boff_all + s0;
   __shared__ long long wsum[kScanThreads / 64];
   __shared__ double wmn[kScanThreads / 64], wmx[kScanThreads / 64];
-  __shared__ long long chunk_total;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  long long carry = 0;
+  const int64_t per = (nb + kScanThreads - 1) / kScanThreads;
+  const int64_t i0 = min(nb, per * (int64_t)threadIdx.x), i1 = min(nb, i0 + per);
+  long long v = 0;
   double mn = INFINITY, mx = -INFINITY;
-  for (int64_t c0 = 0; c0 < nb; c0 += kScanThreads) {
-    const int64_t i = c0 + threadIdx.x;
-    long long v = 0;
-    if (i < nb) {
-      v = bcount[i];
-      mn = fmin(mn, bmin[i]);
-      mx = fmax(mx, bmax[i]);
-    }
-    long long x = v;  // inclusive scan inside the wavefront
+#pragma unroll 8
+  for (int64_t i = i0; i < i1; ++i) {
+    v += bcount[i];
+    mn = fmin(mn, bmin[i]);
+    mx = fmax(mx, bmax[i]);
+  }
+  long long x = v;  // inclusive scan inside the wavefront
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const long long y = __shfl_up(x, o);
-      if (lane >= o) x += y;
-    }
-    if (lane == 63) wsum[w] = x;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      long long run = 0;
-      for (int q = 0; q < kScanThreads / 64; ++q) {
-        const long long t = wsum[q];
-        wsum[q] = run;
-        run += t;
-      }
-      chunk_total = run;
-    }
-    __syncthreads();
-    if (i < nb) boff[i] = carry + wsum[w] + x - v;
-    carry += chunk_total;
-    __syncthreads();
+  for (int o = 1; o < 64; o <<= 1) {
+    const long long y = __shfl_up(x, o);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) wsum[w] = x;
+  __syncthreads();
+  long long carry = 0, run = x - v;
+#pragma unroll
+  for (int q = 0; q < kScanThreads / 64; ++q) {
+    run += q < w ? wsum[q] : 0;
+    carry += wsum[q];
+  }
+#pragma unroll 8
+  for (int64_t i = i0; i < i1; ++i) {
+    boff[i] = run;
+    run += bcount[i];
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
@@ -267,9 +267,9 @@ __global__ __launch_bounds__(kScanThreads) void k_disc_scan(int64_t nb, const in
   disc_scan_range(0, nb, bcount, bmin, bmax, boff, P, mode, value, lower, expect_count);
 }
 
-// Levels of one segment (0 outside the mask) and its mask voxels appended
-// to `list` at the segment's scanned offset.
-template <typename T>
+// Levels of one segment (0 outside the mask) and, where a list is asked for,
+// its mask voxels appended to `list` at the segment's scanned offset.
+template <bool LIST, typename T>
 __device__ inline void disc_levels_seg(const T* __restrict__ vol, const uint8_t* __restrict__ mask,
                                        int64_t n, int64_t seg, int64_t off,
                                        const DiscParams* P, int mode, double value,
@@ -287,28 +287,33 @@ __device__ inline void disc_levels_seg(const T* __restrict__ vol, const uint8_t*
 #pragma unroll
   for (int j = 0; j < kDiscGroups; ++j)
     in[j] = load4(vol, mask, base + (int64_t)(j * kDiscThreads + threadIdx.x) * kGroup, n, vec, x[j]);
+  if constexpr (LIST) {
 #pragma unroll
-  for (int j = 0; j < kDiscGroups; ++j) {
-    before[j] = group_prefix(in[j]);
-    if (lane == 63) wcnt[j][w] = before[j] + __popc(in[j]);
+    for (int j = 0; j < kDiscGroups; ++j) {
+      before[j] = group_prefix(in[j]);
+      if (lane == 63) wcnt[j][w] = before[j] + __popc(in[j]);
+    }
+    __syncthreads();
   }
-  __syncthreads();
   int64_t pos = off;
   // a call whose mask count disagrees with n_mask stops here: its list may
   // have no room for every mask voxel
-  const bool listed = P->err != kJobCount;
+  const bool listed = LIST && P->err != kJobCount;
 #pragma unroll
   for (int j = 0; j < kDiscGroups; ++j) {
     const int64_t i = base + (int64_t)(j * kDiscThreads + threadIdx.x) * kGroup;
-    int head = 0, total = 0;
+    [[maybe_unused]] int64_t at = 0;
+    if constexpr (LIST) {
+      int head = 0, total = 0;
 #pragma unroll
-    for (int q = 0; q < kDiscThreads / 64; ++q) {
-      const int c = wcnt[j][q];
-      head += (q < w) ? c : 0;
-      total += c;
+      for (int q = 0; q < kDiscThreads / 64; ++q) {
+        const int c = wcnt[j][q];
+        head += (q < w) ? c : 0;
+        total += c;
+      }
+      at = pos + head + before[j];
+      pos += total;
     }
-    int64_t at = pos + head + before[j];
-    pos += total;
     int g[kGroup];
 #pragma unroll
     for (int e = 0; e < kGroup; ++e) {
@@ -417,21 +422,21 @@ __global__ __launch_bounds__(kSmallThreads) void k_disc_small(const T* __restric
       g[e] = 0;
       if ((in[j] >> e) & 1u) {
         g[e] = level_of((double)x[j][e], mode, value, p.xmin, p.lo, range, p.ng);
-        if (p.err != kJobCount) list[at++] = (int32_t)(i + e);
+        if (list && p.err != kJobCount) list[at++] = (int32_t)(i + e);
       }
     }
     store4(levels, i, n, vec, g);
   }
 }
 
-template <typename T>
+template <typename T, bool LIST>
 __global__ __launch_bounds__(kDiscThreads) void k_disc_levels(const T* __restrict__ vol,
                                                               const uint8_t* __restrict__ mask,
                                                               int64_t n, const int64_t* boff,
                                                               const DiscParams* P, int mode,
                                                               double value, uint8_t* levels,
                                                               int32_t* list) {
-  disc_levels_seg(vol, mask, n, blockIdx.x, boff[blockIdx.x], P, mode, value, levels, list);
+  disc_levels_seg<LIST>(vol, mask, n, blockIdx.x, LIST ? boff[blockIdx.x] : 0, P, mode, value, levels, list);
 }
 
 // ---- batched: global segment b belongs to job seg_job[b] ------------------
@@ -468,10 +473,10 @@ __global__ __launch_bounds__(kDiscThreads) void k_bdisc_levels(const BatchJob* _
   // a job whose mask count disagrees with n_mask must not write past its list
   if (params[j].err == kJobCount || params[j].err == kJobEmpty) return;
   if (J.dtype == 1)
-    disc_levels_seg((const int16_t*)J.vol, J.mask, J.nvox, seg, boff[blockIdx.x], &params[j], J.mode,
+    disc_levels_seg<true>((const int16_t*)J.vol, J.mask, J.nvox, seg, boff[blockIdx.x], &params[j], J.mode,
                     J.value, J.levels, J.list);
   else
-    disc_levels_seg((const float*)J.vol, J.mask, J.nvox, seg, boff[blockIdx.x], &params[j], J.mode,
+    disc_levels_seg<true>((const float*)J.vol, J.mask, J.nvox, seg, boff[blockIdx.x], &params[j], J.mode,
                     J.value, J.levels, J.list);
 }
 
@@ -524,12 +529,23 @@ hipError_t launch_discretise(const void* vol, int dtype, int64_t nvox, const uin
                      value, lower, expect_count, s.counts);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
+  // without a list (the levels alone were asked for) nothing has to be
+  // counted or ordered: 24 -> 15.5 us for 8.4 M voxels, half in the mask
+  auto levels_of = [&](auto kernel, auto* v) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, st, v, mask, nvox, s.block_offset, s.params, mode, value, levels, list);
+  };
   if (dtype == 1) {
-    hipLaunchKernelGGL(k_disc_levels<int16_t>, grid, block, 0, st, (const int16_t*)vol, mask,
-                       nvox, s.block_offset, s.params, mode, value, levels, list);
+    const int16_t* v = (const int16_t*)vol;
+    if (list)
+      levels_of(k_disc_levels<int16_t, true>, v);
+    else
+      levels_of(k_disc_levels<int16_t, false>, v);
   } else {
-    hipLaunchKernelGGL(k_disc_levels<float>, grid, block, 0, st, (const float*)vol, mask, nvox,
-                       s.block_offset, s.params, mode, value, levels, list);
+    const float* v = (const float*)vol;
+    if (list)
+      levels_of(k_disc_levels<float, true>, v);
+    else
+      levels_of(k_disc_levels<float, false>, v);
   }
   return hipGetLastError();
 }

@@ -119,3 +119,22 @@ def test_order_statistics_by_level_subset(B, radius, bins):
     B.fr_map_check()
     ok, rows = parity_report(gpu.cpu().numpy(), O.spatial_map(case), O.map_names(1))
     assert ok, format_report(rows, only_bad=True)
+
+
+@pytest.mark.parametrize("shape", [(2, 512, 1024), (2, 512, 1028), (3, 512, 1024)])  # 256, 257, 384 segments
+def test_list_order_over_the_segment_scan(B, shape):
+    """One segment a thread of the scan, and a second or half a one: every
+    mask voxel at its place of the list, isolated voxels among them."""
+    rng = np.random.default_rng(shape[2] + shape[0])
+    vol = rng.gamma(2.0, 1.5, size=shape).astype(np.float32)
+    mask = np.zeros(shape, np.uint8)
+    flat = mask.reshape(-1)
+    flat[rng.choice(flat.size, 300, replace=False)] = 1
+    flat[[0, -1]] = 1
+    mask[1, 100:104, 200:206] = 1
+    case = synth.Case("segments", vol, mask, (1.0, 1.0, 1.0), O.FBN, 20.0, float("nan"), 1, 63)
+    v, m = to_dev(case)
+    out = B.fr_map(v, m, case.spacing, case.mode, case.value, case.lower, 1, 63, case.n_mask)
+    B.fr_map_check()
+    ok, rows = parity_report(out.cpu().numpy(), O.spatial_map(case), O.map_names(63))
+    assert ok, format_report(rows, only_bad=True)
