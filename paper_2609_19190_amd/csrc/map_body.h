@@ -2695,16 +2695,21 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
   __syncthreads();
 }
 
-// MOUT: the MCC problems with <= 32 levels go to the stash of a.mcc, so the
-// kernel needs no LDS slots for them; the 32-level instance then holds no
-// MCC code at all and needs far fewer registers, while the 64-level one
-// still solves its wider problems itself.  Five waves per SIMD below radius
-// 3 (96 VGPRs, a few of them spilled): the latency of the zone and run
-// walks shows there; 100 k voxels at radius 2 take 0.90 ms, 0.95 with four
-// waves.  Four at radius 3 (128 VGPRs, none spilled), where the tables in
-// LDS allow fifteen waves per CU: 1 M voxels take 11.4 ms, 12.2 with three.
+// Waves per SIMD that an instance's registers are held to.  The production
+// instances (MOUT: the MCC problems with <= 32 levels go to the stash of
+// a.mcc, so there are no LDS slots for them) with at most 32 levels hold no
+// MCC code.  Five below radius 3 (96 VGPRs, a few of them spilled): the
+// latency of the zone and run walks shows there; 100 k voxels at radius 2
+// take 0.90 ms, 0.95 with four waves.  Four at radius 3 (128 VGPRs, none
+// spilled), where the tables in LDS allow fifteen waves per CU: 1 M voxels
+// take 11.4 ms, 12.2 with three.  Two for the 64-level ones, which solve
+// wider problems themselves, a column of 64 doubles a lane (three spill
+// thirty registers: 60 k voxels of 33 levels and more, 3.2 -> 4.8 ms), and
+// for all others.
+template <int R, int LMAX, bool MOUT>
+constexpr int kMapWaves = !MOUT || LMAX > 32 || R > 3 ? 2 : R == 3 ? 4 : 5;
 template <typename T, int R, int LMAX, bool DEBUG, bool MOUT, int MODE = kPlain>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MOUT && LMAX == 32 && R <= 3 ? (R <= 2 ? 5 : 4) : 2))) void k_map(MapArgs arg) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kMapWaves<R, LMAX, MOUT>))) void k_map(MapArgs arg) {
   static_assert(!MOUT || (!DEBUG && MODE == kPlain), "stash only from production instances");
   __shared__ Smem<R, LMAX, MOUT> sm;
   __shared__ std::conditional_t<MODE == kAveraged, AvgMem, char> av;
@@ -2857,7 +2862,7 @@ __device__ inline int64_t take_item(int32_t* queue, const int32_t* counts, int64
 }
 
 template <typename T, int R, int LMAX, bool MOUT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MOUT && R <= 3 ? 3 : 2))) void k_map_batch(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kMapWaves<R, LMAX, MOUT>))) void k_map_batch(
     const BatchJob* __restrict__ jobs, const DiscParams* __restrict__ params,
     const int2* __restrict__ items, int32_t n_items_host, const int32_t* __restrict__ items_count,
     int32_t vpw, int2* over, int32_t* over_count, int32_t* queue, unsigned char* mcc,
