@@ -7,27 +7,29 @@
 // 16 GLRLM, 16 GLSZM, 14 GLDM, 5 NGTDM maps; feature equations per IBSI as
 // the paper defers to it, with the readings stated in fr.h).
 //
-// How: one wavefront (= one workgroup) owns a contiguous run of compact
-// mask indices and handles its voxels one after another, all 64 lanes on
-// one voxel:
-//   gather   lane per cube position: levels + raw values into LDS
+// How: one wavefront (= one workgroup) handles the voxels of its part of the
+// list one after another, all 64 lanes on one voxel:
+//   gather   lane per cube position: levels and raw values, all loads in
+//            flight together
 //   levels   local compaction of the levels present (L <= LMAX), so every
 //            table is L-sized instead of Ng-sized
-//   count    lane per cube position, one pass over the 26 neighbours:
-//            equal-level neighbour bitmask, GLCM counts (13 forward
-//            offsets, LDS atomics; equal pairs folded into one diagonal add),
-//            GLCM row sums, GLDM dependence, NGTDM exact integer sums,
-//            zone labels by minimum-label propagation over equal-level bits
-//   runs     GLRLM: a run starts where the backward neighbour bit is clear;
-//            walk the forward bits
-//   features FP64, wave-shuffle reductions; integer numerators kept exact
-//            where a feature is a ratio of integer sums; GLCM features via
-//            the sum/difference histograms; MCC as the spectral radius of
+//   first order  order statistics by sorting the values of their own levels
+//   count    lane per cube position, the 26 neighbours as nine rows of three
+//            bytes: equal-level neighbour bitmask, GLCM counts (13 forward
+//            offsets, LDS atomics), GLCM row sums, GLDM dependence, NGTDM
+//            exact integer sums (from row sums of the levels)
+//   zones    union of the equal-level neighbours that no other one implies
+//   runs     a run starts where the backward neighbour bit is clear; runs of
+//            one voxel are counted from the masks, the others walked
+//   features FP64, DPP reductions; integer numerators kept exact where a
+//            feature is a ratio of integer sums; GLCM features via the
+//            sum/difference histograms; MCC as the spectral radius of
 //            D^-1/2 P D^-1/2 - v v^T (v = sqrt(px)), by Householder
-//            tridiagonalisation and Sturm-count multisection (64 probes per
-//            round across the lanes)
-// Nothing here is a dense contraction, so no MFMA; the bound is LDS and
-// VALU (FP64) work per voxel.
+//            tridiagonalisation and Sturm-count multisection
+// The modes kMerged and kAveraged (distance, tolerance, averaged matrices)
+// take the same body with their own counting.  Nothing here is a dense
+// contraction, so no MFMA; the bound is VALU issue, and the latency and
+// bandwidth of LDS where fewer than four waves share a SIMD.
 #include <math.h>
 #include <stddef.h>
 

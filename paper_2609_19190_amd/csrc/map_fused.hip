@@ -9,8 +9,9 @@ namespace {
 // of the three); a workgroup switches layout when its next item's job has
 // another radius (items come grouped by radius, so rarely), after flushing
 // the MCC problems stashed in the old layout (64-level form).  The 32-level
-// form asks for four waves per SIMD (128 VGPRs, none spilled): its LDS
-// allows fifteen waves per CU, three per SIMD left a fifth of them out.
+// form asks for four waves per SIMD (128 VGPRs, some fifteen spilled): its
+// LDS allows fifteen waves per CU, three per SIMD left a fifth of them out
+// (a batch of 16 scans: 2.48 -> 2.37 ms).
 struct FusedNone {};
 template <int LMAX, bool MOUT>
 union FusedSmem {
