@@ -296,9 +296,10 @@ __device__ inline void disc_levels_seg(const T* __restrict__ vol, const uint8_t*
     __syncthreads();
   }
   int64_t pos = off;
-  // a call whose mask count disagrees with n_mask stops here: its list may
-  // have no room for every mask voxel
-  const bool listed = LIST && P->err != kJobCount;
+  // a call with an error stops here: no kernel reads its list, which may have
+  // no room for every mask voxel (a count unlike n_mask is reported only where
+  // nothing else is wrong)
+  const bool listed = LIST && P->err == kJobOk;
 #pragma unroll
   for (int j = 0; j < kDiscGroups; ++j) {
     const int64_t i = base + (int64_t)(j * kDiscThreads + threadIdx.x) * kGroup;
@@ -422,7 +423,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_disc_small(const T* __restric
       g[e] = 0;
       if ((in[j] >> e) & 1u) {
         g[e] = level_of((double)x[j][e], mode, value, p.xmin, p.lo, range, p.ng);
-        if (list && p.err != kJobCount) list[at++] = (int32_t)(i + e);
+        if (list && p.err == kJobOk) list[at++] = (int32_t)(i + e);
       }
     }
     store4(levels, i, n, vec, g);
@@ -470,8 +471,9 @@ __global__ __launch_bounds__(kDiscThreads) void k_bdisc_levels(const BatchJob* _
   const int j = seg_job ? seg_job[blockIdx.x] : 0;
   const BatchJob& J = jobs[j];
   const int64_t seg = (int64_t)blockIdx.x - J.seg_base;
-  // a job whose mask count disagrees with n_mask must not write past its list
-  if (params[j].err == kJobCount || params[j].err == kJobEmpty) return;
+  // a job with an error must not write past its list (its count may be unlike
+  // n_mask, whatever error is reported)
+  if (params[j].err != kJobOk) return;
   if (J.dtype == 1)
     disc_levels_seg<true>((const int16_t*)J.vol, J.mask, J.nvox, seg, boff[blockIdx.x], &params[j], J.mode,
                     J.value, J.levels, J.list);

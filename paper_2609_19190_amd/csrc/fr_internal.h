@@ -57,8 +57,9 @@ struct DiscScratch {
 // Enqueue the three discretisation kernels: block statistics, block scan +
 // parameters, level map + compaction of the mask voxel list.  With
 // expect_count >= 0 the scan also checks the mask-voxel count (kJobCount).
-// The list (nvox entries) never overflows: a segment writes its own voxels;
-// null where the levels alone are asked for.
+// The list is null where the levels alone are asked for, and written only
+// where no error is found: with room for expect_count entries (for nvox
+// without an expected count) it does not overflow.
 hipError_t launch_discretise(const void* vol, int dtype, int64_t nvox, const uint8_t* mask,
                              int mode, double value, double lower, uint8_t* levels,
                              int32_t* list, const DiscScratch& s, int64_t expect_count,

@@ -138,3 +138,57 @@ def test_list_order_over_the_segment_scan(B, shape):
     B.fr_map_check()
     ok, rows = parity_report(out.cpu().numpy(), O.spatial_map(case), O.map_names(63))
     assert ok, format_report(rows, only_bad=True)
+
+
+@pytest.mark.parametrize("shape", [(16, 32, 32), (24, 48, 64)])  # one launch, three kernels
+def test_range_error_with_a_small_n_mask_leaves_other_jobs_alone(B, shape):
+    """More than 255 levels and an n_mask below the mask's count: only the
+    first error is reported, and nothing past the n_mask entries of the job's
+    own list is written (a neighbour's list in a batch, a block in a server,
+    the buffers after it in the allocation-free entry point)."""
+    import torch
+    rng = np.random.default_rng(shape[1])
+    vol = rng.integers(0, 3000, size=shape).astype(np.int16)
+    bad = (torch.from_numpy(vol).to("cuda:0"), torch.ones(shape, dtype=torch.uint8, device="cuda:0"), (1.0, 1.0, 1.0),
+           O.FBW, 5.0, float("nan"), 1, 1, 10)
+    case = synth.random_case(41, shape=(12, 13, 14), dtype=np.int16, radius=1, mode=O.FBN, value=12, families=63)
+    v, m = to_dev(case)
+    good = (v, m, case.spacing, case.mode, case.value, case.lower, 1, 63, case.n_mask)
+    ref = B.fr_map(*good)
+    B.fr_map_check()
+    ref = ref.cpu().numpy().view(np.uint32)
+    for f in (B.fr_map, B.fr_map_noalloc):
+        out = torch.full((18, 10), 5.0, device="cuda:0")
+        f(*bad, out)
+        rc, _ = B.fr_map_status()
+        assert rc == B.FR_E_RANGE
+        assert bool((out == 5.0).all())
+        nxt = torch.empty(ref.shape, device="cuda:0")
+        f(*good, nxt)
+        B.fr_map_check()
+        assert np.array_equal(nxt.cpu().numpy().view(np.uint32), ref)
+    keys = ("volume", "mask", "spacing", "mode", "value", "lower", "radius", "families", "n_mask")
+    bt = B.Batch([dict(zip(keys, a)) for a in (good, bad, good, bad, good)])
+    try:
+        bt.launch()
+        rc, st, _ = bt.status()
+        assert rc != B.FR_OK and st == [0, B.FR_E_RANGE, 0, B.FR_E_RANGE, 0]
+        for k in (0, 2, 4):
+            assert np.array_equal(bt.outs[k].cpu().numpy().view(np.uint32), ref)
+    finally:
+        bt.close()
+    srv = B.Server(1 << 28, slots=2)
+    try:
+        tickets = [srv.submit(*a) for a in (good, bad, good, bad, good)]
+        for k, t in enumerate(tickets):
+            if k % 2:
+                srv.wait(t)
+                assert srv.result(t).status == B.FR_E_RANGE
+            else:
+                srv.wait(t)
+                got = srv.maps(t)
+                torch.cuda.synchronize()
+                assert np.array_equal(got.cpu().numpy().view(np.uint32), ref)
+            srv.release(t)
+    finally:
+        srv.close()
