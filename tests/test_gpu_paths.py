@@ -192,3 +192,24 @@ def test_range_error_with_a_small_n_mask_leaves_other_jobs_alone(B, shape):
             srv.release(t)
     finally:
         srv.close()
+
+
+@pytest.mark.parametrize("shape", [(16, 32, 32), (16, 32, 33), (32, 32, 16), (23, 25, 29)])  # 16,384, 16,896, 16,384, 16,675
+@pytest.mark.parametrize("dt", [np.float32, np.int16])
+def test_edge_of_the_one_launch_discretisation(B, shape, dt):
+    import torch
+    rng = np.random.default_rng(shape[2])
+    vol = synth.ct_mixture(rng, shape) if dt == np.int16 else rng.gamma(2.0, 1.5, size=shape).astype(np.float32)
+    mask = (rng.random(shape) < 0.4).astype(np.uint8)
+    mask.reshape(-1)[[0, -1]] = 1
+    case = synth.Case("edge", vol, mask, (1.0, 1.0, 1.0), O.FBN, 14.0, float("nan"), 1, 1)
+    v, m = to_dev(case)
+    lev, ng, xmin, xmax, n = B.fr_discretise(v, m, case.mode, case.value, case.lower)
+    olev, ong, oxmin, oxmax = O.discretise(vol, mask, case.mode, case.value, case.lower)
+    torch.cuda.synchronize()
+    assert (ng, xmin, xmax, n) == (ong, oxmin, oxmax, case.n_mask)
+    assert np.array_equal(lev.cpu().numpy(), olev)
+    out = B.fr_map(v, m, case.spacing, case.mode, case.value, case.lower, 1, 1, case.n_mask)
+    B.fr_map_check()
+    ok, rows = parity_report(out.cpu().numpy(), O.spatial_map(case), O.map_names(1))
+    assert ok, format_report(rows, only_bad=True)
