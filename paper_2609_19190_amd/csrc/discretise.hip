@@ -10,7 +10,7 @@
 //                  raster-ordered list of mask voxels (compact index ->
 //                  linear index), each segment writing at its scanned offset
 //                  (no list where the levels alone are asked for)
-// (one launch, k_disc_small, up to 16,384 voxels).  A segment's loads are
+// (one launch, k_disc_small, up to 32,768 voxels).  A segment's loads are
 // lane-interleaved groups of four voxels, all in flight before the first is
 // used.
 #include <math.h>
@@ -331,14 +331,15 @@ __device__ inline void disc_levels_seg(const T* __restrict__ vol, const uint8_t*
 // The whole discretisation of a small volume in one workgroup: its values
 // stay in registers between the statistics and the levels.  Three launches
 // of a few microseconds each become one (with the maps written directly, a
-// call of 1,537 mask voxels in 8 k: 84 -> 63 us).  One CU's bandwidth costs
-// more than the launches beyond kDiscSmall voxels: one launch and three take
-// 24.2 and 26.9 us at 8 k voxels (fr_discretise, half in the mask), 26.8
-// and 26.9 at 16 k, 29.6 and 27.5 at 24 k, 33.7 and 27.9 at 36 k, 44 and
-// 28 at 65 k; before a radius-1 map of a tenth of the voxels 21.1 and 22.3
-// at 16 k, 27.7 and 24.6 at 36 k.
-constexpr int kSmallThreads = 1024, kSmallGroups = 4;
-constexpr int64_t kDiscSmall = (int64_t)kSmallThreads * kSmallGroups * kGroup;  // 16,384
+// call of 2,145 mask voxels in 24 k: 52.6 -> 35.3 us, of 1,537 in 8 k: 84 ->
+// 63 us).  One CU's bandwidth costs more than the launches beyond
+// kDiscSmall voxels: one launch and three take 23.3 and 26.9 us at 8 k
+// voxels (fr_discretise, half in the mask), 25.9 and 26.9 at 16 k, 28.5 and
+// 27.5 at 24 k, 33.7 and 27.9 at 36 k, 44 and 28 at 65 k.  A small map call
+// gains from fewer launches for longer (2,145 mask voxels in 24 k: 33.8 and
+// 35.4 us; 3,686 in 36 k: 27.7 and 24.6).
+constexpr int kSmallThreads = 1024, kSmallGroups = 8;
+constexpr int64_t kDiscSmall = (int64_t)kSmallThreads * kSmallGroups * kGroup;  // 32,768
 template <typename T>
 __global__ __launch_bounds__(kSmallThreads) void k_disc_small(const T* __restrict__ vol,
                                                               const uint8_t* __restrict__ mask, int64_t n, int mode,
@@ -389,17 +390,18 @@ __global__ __launch_bounds__(kSmallThreads) void k_disc_small(const T* __restric
     if (lane == 63) wcnt[j][w] = before[j] + __popc(in[j]);
   }
   __syncthreads();
-  static_assert(kSmallGroups * W == 64, "a wave count a lane");
+  static_assert(kSmallGroups * W == 128, "two wave counts a lane");
   if (w == 0) {  // exclusive scan of the wave counts, group by group
-    int* c = &wcnt[0][0] + lane;
-    const int sum = *c;
+    int* c = &wcnt[0][0] + 2 * lane;
+    const int c0 = c[0], sum = c0 + c[1];
     int inc = sum;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
       const int y = __shfl_up(inc, o);
       if (lane >= o) inc += y;
     }
-    *c = inc - sum;
+    c[0] = inc - sum;
+    c[1] = inc - sum + c0;
     if (lane == 63) total = inc;
   }
   __syncthreads();

@@ -194,7 +194,7 @@ def test_range_error_with_a_small_n_mask_leaves_other_jobs_alone(B, shape):
         srv.close()
 
 
-@pytest.mark.parametrize("shape", [(16, 32, 32), (16, 32, 33), (32, 32, 16), (23, 25, 29)])  # 16,384, 16,896, 16,384, 16,675
+@pytest.mark.parametrize("shape", [(16, 32, 32), (31, 33, 32), (32, 32, 32), (32, 32, 33), (29, 31, 37)])  # 16,384 .. 33,792
 @pytest.mark.parametrize("dt", [np.float32, np.int16])
 def test_edge_of_the_one_launch_discretisation(B, shape, dt):
     import torch
