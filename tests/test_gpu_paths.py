@@ -213,3 +213,39 @@ def test_edge_of_the_one_launch_discretisation(B, shape, dt):
     B.fr_map_check()
     ok, rows = parity_report(out.cpu().numpy(), O.spatial_map(case), O.map_names(1))
     assert ok, format_report(rows, only_bad=True)
+
+
+@pytest.mark.parametrize("off", [0, 1])
+@pytest.mark.parametrize("dt", [np.float32, np.int16])
+def test_segments_without_a_mask_voxel(B, dt, off):
+    """Empty segments before, between and after those with one mask voxel or
+    more, a partial last one among them: their levels are 0, whatever was in
+    the buffer; the same maps from a batch of such volumes."""
+    import torch
+    shape = (11, 64, 65)  # 12 segments of 4,096, the last of 704
+    rng = np.random.default_rng(off)
+    vol = synth.ct_mixture(rng, shape) if dt == np.int16 else rng.gamma(2.0, 1.5, size=shape).astype(np.float32)
+    for at in ([4096 * 3, 4096 * 3 + 70, 4096 * 7 - 1], [0, 1, 45759], list(range(20000, 20600))):
+        mask = np.zeros(shape, np.uint8)
+        mask.reshape(-1)[at] = 1
+        v, m = shifted(vol, off), shifted(mask, off)
+        levels = shifted(np.full(shape, 77, np.uint8), off)
+        B.fr_discretise(v, m, O.FBN, 9, float("nan"), levels=levels)
+        olev, _, _, _ = O.discretise(vol, mask, O.FBN, 9, float("nan"))
+        torch.cuda.synchronize()
+        assert np.array_equal(levels.cpu().numpy(), olev)
+        case = synth.Case("sparse", vol, mask, (1.0, 1.0, 1.0), O.FBN, 9.0, float("nan"), 1, 63)
+        job = dict(volume=v, mask=m, spacing=case.spacing, mode=case.mode, value=case.value, lower=case.lower, radius=1,
+                   families=63, n_mask=case.n_mask)
+        out = B.fr_map(*job.values())
+        B.fr_map_check()
+        ok, rows = parity_report(out.cpu().numpy(), O.spatial_map(case), O.map_names(63))
+        assert ok, format_report(rows, only_bad=True)
+        bt = B.Batch([job, job])
+        try:
+            bt.launch()
+            assert bt.status()[0] == B.FR_OK
+            for o in bt.outs:
+                assert np.array_equal(o.cpu().numpy().view(np.uint32), out.cpu().numpy().view(np.uint32))
+        finally:
+            bt.close()
