@@ -42,8 +42,6 @@
 namespace fr {
 namespace {
 
-#define FR_INLINE __attribute__((always_inline))
-
 // Runs of two and more voxels that start at one voxel: up to this many are
 // walked one after another.
 constexpr int kRunBits = 6;
@@ -454,57 +452,6 @@ __device__ inline void wsum8i(int (&v)[8]) {
   for (int k = 0; k < 8; ++k) v[k] = __builtin_amdgcn_readlane(c, 8 * k);
 }
 
-// Number of eigenvalues of the symmetric tridiagonal (d, e) inside [-x, x)
-// (Sturm): the sign changes of the leading principal minors
-//   p_0 = 1, p_1 = d_0 - y, p_i = (d_{i-1} - y) p_{i-1} - e_{i-2}^2 p_{i-2}
-// count the eigenvalues below y; the sequences for y = x and y = -x run
-// interleaved, without divisions.  The matrices here have n <= 64 and
-// entries of magnitude below 3, so |p_i| < 6^64 never overflows.  Every
-// minor has kMinorShift added, far below any but a zero one's magnitude, so
-// a zero minor counts as positive: right between two minors of opposite
-// sign, and off by the eigenvalue that equals y otherwise, a probe exactly
-// at a bracket's end.  The signs are shifted into a word as they come (one
-// instruction a minor) and the changes counted at the end: four
-// instructions a minor instead of ten, with the reciprocals and roots of the
-// reflections by one Newton step 2.6 k -> 2.1 k VALU instructions a problem
-// of 17..32 levels (k_mcc of 1 M voxels 5.4 -> 4.5 ms), 1.1 k -> 0.8 k of the
-// radius-2 workload (249 -> 190 us).
-constexpr double kMinorShift = 1e-290;
-__device__ inline uint32_t push_sign(uint32_t acc, double p) {
-  return __builtin_amdgcn_alignbit(acc, (uint32_t)(__double_as_longlong(p) >> 32), 31);
-}
-// D[i] = d_i and E2[i] = e_i^2 are LDS arrays read as broadcasts.
-// SEQ 3: Sturm count of [-x, x) (eigenvalues below x minus those below -x);
-// SEQ 1: eigenvalues below x only; SEQ 2: eigenvalues below -x only.  The
-// counts of 1 and 2 are the two terms of 3, computed the same way.
-template <int SEQ = 3>
-__device__ inline int sturm_span_r(const double* D, const double* E2, int n, double x) {
-  const double d0 = D[0];
-  double ap = d0 - x, am = d0 + x, bp = 1.0, bm = 1.0;
-  uint32_t hp = 0, lp = push_sign(0, ap), hm = 0, lm = push_sign(0, am);
-#pragma unroll 4
-  for (int i = 1; i < n; ++i) {
-    const double di = D[i], e2 = E2[i - 1];
-    if constexpr (SEQ & 1) {
-      const double np = fma(di - x, ap, fma(-e2, bp, kMinorShift));
-      hp = __builtin_amdgcn_alignbit(hp, lp, 31);
-      lp = push_sign(lp, np);
-      bp = ap;
-      ap = np;
-    }
-    if constexpr (SEQ & 2) {
-      const double nm = fma(di + x, am, fma(-e2, bm, kMinorShift));
-      hm = __builtin_amdgcn_alignbit(hm, lm, 31);
-      lm = push_sign(lm, nm);
-      bm = am;
-      am = nm;
-    }
-  }
-  auto changes = [](uint32_t h, uint32_t l) { return __popc(h ^ (h >> 1)) + __popc(l ^ __builtin_amdgcn_alignbit(h, l, 1)); };
-  const int cp = SEQ & 1 ? changes(hp, lp) : 0, cm = SEQ & 2 ? changes(hm, lm) : 0;
-  return SEQ == 3 ? cp - cm : cp + cm;
-}
-
 // ---- MCC of four neighbourhoods at once --------------------------------
 // Row r of 16 lanes holds problem r; lane j of the row is column j.  Values
 // move inside a row by DPP (row broadcast of lane I, row mirrors), so the
@@ -516,13 +463,6 @@ __device__ FR_INLINE inline int opaque_lane() {
   int lane;
   asm volatile("v_mov_b32 %0, %1" : "=v"(lane) : "v"((int)threadIdx.x));
   return lane;
-}
-template <int B, int E, typename F>
-__device__ FR_INLINE inline void static_for(F&& f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>{});
-    static_for<B + 1, E>(f);
-  }
 }
 template <int I>
 __device__ inline double rbc(double v) {  // lane I of this row
@@ -543,37 +483,6 @@ __device__ inline double rmax(double v) {
   b = __double_as_longlong(fmax(__longlong_as_double(b), __longlong_as_double(dpp64<0x141>(b))));
   b = __double_as_longlong(fmax(__longlong_as_double(b), __longlong_as_double(dpp64<0x140>(b))));
   return __longlong_as_double(b);
-}
-
-// Sturm count of [-x, x) for the row's tridiagonal (D[i] = d_i and
-// E2[i] = e_i^2 already broadcast to every lane of the row), N = 16 or 32
-// entries; past a problem's n they hold kPastN and 0, an eigenvalue above
-// every probe, so that no entry needs a test.  SEQ as for sturm_span_r.
-constexpr double kPastN = 2.0;
-template <int N, int SEQ = 3>
-__device__ FR_INLINE inline int sturm_row(const double (&D)[N], const double (&E2)[N], double x) {
-  static_assert(N <= 32, "the signs fit a word");
-  const double d0 = D[0];
-  double ap = d0 - x, am = d0 + x, bp = 1.0, bm = 1.0;
-  uint32_t sp = push_sign(0, ap), sm = push_sign(0, am);
-  static_for<1, N>([&](auto ic) FR_INLINE {
-    constexpr int i = decltype(ic)::value;
-    const double di = D[i], e2 = E2[i - 1];
-    if constexpr (SEQ & 1) {
-      const double np = fma(di - x, ap, fma(-e2, bp, kMinorShift));
-      sp = push_sign(sp, np);
-      bp = ap;
-      ap = np;
-    }
-    if constexpr (SEQ & 2) {
-      const double nm = fma(di + x, am, fma(-e2, bm, kMinorShift));
-      sm = push_sign(sm, nm);
-      bm = am;
-      am = nm;
-    }
-  });
-  const int cp = SEQ & 1 ? __popc(sp ^ (sp >> 1)) : 0, cm = SEQ & 2 ? __popc(sm ^ (sm >> 1)) : 0;
-  return SEQ == 3 ? cp - cm : cp + cm;
 }
 
 // Slot of the stash that row r takes: the r-th set bit of mask (-1: none).

@@ -1,14 +1,143 @@
 // Device helpers shared by the map kernels of this library (the fused
 // fixed-radius kernel and the generic kernel): the 13 GLCM/GLRLM direction
-// representatives, the exact NGTDM scale table and two FP64 primitives.
+// representatives, the exact NGTDM scale table, FP64 primitives and the
+// Sturm counts of the MCC.
 #pragma once
 
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace fr {
 namespace {
+
+#define FR_INLINE __attribute__((always_inline))
+template <int B, int E, typename F>
+__host__ __device__ FR_INLINE inline void static_for(F&& f) {
+  if constexpr (B < E) {
+    f(std::integral_constant<int, B>{});
+    static_for<B + 1, E>(f);
+  }
+}
+
+// ---- Sturm counts of the MCC searches (host code calls them in a test) ----
+// Eigenvalues of the symmetric tridiagonal (d, e) inside [-x, x): the sign
+// changes of the leading principal minors
+//   p_0 = 1, p_1 = d_0 - y, p_i = (d_{i-1} - y) p_{i-1} - e_{i-2}^2 p_{i-2}
+// count the eigenvalues below y; the sequences for y = x and y = -x run
+// interleaved, without divisions.  Every minor has kMinorShift added, so
+// that a zero minor counts as positive: right between two minors of opposite
+// sign, and off by the eigenvalue that equals y otherwise, a probe exactly at
+// a bracket's end.  The range: the spectrum and |y| lie within [-1, 1] but
+// for rounding (an entry past a problem's end, kPastN, within 3 of y), so a
+// step multiplies a minor by at most 3, and, with an m-fold eigenvalue a (m
+// equal rows of a co-occurrence matrix; near a matrix of rank one a = 0), by
+// as little as |a - y|.  The sequences start at kMinorOne and, past
+// kMinorRun minors, go on from there again: a run of them stays between
+// kMinorOne 3^32 = 2^951 and, down to |a - y| = 3e-18, above the shift.
+// (From 1, without a second start, 64 levels lost the sign at |a - y| =
+// 3e-5: MCCs off by that much.)
+// The signs are shifted into a word as they come (one instruction a minor)
+// and the changes counted at the end: four instructions a minor instead of
+// ten, with the reciprocals and roots of the reflections by one Newton step
+// 2.6 k -> 2.1 k VALU instructions a problem of 17..32 levels (k_mcc of 1 M
+// voxels 5.4 -> 4.5 ms), 1.1 k -> 0.8 k of the radius-2 workload (249 -> 190
+// us).
+constexpr double kMinorShift = 1e-290;
+constexpr int kMinorOneExp = 900, kMinorRun = 32;
+constexpr double kMinorOne = 0x1p900;
+// acc with the top bit of h shifted in (one instruction on the GPU, where the
+// general expression becomes two and its registers spill).
+__host__ __device__ inline uint32_t push_bit(uint32_t acc, uint32_t h) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_alignbit(acc, h, 31);
+#else
+  return acc << 1 | h >> 31;
+#endif
+}
+__host__ __device__ inline uint32_t push_sign(uint32_t acc, double p) {
+  return push_bit(acc, (uint32_t)(__builtin_bit_cast(uint64_t, p) >> 32));
+}
+// The last two minors of a sequence, the larger one brought back to kMinorOne.
+__host__ __device__ inline void minors_rescale(double& a, double& b) {
+  int e;
+  (void)frexp(fmax(fabs(a), fabs(b)), &e);
+  a = ldexp(a, kMinorOneExp - e);
+  b = ldexp(b, kMinorOneExp - e);
+}
+// n <= 64; D[i] = d_i and E2[i] = e_i^2 are (LDS) arrays, read as broadcasts.
+// SEQ 3: Sturm count of [-x, x) (eigenvalues below x minus those below -x);
+// SEQ 1: eigenvalues below x only; SEQ 2: eigenvalues below -x only.  The
+// counts of 1 and 2 are the two terms of 3, computed the same way.
+template <int SEQ = 3>
+__host__ __device__ inline int sturm_span_r(const double* D, const double* E2, int n, double x) {
+  const double d0 = D[0];
+  double ap = (d0 - x) * kMinorOne, am = (d0 + x) * kMinorOne, bp = kMinorOne, bm = kMinorOne;
+  uint32_t hp = 0, lp = push_sign(0, ap), hm = 0, lm = push_sign(0, am);
+  auto run = [&](int i0, int i1) FR_INLINE {
+#pragma unroll 4
+    for (int i = i0; i < i1; ++i) {
+      const double di = D[i], e2 = E2[i - 1];
+      if constexpr (SEQ & 1) {
+        const double np = fma(di - x, ap, fma(-e2, bp, kMinorShift));
+        hp = push_bit(hp, lp);
+        lp = push_sign(lp, np);
+        bp = ap;
+        ap = np;
+      }
+      if constexpr (SEQ & 2) {
+        const double nm = fma(di + x, am, fma(-e2, bm, kMinorShift));
+        hm = push_bit(hm, lm);
+        lm = push_sign(lm, nm);
+        bm = am;
+        am = nm;
+      }
+    }
+  };
+  run(1, n < kMinorRun ? n : kMinorRun);
+  if (n > kMinorRun) {
+    if constexpr (SEQ & 1) minors_rescale(ap, bp);
+    if constexpr (SEQ & 2) minors_rescale(am, bm);
+    run(kMinorRun, n);
+  }
+  auto changes = [](uint32_t h, uint32_t l) FR_INLINE {
+    return __builtin_popcount(h ^ (h >> 1)) + __builtin_popcount(l ^ (l >> 1 | h << 31));
+  };
+  const int cp = SEQ & 1 ? changes(hp, lp) : 0, cm = SEQ & 2 ? changes(hm, lm) : 0;
+  return SEQ == 3 ? cp - cm : cp + cm;
+}
+// The same for a row's tridiagonal (D[i] = d_i and E2[i] = e_i^2 already
+// broadcast to every lane of the row), N = 16 or 32 entries; past a
+// problem's n they hold kPastN and 0, an eigenvalue above every probe, so
+// that no entry needs a test.
+constexpr double kPastN = 2.0;
+template <int N, int SEQ = 3>
+__host__ __device__ FR_INLINE inline int sturm_row(const double (&D)[N], const double (&E2)[N], double x) {
+  static_assert(N <= 32 && N <= kMinorRun, "the signs fit a word, the minors their range");
+  const double d0 = D[0];
+  double ap = (d0 - x) * kMinorOne, am = (d0 + x) * kMinorOne, bp = kMinorOne, bm = kMinorOne;
+  uint32_t sp = push_sign(0, ap), sm = push_sign(0, am);
+  static_for<1, N>([&](auto ic) FR_INLINE {
+    constexpr int i = decltype(ic)::value;
+    const double di = D[i], e2 = E2[i - 1];
+    if constexpr (SEQ & 1) {
+      const double np = fma(di - x, ap, fma(-e2, bp, kMinorShift));
+      sp = push_sign(sp, np);
+      bp = ap;
+      ap = np;
+    }
+    if constexpr (SEQ & 2) {
+      const double nm = fma(di + x, am, fma(-e2, bm, kMinorShift));
+      sm = push_sign(sm, nm);
+      bm = am;
+      am = nm;
+    }
+  });
+  const int cp = SEQ & 1 ? __builtin_popcount(sp ^ (sp >> 1)) : 0, cm = SEQ & 2 ? __builtin_popcount(sm ^ (sm >> 1)) : 0;
+  return SEQ == 3 ? cp - cm : cp + cm;
+}
 
 // lcm(1..26) / c for c = 1..26: NGTDM differences |g c - sum| scaled by it
 // are exact integers (s_i * lcm(1..26)).
