@@ -507,7 +507,7 @@ __device__ FR_INLINE inline double multisect_row(double gb, int r, int j, bool f
                                                  double* lo_out) {
   double lo = 0.0, hi = fmin(gb, 1.0) * (1.0 + 1e-12) + 1e-300;
   const double frac = (double)(j + 1) / 17.0;
-  const int rounds = fine ? 8 : 6;
+  const int rounds = fine ? kRowRounds<true> : kRowRounds<false>;
   const double wabs = fine ? 0.0 : 1e-8, wrel = fine ? 2e-9 : 2e-6;
   bool done = false;
 #pragma unroll 1
@@ -872,7 +872,7 @@ __device__ FR_INLINE inline void mcc_wide(const McProblem* slots, unsigned mask,
 // steps in runtime loops over groups of eight (each group's body covers the
 // rows from its first step on; rows <= k get v_i = q_i = 0 and stay
 // unchanged), then 4 rounds of 65-way Sturm multisection on the tridiagonal
-// form (width <= 1 / 65^4), 5 if FINE (1 / 65^5).
+// form (width <= 1 / 65^4), 6 if FINE (1 / 65^6).
 template <typename O, bool FINE, int R, int LMAX, bool MOUT>
 __device__ FR_INLINE inline void mcc_big(Smem<R, LMAX, MOUT>& sm) {
   const int lane = opaque_lane();
@@ -983,7 +983,7 @@ __device__ FR_INLINE inline void mcc_big(Smem<R, LMAX, MOUT>& sm) {
     lo = 0.0;
     hi = hi0;
 #pragma unroll 1
-    for (int round = 0; round < (FINE ? 5 : 4); ++round) {
+    for (int round = 0; round < kBigRounds<FINE>; ++round) {
       const double xr = lo + (hi - lo) * frac;
       const uint64_t bal = __ballot(sturm_span_r<SEQ>(sm.u.b.d, sm.u.b.e2, n, xr) == n);
       if (bal == 0ull) {

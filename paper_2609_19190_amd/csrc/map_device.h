@@ -67,6 +67,13 @@ __host__ __device__ inline void minors_rescale(double& a, double& b) {
   a = ldexp(a, kMinorOneExp - e);
   b = ldexp(b, kMinorOneExp - e);
 }
+// Rounds of the searches: 17-way (16 probes a row) for up to 32 levels, 65-way
+// (a probe a lane) beyond.  FINE (radii 4 and 5 and the extraction variants):
+// no wider a last bracket than the generic kernel's, 1 / 257^4.
+template <bool FINE>
+constexpr int kRowRounds = FINE ? 8 : 6;
+template <bool FINE>
+constexpr int kBigRounds = FINE ? 6 : 4;
 // n <= 64; D[i] = d_i and E2[i] = e_i^2 are (LDS) arrays, read as broadcasts.
 // SEQ 3: Sturm count of [-x, x) (eigenvalues below x minus those below -x);
 // SEQ 1: eigenvalues below x only; SEQ 2: eigenvalues below -x only.  The

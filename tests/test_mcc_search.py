@@ -50,6 +50,9 @@ static double radius_row(const double* d, const double* e2, int n, double gb, in
   return radius(17, rounds, gb, n, [&](double x) { return sturm_row<N, 1>(D, E, x); },
                 [&](double x) { return sturm_row<N, 2>(D, E, x); }, [&](double x) { return sturm_row<N, 3>(D, E, x); });
 }
+extern "C" int rounds(int rows, int fine) {
+  return rows ? (fine ? kRowRounds<true> : kRowRounds<false>) : fine ? kBigRounds<true> : kBigRounds<false>;
+}
 extern "C" double radius_rows(const double* d, const double* e2, int n, double gb, int rounds) {
   return n <= 16 ? radius_row<16>(d, e2, n, gb, rounds) : radius_row<32>(d, e2, n, gb, rounds);
 }
@@ -109,3 +112,17 @@ def test_radius_of_random_tridiagonals(lib, n):
         want = np.abs(np.linalg.eigvalsh(np.diag(d) + np.diag(e, 1) + np.diag(e, -1))).max()
         f, rounds, width = (lib.radius_rows, 6, 17.0 ** -6) if n <= 32 else (lib.radius_span, 4, 65.0 ** -4)
         assert abs(run(f, d, e, rounds) - want) <= 0.5 * width + 1e-13
+
+
+@pytest.mark.parametrize("n", [2, 16, 20, 32, 33, 47, 64])
+def test_finer_searches_err_no_more_than_the_generic_kernels(lib, n):
+    """Radii 4 and 5 and the extraction variants: half of 1 / 257^4, the
+    generic kernel's last bracket."""
+    for seed in range(8):
+        r = np.random.default_rng(1000 * n + seed)
+        d, e = r.uniform(-0.4, 0.4, n), r.uniform(-0.3, 0.3, n - 1)
+        want = np.abs(np.linalg.eigvalsh(np.diag(d) + np.diag(e, 1) + np.diag(e, -1))).max()
+        f, rows = (lib.radius_rows, 1) if n <= 32 else (lib.radius_span, 0)
+        assert abs(run(f, d, e, lib.rounds(rows, 1)) - want) <= 0.5 * 257.0 ** -4 + 1e-13
+        width = 17.0 ** -6 if rows else 65.0 ** -4
+        assert abs(run(f, d, e, lib.rounds(rows, 0)) - want) <= 0.5 * width + 1e-13
