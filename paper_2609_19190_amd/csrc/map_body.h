@@ -697,7 +697,7 @@ __device__ FR_INLINE inline void mcc_narrow(const P* slots, unsigned mask, bool 
     const double a2 = rsum(xi * xi);
     const double x0 = rbc<k + 1>(xi);
     const double alpha = a2 == 0.0 ? 0.0 : -copysign(fsqrt(a2), x0);
-    const double beta = a2 == 0.0 ? 0.0 : frcp(a2 - x0 * alpha);  // 2 / v.v
+    const double beta = a2 == 0.0 ? 0.0 : rcp64(a2 - x0 * alpha);  // 2 / v.v
     const double vi = j == k + 1 ? x0 - alpha : xi;
     // rows in blocks of eight, the finished ones (v_i = q_i = 0) along
     double pp[4] = {0.0, 0.0, 0.0, 0.0};
@@ -798,7 +798,7 @@ __device__ FR_INLINE inline void mcc_wide(const McProblem* slots, unsigned mask,
       const double xB = (jb > k && jb < n) ? ckB : 0.0;
       const double a2 = rsum(xA * xA + xB * xB);
       const double alpha = a2 == 0.0 ? 0.0 : -copysign(fsqrt(a2), x0);
-      const double beta = a2 == 0.0 ? 0.0 : frcp(a2 - x0 * alpha);  // 2 / v.v
+      const double beta = a2 == 0.0 ? 0.0 : rcp64(a2 - x0 * alpha);  // 2 / v.v
       const double vA = j == k + 1 ? x0 - alpha : xA;
       const double vB = jb == k + 1 ? x0 - alpha : xB;
       // rows from K0 on, in blocks of eight behind one uniform branch each
@@ -918,7 +918,7 @@ __device__ FR_INLINE inline void mcc_big(Smem<R, LMAX, MOUT>& sm) {
       const double a2 = wsum(x * x);
       const double x0 = readlane_d(x, k + 1);
       const double alpha = a2 == 0.0 ? 0.0 : -copysign(fsqrt(a2), x0);
-      const double beta = a2 == 0.0 ? 0.0 : frcp(a2 - x0 * alpha);  // 2 / v.v
+      const double beta = a2 == 0.0 ? 0.0 : rcp64(a2 - x0 * alpha);  // 2 / v.v
       const double v = lane == k + 1 ? x0 - alpha : x;
       double vr[4];  // vr[m] = v_{16 m + n} in lane n of every row
       hv[lane] = v;
@@ -1265,7 +1265,7 @@ __device__ inline uint32_t row_total(uint32_t n) {
 template <typename O>
 __device__ inline void emph16(const Emph& a, long long gln, long long rln, double units, double nlogn, O* f) {
   const double N = (double)a.n;
-  const double rN = frcp(N), rN2 = rN * rN;  // one reciprocal; the rest multiply
+  const double rN = rcp64(N), rN2 = rN * rN;  // one reciprocal; the rest multiply
   f[0] = (O)(a.invj2 * rN);
   f[1] = (O)((double)a.sj2 * rN);
   f[2] = (O)((double)gln * rN);
@@ -1472,7 +1472,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
   // 1,000 VALU instructions a voxel at radius 3, this is about 300.)
   const double Kd = (double)K;
   if (fFO) {
-    const double rKd = frcp(Kd);  // one reciprocal; the rest multiply
+    const double rKd = rcp64(Kd);  // one reciprocal; the rest multiply
     float* srt = reinterpret_cast<float*>(sm.u.a.parent);
     const double rank[5] = {(double)(K - 1) * 0.10, (double)(K - 1) * 0.25, (double)(K - 1) * 0.50,
                             (double)(K - 1) * 0.75, (double)(K - 1) * 0.90};
@@ -1607,7 +1607,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     rn = r2[5];
     double rmad = NAN;
     if (rn > 0.0) {
-      const double rrn = frcp(rn), rmu = rs * rrn;
+      const double rrn = rcp64(rn), rmu = rs * rrn;
       double acc = 0.0;
 #pragma unroll
       for (int q = 0; q < NIT; ++q) {
@@ -1806,7 +1806,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     }
     emph_reduce(ed, gln, dn);
     const double N = (double)ed.n;
-    const double rN = frcp(N), rN2 = rN * rN;  // one reciprocal; the rest multiply
+    const double rN = rcp64(N), rN2 = rN * rN;  // one reciprocal; the rest multiply
     if (lane == 0) {
       float* f = sm.early + kNFO;
       f[0] = (float)(ed.invj2 * rN);
@@ -1891,7 +1891,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       const long long Sn1 = ri[4], Sn2 = ri[5];
       const double ssum = rd[0];
       const double Nd = (double)Nvc;
-      const double rNd = frcp(Nd);      // one reciprocal; the rest multiply
+      const double rNd = rcp64(Nd);      // one reciprocal; the rest multiply
       const double psum = rd[1] * rNd;  // sum_i p_i s_i
       const bool any_s = __ballot(anys) != 0ull;
       bden = ri[6];
@@ -1902,7 +1902,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
         // 2 sum_i p_i (Ngp i^2 - 2 i A1 + A2)
         const double c1 = 2.0 * (double)(Nvc * Sn2 - Sn1 * Sn1) * (rNd * rNd);
         const double strn = 2.0 * (double)(Ngp * Sn2 - 2 * A1 * Sn1 + A2 * Nvc) * rNd;
-        f[0] = any_s ? (float)frcp(psum) : 1e6f;
+        f[0] = any_s ? (float)rcp64(psum) : 1e6f;
         f[1] = Ngp <= 1 ? 0.f : (float)(fdiv(c1, (double)(Ngp * (Ngp - 1))) * (ssum * rNd));
         f[2] = bden == 0 ? 0.f : (float)fdiv(rd[1], (double)bden);
         f[3] = (float)(cplx * rNd);
@@ -2423,13 +2423,13 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       pmax = wmaxu(pmax);
       __syncthreads();
       const int ng = a.ng;
-      const double rNd = frcp(Nd), rN2 = rNd * rNd;  // one reciprocal; the rest multiply
+      const double rNd = rcp64(Nd), rN2 = rNd * rNd;  // one reciprocal; the rest multiply
       const double mu = (double)S1x * rNd;
       uint32_t sd1 = 0, sd2 = 0, ss1 = 0;
       std::conditional_t<(R > 3), double, uint32_t> ss2 = 0;
       double dlog = 0, slog = 0, iv = 0, idm = 0, idmn = 0, id = 0, idn = 0, ct = 0, cs = 0, cp = 0;
       const double ngd = (double)ng;
-      const double rng = frcp(ngd), rng2 = rng * rng;
+      const double rng = rcp64(ngd), rng2 = rng * rng;
       for (int k = lane; k < ng; k += 64) {
         const uint32_t c = sm.u.c.pd[k];
         if (c) {

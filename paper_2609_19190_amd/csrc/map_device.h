@@ -201,16 +201,35 @@ __host__ __device__ constexpr int ndx(int n) { return n < 13 ? fdx(n) : -fdx(n -
 __host__ __device__ constexpr int ndy(int n) { return n < 13 ? fdy(n) : -fdy(n - 13); }
 __host__ __device__ constexpr int ndz(int n) { return n < 13 ? fdz(n) : -fdz(n - 13); }
 
-// 1/x from the hardware reciprocal refined by one Newton step (relative
-// error ~1e-16; used where a quotient feeds a sum or a sign test).
+// Reciprocal and root from a seed r (the hardware's: relative errors up to
+// 4.7e-8 and 5.3e-8 measured here, 2^-23 documented), by two Newton steps:
+// correctly rounded but for a hair, a relative error of 2^-53 as 1 / x and
+// sqrt have (one step leaves 2.2e-15 and 4.2e-15, 20 and 38 times as much).
+// x normal and positive for the root.
+__host__ __device__ inline double rcp_refine(double x, double r) {
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+__host__ __device__ inline double sqrt_refine(double x, double r) {
+  double g = x * r, h = 0.5 * r;
+  const double e = fma(-h, g, 0.5);
+  g = fma(g, e, g);
+  h = fma(h, e, h);
+  return fma(fma(-g, g, x), h, g);
+}
+__device__ inline double rcp64(double x) { return rcp_refine(x, __builtin_amdgcn_rcp(x)); }
+__device__ inline double fsqrt(double x) { return sqrt_refine(x, __builtin_amdgcn_rsq(x)); }
+
+// 1/x by one Newton step (relative error up to 2.2e-15): for terms of the
+// sums where every entry takes one, and fdiv.
 __device__ inline double frcp(double x) {
   const double r0 = __builtin_amdgcn_rcp(x);
   return fma(fma(-x, r0, 1.0), r0, r0);
 }
 
 // a / b of normal b != 0 from frcp and one correction of the quotient (the
-// residual is exact in the FMA): six instructions where the division, which
-// scales for the range's ends, takes eleven.  A voxel has some twenty
+// residual is exact in the FMA; 2^-53, as a / b): six instructions where the
+// division, which scales for the range's ends, takes eleven.  A voxel has some twenty
 // quotients and roots; with them so, the positions and triangles from
 // tables (below) and the co-occurrence counts handed to the MCC kernel in
 // the pass that sums them, 5.9 k -> 4.7 k VALU instructions a voxel at
@@ -219,13 +238,6 @@ __device__ inline double frcp(double x) {
 __device__ inline double fdiv(double a, double b) {
   const double r = frcp(b), q = a * r;
   return fma(fma(-b, q, a), r, q);
-}
-
-// sqrt(x) of a positive normal x from the hardware reciprocal square root
-// and one Newton step (relative error ~1e-16).
-__device__ inline double fsqrt(double x) {
-  const double r = __builtin_amdgcn_rsq(x), g = x * r;
-  return fma(g, fma(-0.5 * r, g, 0.5), g);
 }
 
 // log2 of a positive finite normal x, for the entropy terms: x = m 2^e with

@@ -1,6 +1,7 @@
 """The MCC's eigenvalue searches on the CPU: the kernels' own Sturm counts
 (csrc/map_device.h, compiled for the host) in the kernels' brackets, on
-tridiagonals whose spectral radius is known."""
+tridiagonals whose spectral radius is known; and the reciprocals and roots of
+its reflections from seeds as coarse as the hardware's may be."""
 import ctypes
 import os
 import subprocess
@@ -50,6 +51,8 @@ static double radius_row(const double* d, const double* e2, int n, double gb, in
   return radius(17, rounds, gb, n, [&](double x) { return sturm_row<N, 1>(D, E, x); },
                 [&](double x) { return sturm_row<N, 2>(D, E, x); }, [&](double x) { return sturm_row<N, 3>(D, E, x); });
 }
+extern "C" double rcp(double x, double r) { return rcp_refine(x, r); }
+extern "C" double root(double x, double r) { return sqrt_refine(x, r); }
 extern "C" int rounds(int rows, int fine) {
   return rows ? (fine ? kRowRounds<true> : kRowRounds<false>) : fine ? kBigRounds<true> : kBigRounds<false>;
 }
@@ -70,6 +73,9 @@ def lib(tmp_path_factory):
     L = ctypes.CDLL(os.fspath(so))
     for f in (L.radius_span, L.radius_rows):
         f.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int, ctypes.c_double, ctypes.c_int]
+        f.restype = ctypes.c_double
+    for f in (L.rcp, L.root):
+        f.argtypes = [ctypes.c_double, ctypes.c_double]
         f.restype = ctypes.c_double
     return L
 
@@ -126,3 +132,17 @@ def test_finer_searches_err_no_more_than_the_generic_kernels(lib, n):
         assert abs(run(f, d, e, lib.rounds(rows, 1)) - want) <= 0.5 * 257.0 ** -4 + 1e-13
         width = 17.0 ** -6 if rows else 65.0 ** -4
         assert abs(run(f, d, e, lib.rounds(rows, 0)) - want) <= 0.5 * width + 1e-13
+
+
+@pytest.mark.parametrize("seed_error", [0.0, 2.0 ** -23, -2.0 ** -23, 5.3e-8, -5.3e-8, 2.0 ** -30])
+def test_reciprocals_and_roots_are_as_near_as_ieee_ones(lib, seed_error):
+    """One rounding: 2^-53, and what two Newton steps leave of the seed's
+    error (below 2^-88)."""
+    r = np.random.default_rng(3)
+    x = np.concatenate((r.uniform(1.0, 4.0, 3000), np.arange(1.0, 2000.0), 10.0 ** r.uniform(-40, 40, 500)))
+    for v in x:
+        v = np.longdouble(float(v))
+        got = np.longdouble(lib.rcp(float(v), float((1 / v) * (1 + np.longdouble(seed_error)))))
+        assert abs(got * v - 1) <= 2.0 ** -53 * (1 + 1e-3)
+        got = np.longdouble(lib.root(float(v), float((1 / np.sqrt(v)) * (1 + np.longdouble(seed_error)))))
+        assert abs(got / np.sqrt(v) - 1) <= 2.0 ** -53 * (1 + 1e-3)
