@@ -543,10 +543,16 @@ fr_status map_common(const void* volume, int32_t dtype, int32_t nx, int32_t ny, 
   if (needs_generic(kernel_radius, lcap) &&
       (st = pool_gscratch(p, (size_t)fr::kGenericGrid * fr::generic_scratch_bytes(lcap))) != FR_OK)
     return st;
-  if (!debug && default_options(opt) && (st = pool_mcc(p, n_items)) != FR_OK)
-    return st;
+  bool stashed = !debug && default_options(opt);
+  if (stashed && (st = pool_mcc(p, n_items)) != FR_OK) {
+    // no room (1,072 bytes a voxel): radii 4 and 5 have instances that solve
+    // the MCC themselves, and need no more than the maps do
+    if (kernel_radius <= 3) return st;
+    (void)hipGetLastError();
+    stashed = false;
+  }
   const PassBuffers pb = {p->params, p->counts, {p->over[0], p->over[1]}, p->gscratch, fr::kGenericGrid,
-                          debug ? nullptr : p->mcc};
+                          stashed ? p->mcc : nullptr};
   std::pair<hipEvent_t, hipEvent_t> ev;
   if (prof && (st = prof_begin(stream, &ev)) != FR_OK) return st;
   if ((st = enqueue_map_passes(a, dtype, kernel_radius, lcap, debug, pb, stream)) != FR_OK) return st;

@@ -125,3 +125,29 @@ def test_wide_batch_served_and_noalloc_equal_plain(B):
         B.fr_map_noalloc(*a, out)
         B.fr_map_check()
         assert np.array_equal(out.cpu().numpy().view(np.uint32), ref)
+
+
+def test_no_room_for_the_stash(B):
+    """A radius-4 call whose MCC stash (4.4 GB) does not fit beside its other
+    buffers is mapped without it, to the same bits."""
+    import torch
+    shape = (160, 160, 160)
+    torch.manual_seed(4)
+    vol = torch.rand(shape, device="cuda:0")
+    mask = torch.ones(shape, dtype=torch.uint8, device="cuda:0")
+    n = mask.numel()
+    args = (vol, mask, (1.0, 1.0, 1.0), O.FBN, 6, float("nan"), 4, 2, n)
+    out = torch.empty((24, n), device="cuda:0")
+    B.fr_map(*args, out, options=B.map_options(2, 0))  # the other buffers, no stash
+    B.fr_map_check()
+    free, _ = torch.cuda.mem_get_info()
+    print("free", free, flush=True)
+    fill = torch.empty(free - (3 << 30), dtype=torch.uint8, device="cuda:0")
+    B.fr_map(*args, out)
+    B.fr_map_check()
+    without = out[:, ::997].clone()
+    del fill
+    torch.cuda.empty_cache()
+    B.fr_map(*args, out)
+    B.fr_map_check()
+    assert torch.equal(without.view(torch.int32), out[:, ::997].clone().view(torch.int32))
