@@ -263,8 +263,8 @@ __device__ double gmcc(GSmem& sm, const uint32_t* glcm, int L, double* mat, int 
     if (t == k + 1) sm.dv[0] = x;
     __syncthreads();
     const double x0 = sm.dv[0];
-    const double alpha = a2 == 0.0 ? 0.0 : (x0 >= 0.0 ? -sqrt(a2) : sqrt(a2));
-    const double beta = a2 == 0.0 ? 0.0 : 1.0 / (a2 - x0 * alpha);
+    const double alpha = a2 < kNoColumn ? 0.0 : (x0 >= 0.0 ? -sqrt(a2) : sqrt(a2));
+    const double beta = a2 < kNoColumn ? 0.0 : 1.0 / (a2 - x0 * alpha);
     const double v = t == k + 1 ? x0 - alpha : x;
     sm.va[t] = v;  // zero for t <= k and t >= n
     if (t == 0) sm.ve[k] = alpha;

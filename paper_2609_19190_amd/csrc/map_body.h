@@ -696,8 +696,8 @@ __device__ FR_INLINE inline void mcc_narrow(const P* slots, unsigned mask, bool 
     const double xi = (j > k && j < n) ? col[k] : 0.0;
     const double a2 = rsum(xi * xi);
     const double x0 = rbc<k + 1>(xi);
-    const double alpha = a2 == 0.0 ? 0.0 : -copysign(fsqrt(a2), x0);
-    const double beta = a2 == 0.0 ? 0.0 : rcp64(a2 - x0 * alpha);  // 2 / v.v
+    const double alpha = a2 < kNoColumn ? 0.0 : -copysign(fsqrt(a2), x0);
+    const double beta = a2 < kNoColumn ? 0.0 : rcp64(a2 - x0 * alpha);  // 2 / v.v
     const double vi = j == k + 1 ? x0 - alpha : xi;
     // rows in blocks of eight, the finished ones (v_i = q_i = 0) along
     double pp[4] = {0.0, 0.0, 0.0, 0.0};
@@ -797,8 +797,8 @@ __device__ FR_INLINE inline void mcc_wide(const McProblem* slots, unsigned mask,
       const double xA = (j > k && j < n) ? ckA : 0.0;
       const double xB = (jb > k && jb < n) ? ckB : 0.0;
       const double a2 = rsum(xA * xA + xB * xB);
-      const double alpha = a2 == 0.0 ? 0.0 : -copysign(fsqrt(a2), x0);
-      const double beta = a2 == 0.0 ? 0.0 : rcp64(a2 - x0 * alpha);  // 2 / v.v
+      const double alpha = a2 < kNoColumn ? 0.0 : -copysign(fsqrt(a2), x0);
+      const double beta = a2 < kNoColumn ? 0.0 : rcp64(a2 - x0 * alpha);  // 2 / v.v
       const double vA = j == k + 1 ? x0 - alpha : xA;
       const double vB = jb == k + 1 ? x0 - alpha : xB;
       // rows from K0 on, in blocks of eight behind one uniform branch each
@@ -917,8 +917,8 @@ __device__ FR_INLINE inline void mcc_big(Smem<R, LMAX, MOUT>& sm) {
       const double x = lane > k ? ck : 0.0;
       const double a2 = wsum(x * x);
       const double x0 = readlane_d(x, k + 1);
-      const double alpha = a2 == 0.0 ? 0.0 : -copysign(fsqrt(a2), x0);
-      const double beta = a2 == 0.0 ? 0.0 : rcp64(a2 - x0 * alpha);  // 2 / v.v
+      const double alpha = a2 < kNoColumn ? 0.0 : -copysign(fsqrt(a2), x0);
+      const double beta = a2 < kNoColumn ? 0.0 : rcp64(a2 - x0 * alpha);  // 2 / v.v
       const double v = lane == k + 1 ? x0 - alpha : x;
       double vr[4];  // vr[m] = v_{16 m + n} in lane n of every row
       hv[lane] = v;

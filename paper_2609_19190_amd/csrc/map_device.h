@@ -22,6 +22,14 @@ __host__ __device__ FR_INLINE inline void static_for(F&& f) {
   }
 }
 
+// A column with a smaller sum of squares is left as it is by the
+// tridiagonalisation of the MCC's matrix (whose entries are of order 1): that
+// changes no eigenvalue by more than 1e-30.  Levels with equal rows of
+// counts leave a trailing block of nothing but rounding, of one rank itself,
+// so that each reflection leaves 1e-16 of it: after ten of them 2 / v.v
+// overflows, and the infinity spreads over the whole form.
+constexpr double kNoColumn = 1e-60;
+
 // ---- Sturm counts of the MCC searches (host code calls them in a test) ----
 // Eigenvalues of the symmetric tridiagonal (d, e) inside [-x, x): the sign
 // changes of the leading principal minors

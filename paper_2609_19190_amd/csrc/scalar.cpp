@@ -177,7 +177,10 @@ double spectral_radius(std::vector<double> A, int n) {
   for (int k = 0; k + 2 < n; ++k) {
     double s = 0.0;
     for (int i = k + 1; i < n; ++i) s += M(i, k) * M(i, k);
-    if (s == 0.0) {
+    // nothing but rounding (the entries are of order 1): left as it is.  Equal
+    // rows leave a block whose every reflection leaves 1e-16 of it, until
+    // 2 / |v|^2 overflows
+    if (s < 1e-60) {
       b[k] = 0.0;
       continue;
     }
