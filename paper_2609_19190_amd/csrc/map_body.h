@@ -1647,6 +1647,26 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
   // 6.0 k VALU instructions a voxel at radius 3 (16.6 -> 14.9 ms for 1 M
   // voxels), 4.0 k -> 3.7 k at radius 2.
   constexpr int SQ = SM::SQ;
+  // The variants.  A tolerance: the levels that a level depends on are
+  // neighbours of it in the (sorted) list of the present ones, so a
+  // neighbour is tested by its compact level, all of a row at a time.
+  [[maybe_unused]] const bool tolerant = MODE != kPlain && fGLDM && a.opt.gldm_alpha > 0;
+  [[maybe_unused]] uint32_t* range = sm.u.a.parent;  // per level: the first compact level + 1, the last one's << 8
+  if constexpr (MODE != kPlain) {
+    if (tolerant) {
+      const int g = lane < L ? (int)sm.lval[lane] : 0;
+      uint32_t first = 1, last = 0;
+      for (int m = 0; m < L; ++m) {
+        const int d = __builtin_amdgcn_readlane(g, m) - g;
+        first += d < -a.opt.gldm_alpha;
+        last += d <= a.opt.gldm_alpha;
+      }
+      if (lane < L) range[lane] = first | last << 8;
+      __syncthreads();
+    }
+  }
+  // at distance 1 the merged GLCM is the plain one
+  const bool nearest = MODE == kPlain || (MODE == kMerged && a.opt.glcm_dist == 1);
 #pragma unroll 1
   for (int q = 0; q < NIT; ++q) {
     const int c = lane + 64 * q;
@@ -1673,7 +1693,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       const int l = (int)l1 - 1, g = sm.lval[l];
       const int cnt = (int)(wsum & 31u) - 1, lsum = (int)(wsum >> 5) - g;
       sm.u.a.same[c] = same;
-      if (MODE == kPlain && fGLCM) {
+      if (nearest && fGLCM) {
         if constexpr (SM::kFullGlcm) {
           uint32_t* row = &sm.u.a.glcm[(l >> 1) * SM::kRowWords];
           const int shift = (l & 1) << 4;
@@ -1714,12 +1734,15 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       if (fGLDM) {
         int dep = __popc(same);
         if constexpr (MODE != kPlain) {
-          dep = 0;
+          if (tolerant) {
+            // top bit of a byte: not below the first level of the range, not
+            // above the last (bytes of 0 lie below)
+            const uint32_t w = range[l], lo4 = (w & 0xffu) * 0x01010101u, hi4 = (0x7fu - (w >> 8)) * 0x01010101u;
+            auto inside = [&](uint32_t r) FR_INLINE { return ((r | 0x80808080u) - lo4) & ~(r + hi4) & 0x00808080u; };
+            uint32_t in = 0;
 #pragma unroll
-          for (int n = 0; n < 27; ++n) {
-            if (n == 25) continue;  // the voxel itself
-            const int h1 = (int)((rw[n / 3] >> (8 * (n % 3))) & 0xffu);
-            dep += h1 != 0 && abs((int)sm.lval[h1 ? h1 - 1 : 0] - g) <= a.opt.gldm_alpha;
+            for (int r = 0; r < 8; ++r) in = (in >> 1) | inside(rw[r]);
+            dep = __popc(in) + __popc(inside(rw[8]) & 0x00800080u);
           }
         }
         gadd(sm.u.a.gldm, l * (2 * SM::kGldmWords) + dep, 1u);
@@ -1733,34 +1756,58 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
   }
   __syncthreads();
 
-  // GLCM of the variants: the pairs of directions d0..d1 - 1 at the distance
-  // of the options, the neighbour's bounds tested per direction; an entry
-  // off the diagonal is added once, at (min, max)
-  auto count_pairs = [&](int d0, int d1) FR_INLINE {
-    const int dist = a.opt.glcm_dist;
+  // GLCM of the variants.  The neighbour's compact level + 1 (0: none) at
+  // `dist` along a direction, its bounds tested.
+  [[maybe_unused]] auto neighbour = [&](uint32_t pos, int dist, int dx, int dy, int dz) FR_INLINE {
+    const uint32_t ux = (pos & 0xffu) + dist * dx, uy = ((pos >> 8) & 0xffu) + dist * dy, uz = ((pos >> 16) & 0xffu) + dist * dz;
+    const bool in = ux < (uint32_t)S && uy < (uint32_t)S && uz < (uint32_t)S;
+    const uint32_t m1 = sm.cl[in ? (uz * S + uy) * S + ux : 0u];
+    return in ? (int)m1 : 0;
+  };
+  // One direction's pairs (kAveraged); an entry off the diagonal is added
+  // once, at (min, max).
+  [[maybe_unused]] auto count_direction = [&](int d) FR_INLINE {
 #pragma unroll 1
     for (int q = 0; q < NIT; ++q) {
       const int c = lane + 64 * q;
       const int l1 = (c < C) ? sm.cl[c] : 0;
       if (l1) {
-        const int x = c % S, y = (c / S) % S, z = c / (S * S);
-        const int l = l1 - 1;
-#pragma unroll 1
-        for (int d = d0; d < d1; ++d) {
-          const int ux = x + dist * kDir[d][0], uy = y + dist * kDir[d][1], uz = z + dist * kDir[d][2];
-          if (ux < 0 || uy < 0 || uz < 0 || ux >= S || uy >= S || uz >= S) continue;
-          const int m = (int)sm.cl[(uz * S + uy) * S + ux] - 1;
-          if (m < 0) continue;
-          gpair<SM>(sm.u.a.glcm, l, m);
-          atomicAdd(&sm.pxc[l], 1u);
-          atomicAdd(&sm.pxc[m], 1u);
+        const int m1 = neighbour(kPos<R>.v[c], a.opt.glcm_dist, kDir[d][0], kDir[d][1], kDir[d][2]);
+        if (m1) {
+          gpair<SM>(sm.u.a.glcm, l1 - 1, m1 - 1);
+          atomicAdd(&sm.pxc[l1 - 1], 1u);
+          atomicAdd(&sm.pxc[m1 - 1], 1u);
         }
       }
     }
     __syncthreads();
   };
   if constexpr (MODE == kMerged) {
-    if (fGLCM) count_pairs(0, 13);
+    // every direction's pairs, a position's neighbours read together; the
+    // row sums from the table
+    if (fGLCM && !nearest) {
+#pragma unroll 1
+      for (int q = 0; q < NIT; ++q) {
+        const int c = lane + 64 * q;
+        const int l1 = (c < C) ? sm.cl[c] : 0;
+        if (l1) {
+          const uint32_t pos = kPos<R>.v[c];
+          int m1[13];
+#pragma unroll
+          for (int d = 0; d < 13; ++d) m1[d] = neighbour(pos, a.opt.glcm_dist, fdx(d), fdy(d), fdz(d));
+#pragma unroll
+          for (int d = 0; d < 13; ++d)
+            if (m1[d]) gpair<SM>(sm.u.a.glcm, l1 - 1, m1[d] - 1);
+        }
+      }
+      __syncthreads();
+      if (lane < L) {
+        uint32_t sum = 0;
+        for (int m = 0; m < L; ++m) sum += gsym<SM>(sm.u.a.glcm, lane, m);
+        sm.pxc[lane] = sum;
+      }
+      __syncthreads();
+    }
   }
 
   const LevelRow<LMAX> lrow(sm.lval, L, lane);
@@ -2297,7 +2344,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       for (int e = lane; e < SM::glcm_words(L); e += 64) sm.u.a.glcm[e] = 0;
       if (lane < L) sm.pxc[lane] = 0;
       __syncthreads();
-      count_pairs(pass, pass + 1);
+      count_direction(pass);
       if (dbg) dump_glcm();
     }
     __syncthreads();
