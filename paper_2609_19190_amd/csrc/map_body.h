@@ -1571,7 +1571,8 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     double r1[8] = {s1, s2, ent, uni, 0.0, 0.0, 0.0, 0.0};
     wsum8d(r1);
     const double S1 = r1[0], S2 = r1[1];
-    ent = (xlog2x<R>((uint32_t)K) - r1[2]) * rKd;
+    // (no value at all, where every voxel is a NaN that got no level: entropy 0)
+    ent = K ? (xlog2x<R>((uint32_t)K) - r1[2]) * rKd : 0.0;
     uni = r1[3];
     const double mu = S1 * rKd;
     double m2 = 0, m3 = 0, m4 = 0, mad = 0, rs = 0, rn = 0;
@@ -1628,7 +1629,7 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
       f[10] = (float)(mx - mn);
       f[11] = (float)mad;
       f[12] = (float)rmad;
-      f[13] = (float)(S2 > 0.0 && S2 < (double)INFINITY ? fsqrt(S2 * rKd) : S2);
+      f[13] = (float)(S2 > 0.0 && S2 < (double)INFINITY ? fsqrt(S2 * rKd) : S2 * rKd);
       f[14] = flat ? 0.f : (float)fdiv(m3, m2 * fsqrt(m2));  // m2^1.5
       f[15] = flat ? 0.f : (float)(fdiv(m4, m2 * m2) - 3.0);
       f[16] = (float)m2;

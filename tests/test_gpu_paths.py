@@ -249,3 +249,23 @@ def test_segments_without_a_mask_voxel(B, dt, off):
                 assert np.array_equal(o.cpu().numpy().view(np.uint32), out.cpu().numpy().view(np.uint32))
         finally:
             bt.close()
+
+
+@pytest.mark.parametrize("radius", [1, 2, 3])
+def test_neighbourhoods_without_a_value(B, radius):
+    """Fixed bin width gives a NaN no level: where a whole neighbourhood is
+    NaN, the sums are empty and the means undefined."""
+    rng = np.random.default_rng(radius)
+    vol = rng.gamma(2.0, 1.5, size=(16, 17, 18)).astype(np.float32)
+    vol[4:13, 4:13, 4:13] = np.nan
+    mask = np.ones(vol.shape, np.uint8)
+    v, m = to_dev(synth.Case("nan", vol, mask, (1.0, 1.0, 1.0), O.FBW, 1.0, 0.0, radius, 1))
+    out = B.fr_map(v, m, (1.0, 1.0, 1.0), O.FBW, 1.0, 0.0, radius, 1, mask.size)
+    B.fr_map_check()
+    names = O.map_names(1)
+    f = dict(zip(names, out.cpu().numpy().reshape(len(names), *vol.shape)[:, 8, 8, 8]))
+    for k in ("Energy", "TotalEnergy", "Entropy", "Uniformity"):
+        assert f["firstorder_" + k] == 0.0, k
+    for k in ("Mean", "Variance", "MeanAbsoluteDeviation", "RobustMeanAbsoluteDeviation", "RootMeanSquared"):
+        assert np.isnan(f["firstorder_" + k]), k
+    assert f["firstorder_Minimum"] == np.inf
