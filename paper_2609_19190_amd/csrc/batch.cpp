@@ -326,12 +326,10 @@ fr_status enqueue(fr_batch_s* b, hipStream_t st) {
     if (!v.wide) continue;
     int32_t* c = wide_counters(b, v.widx);
     BHIP(fr::launch_map_batch(b->d_jobs, b->d_params, v.d_items, v.n_items, nullptr, 1, v.dtype, v.radius, 32,
-                              v.grid32, v.d_over[0], c + fr::kCntOver0, c + fr::kCntQueue0, nullptr, v.n_vox, nullptr,
-                              st));
+                              v.grid32, v.d_over[0], c + fr::kCntOver0, c + fr::kCntQueue0, v.n_vox, st));
     if (v.lcap <= 32) continue;
     BHIP(fr::launch_map_batch(b->d_jobs, b->d_params, v.d_over[0], 0, c + fr::kCntOver0, 1, v.dtype, v.radius, 64,
-                              v.grid64, v.d_over[1], c + fr::kCntOver1, c + fr::kCntQueue1, nullptr, v.n_vox,
-                              nullptr, st));
+                              v.grid64, v.d_over[1], c + fr::kCntOver1, c + fr::kCntQueue1, v.n_vox, st));
     if (v.lcap <= 64) continue;
     BHIP(fr::launch_map_generic(none, b->d_jobs, b->d_params, v.d_over[1], c + fr::kCntOver1, v.n_vox, v.dtype,
                                 b->d_gscratch, b->lcap_generic, fr::kGenericGrid, st));
@@ -576,8 +574,8 @@ fr_status fr_batch_prepare(fr_batch b, const fr_job* jobs, int32_t n_jobs) {
       free_workspace(b);
       return bfail(FR_E_NOMEM, "overflow-list allocation failed");
     }
-    v.grid32 = b->n_cu * fr::map_batch_blocks_per_cu(v.dtype, v.radius, 32, false);
-    v.grid64 = b->n_cu * fr::map_batch_blocks_per_cu(v.dtype, v.radius, 64, false);
+    v.grid32 = b->n_cu * fr::map_batch_blocks_per_cu(v.dtype, v.radius, 32);
+    v.grid64 = b->n_cu * fr::map_batch_blocks_per_cu(v.dtype, v.radius, 64);
   }
   for (auto& g : b->groups) {
     if (g.variants.empty()) continue;

@@ -169,27 +169,23 @@ hipError_t launch_discretise_batch(const BatchJob* jobs, int32_t n_jobs, const i
 // present levels is appended as (job, voxel) to over, counted in over_count
 // (radius >= 2).  With queue set (zeroed counters of a block), workgroups
 // take items dynamically from its partitions; otherwise (host-made items
-// only) item w goes to workgroup w mod grid.  With mcc set (lmax 32), the
-// MCC problems go to that stash (counter block mcc_count) and launch_mcc
-// must follow.  part_n: positions the lists and the stash are laid out for.
+// only) item w goes to workgroup w mod grid.  The MCC is solved in the
+// kernel.  part_n: positions the lists are laid out for.
 hipError_t launch_map_batch(const BatchJob* jobs, const DiscParams* params, const int2* items,
                             int32_t n_items, const int32_t* items_count, int32_t vpw, int dtype,
                             int radius, int lmax, int grid, int2* over, int32_t* over_count,
-                            int32_t* queue, unsigned char* mcc, int64_t part_n, int32_t* mcc_count,
-                            hipStream_t st);
+                            int32_t* queue, int64_t part_n, hipStream_t st);
 
 // launch_map_batch's kernels of radius 1..3 by raw type and their occupancy.
 hipError_t launch_map_batch_i16(const BatchJob* jobs, const DiscParams* params, const int2* items, int32_t n_items,
                                 const int32_t* items_count, int32_t vpw, int radius, int lmax, int grid, int2* over,
-                                int32_t* over_count, int32_t* queue, unsigned char* mcc, int64_t part_n,
-                                int32_t* mcc_count, hipStream_t st);
-int map_batch_i16_blocks_per_cu(int radius, int lmax, bool stash);
+                                int32_t* over_count, int32_t* queue, int64_t part_n, hipStream_t st);
+int map_batch_i16_blocks_per_cu(int radius, int lmax);
 hipError_t launch_map_batch_f32(const BatchJob* jobs, const DiscParams* params, const int2* items, int32_t n_items,
                                 const int32_t* items_count, int32_t vpw, int radius, int lmax, int grid, int2* over,
-                                int32_t* over_count, int32_t* queue, unsigned char* mcc, int64_t part_n,
-                                int32_t* mcc_count, hipStream_t st);
-int map_batch_f32_blocks_per_cu(int radius, int lmax, bool stash);
-// launch_map_batch's kernels of radius 4 and 5 (no stash) and their occupancy.
+                                int32_t* over_count, int32_t* queue, int64_t part_n, hipStream_t st);
+int map_batch_f32_blocks_per_cu(int radius, int lmax);
+// launch_map_batch's kernels of radius 4 and 5 and their occupancy.
 hipError_t launch_map_batch_wide(const BatchJob* jobs, const DiscParams* params, const int2* items,
                                  int32_t n_items, const int32_t* items_count, int32_t vpw, int radius, int lmax,
                                  int grid, int2* over, int32_t* over_count, int32_t* queue, int64_t part_n,
@@ -229,9 +225,8 @@ constexpr int kGenericGrid = 256;
 hipError_t launch_map_generic(const MapArgs& a, const BatchJob* jobs, const DiscParams* params,
                               const int2* items, const int32_t* items_count, int64_t part_n, int dtype,
                               void* scratch, int lcap, int grid, hipStream_t st);
-// Resident workgroups per CU of a batched map variant (occupancy; stash:
-// the instance that stashes its MCC problems).
-int map_batch_blocks_per_cu(int dtype, int radius, int lmax, bool stash);
+// Resident workgroups per CU of a batched map variant (occupancy).
+int map_batch_blocks_per_cu(int dtype, int radius, int lmax);
 // Batched transpose: items[w] = (job, first compact index of a 64-voxel tile)
 // (items NULL: a single job, tile w starting at voxel 64 w).
 hipError_t launch_transpose_batch(const BatchJob* jobs, const DiscParams* params, const int2* items,

@@ -6,12 +6,11 @@ namespace fr {
 
 hipError_t launch_map_batch_i16(const BatchJob* jobs, const DiscParams* params, const int2* items, int32_t n_items,
                                 const int32_t* items_count, int32_t vpw, int radius, int lmax, int grid, int2* over,
-                                int32_t* over_count, int32_t* queue, unsigned char* mcc, int64_t part_n,
-                                int32_t* mcc_count, hipStream_t st) {
+                                int32_t* over_count, int32_t* queue, int64_t part_n, hipStream_t st) {
   return launch_b_r<int16_t>(jobs, params, items, n_items, items_count, vpw, radius, lmax, grid, over, over_count,
-                           queue, mcc, part_n, mcc_count, st);
+                           queue, part_n, st);
 }
 
-int map_batch_i16_blocks_per_cu(int radius, int lmax, bool stash) { return occ_b_r<int16_t>(radius, lmax, stash); }
+int map_batch_i16_blocks_per_cu(int radius, int lmax) { return occ_b_r<int16_t>(radius, lmax); }
 
 }  // namespace fr

@@ -2793,14 +2793,12 @@ __device__ inline int64_t take_item(int32_t* queue, const int32_t* counts, int64
   return -1;
 }
 
-template <typename T, int R, int LMAX, bool MOUT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kMapWaves<R, LMAX, MOUT>))) void k_map_batch(
+template <typename T, int R, int LMAX>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kMapWaves<R, LMAX, false>))) void k_map_batch(
     const BatchJob* __restrict__ jobs, const DiscParams* __restrict__ params,
     const int2* __restrict__ items, int32_t n_items_host, const int32_t* __restrict__ items_count,
-    int32_t vpw, int2* over, int32_t* over_count, int32_t* queue, unsigned char* mcc,
-    int64_t part_n, int32_t* mcc_count) {
-  static_assert(!MOUT || LMAX == 32, "stash only from the 32-level instance");
-  __shared__ Smem<R, LMAX, MOUT> sm;
+    int32_t vpw, int2* over, int32_t* over_count, int32_t* queue, int64_t part_n) {
+  __shared__ Smem<R, LMAX, false> sm;
   smem_layout(sm);
   int ns = 0, nq = 0;  // deferred MCC problems in sm.ms and sm.mq
   bool big = false;    // a problem with > 32 levels pending
@@ -2855,27 +2853,25 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kMapWaves<R,
       a.over_job = it2.x;
       a.radius = J->radius;
       a.opt = J->opt;
-      a.mcc = mcc;
+      a.mcc = nullptr;
       a.part_n = part_n;
       a.key0 = J->key0;
-      a.mcc_count = mcc_count;
+      a.mcc_count = nullptr;
       m = it2.y;
       m1 = (int64_t)it2.y + vpw;
       if (m1 > J->n_mask) m1 = J->n_mask;
     }
     if (more) {
-      map_voxel<T, R, LMAX, false, MOUT>(sm, a, a.list[m], m, ns, nq, big);
+      map_voxel<T, R, LMAX, false, false>(sm, a, a.list[m], m, ns, nq, big);
       ++m;
     }
-    if constexpr (!MOUT) {
-      const int fs = (ns == kSmallSlots<R, LMAX> || !more) ? ns : 0;
-      const int fq = (nq == kMcSlots<R, LMAX> || !more) ? nq : 0;
-      if (big || fs || fq) {
-        mcc_flush<float, kFineMcc<R, kPlain>>(sm, fs, fq, big);
-        ns -= fs;
-        nq -= fq;
-        big = false;
-      }
+    const int fs = (ns == kSmallSlots<R, LMAX> || !more) ? ns : 0;
+    const int fq = (nq == kMcSlots<R, LMAX> || !more) ? nq : 0;
+    if (big || fs || fq) {
+      mcc_flush<float, kFineMcc<R, kPlain>>(sm, fs, fq, big);
+      ns -= fs;
+      nq -= fq;
+      big = false;
     }
     if (!more) break;
   }
@@ -2884,56 +2880,38 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kMapWaves<R,
 template <typename T, int R, int LMAX>
 hipError_t launch_b(const BatchJob* jobs, const DiscParams* params, const int2* items,
                     int32_t n_items, const int32_t* items_count, int32_t vpw, int grid, int2* over,
-                    int32_t* over_count, int32_t* queue, unsigned char* mcc, int64_t part_n,
-                    int32_t* mcc_count, hipStream_t st) {
-  if constexpr (LMAX == 32) {
-    if (mcc) {
-      hipLaunchKernelGGL((k_map_batch<T, R, 32, true>), dim3((unsigned)grid), dim3(64), 0, st, jobs, params,
-                         items, n_items, items_count, vpw, over, over_count, queue, mcc, part_n, mcc_count);
-      return hipGetLastError();
-    }
-  }
-  hipLaunchKernelGGL((k_map_batch<T, R, LMAX, false>), dim3((unsigned)grid), dim3(64), 0, st, jobs, params,
-                     items, n_items, items_count, vpw, over, over_count, queue, nullptr, part_n,
-                     nullptr);
+                    int32_t* over_count, int32_t* queue, int64_t part_n, hipStream_t st) {
+  hipLaunchKernelGGL((k_map_batch<T, R, LMAX>), dim3((unsigned)grid), dim3(64), 0, st, jobs, params,
+                     items, n_items, items_count, vpw, over, over_count, queue, part_n);
   return hipGetLastError();
 }
 
-template <typename T, int R, int LMAX, bool MOUT>
+template <typename T, int R, int LMAX>
 int occ_b() {
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void*)k_map_batch<T, R, LMAX, MOUT>, 64, 0) !=
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void*)k_map_batch<T, R, LMAX>, 64, 0) !=
       hipSuccess)
     return 1;
   return nb > 0 ? nb : 1;
 }
 
-
 template <typename T>
 hipError_t launch_b_r(const BatchJob* jobs, const DiscParams* params, const int2* items,
                       int32_t n_items, const int32_t* items_count, int32_t vpw, int radius,
                       int lmax, int grid, int2* over, int32_t* over_count, int32_t* queue,
-                      unsigned char* mcc, int64_t part_n, int32_t* mcc_count, hipStream_t st) {
-  if (radius == 1)
-    return launch_b<T, 1, 32>(jobs, params, items, n_items, items_count, vpw, grid, over, over_count,
-                              queue, mcc, part_n, mcc_count, st);
-  if (radius == 2)
-    return lmax <= 32 ? launch_b<T, 2, 32>(jobs, params, items, n_items, items_count, vpw, grid, over,
-                                           over_count, queue, mcc, part_n, mcc_count, st)
-                      : launch_b<T, 2, 64>(jobs, params, items, n_items, items_count, vpw, grid, over,
-                                           over_count, queue, nullptr, part_n, nullptr, st);
-  return lmax <= 32 ? launch_b<T, 3, 32>(jobs, params, items, n_items, items_count, vpw, grid, over,
-                                         over_count, queue, mcc, part_n, mcc_count, st)
-                    : launch_b<T, 3, 64>(jobs, params, items, n_items, items_count, vpw, grid, over,
-                                         over_count, queue, nullptr, part_n, nullptr, st);
+                      int64_t part_n, hipStream_t st) {
+  const bool l32 = lmax <= 32;
+  auto f = radius == 1   ? launch_b<T, 1, 32>
+           : radius == 2 ? (l32 ? launch_b<T, 2, 32> : launch_b<T, 2, 64>)
+                         : (l32 ? launch_b<T, 3, 32> : launch_b<T, 3, 64>);
+  return f(jobs, params, items, n_items, items_count, vpw, grid, over, over_count, queue, part_n, st);
 }
 
 template <typename T>
-int occ_b_r(int radius, int lmax, bool stash) {
-  if (radius == 1) return stash ? occ_b<T, 1, 32, true>() : occ_b<T, 1, 32, false>();
-  if (radius == 2)
-    return lmax > 32 ? occ_b<T, 2, 64, false>() : (stash ? occ_b<T, 2, 32, true>() : occ_b<T, 2, 32, false>());
-  return lmax > 32 ? occ_b<T, 3, 64, false>() : (stash ? occ_b<T, 3, 32, true>() : occ_b<T, 3, 32, false>());
+int occ_b_r(int radius, int lmax) {
+  if (radius == 1) return occ_b<T, 1, 32>();
+  if (radius == 2) return lmax > 32 ? occ_b<T, 2, 64>() : occ_b<T, 2, 32>();
+  return lmax > 32 ? occ_b<T, 3, 64>() : occ_b<T, 3, 32>();
 }
 
 }  // namespace

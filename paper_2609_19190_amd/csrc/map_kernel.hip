@@ -125,21 +125,18 @@ hipError_t launch_map(const MapArgs& a, int dtype, int radius, int lmax, bool de
 hipError_t launch_map_batch(const BatchJob* jobs, const DiscParams* params, const int2* items,
                             int32_t n_items, const int32_t* items_count, int32_t vpw, int dtype,
                             int radius, int lmax, int grid, int2* over, int32_t* over_count,
-                            int32_t* queue, unsigned char* mcc, int64_t part_n, int32_t* mcc_count,
-                            hipStream_t st) {
+                            int32_t* queue, int64_t part_n, hipStream_t st) {
   if (n_items <= 0 && !items_count) return hipSuccess;
-  if (radius > 3)  // no stashing instances: the problems are solved in the kernel
+  if (radius > 3)
     return launch_map_batch_wide(jobs, params, items, n_items, items_count, vpw, radius, lmax, grid, over,
                                  over_count, queue, part_n, st);
   auto f = dtype == 1 ? launch_map_batch_i16 : launch_map_batch_f32;
-  return f(jobs, params, items, n_items, items_count, vpw, radius, lmax, grid, over, over_count, queue, mcc,
-           part_n, mcc_count, st);
+  return f(jobs, params, items, n_items, items_count, vpw, radius, lmax, grid, over, over_count, queue, part_n, st);
 }
 
-int map_batch_blocks_per_cu(int dtype, int radius, int lmax, bool stash) {
+int map_batch_blocks_per_cu(int dtype, int radius, int lmax) {
   if (radius > 3) return map_batch_wide_blocks_per_cu(radius, lmax);
-  return dtype == 1 ? map_batch_i16_blocks_per_cu(radius, lmax, stash)
-                    : map_batch_f32_blocks_per_cu(radius, lmax, stash);
+  return dtype == 1 ? map_batch_i16_blocks_per_cu(radius, lmax) : map_batch_f32_blocks_per_cu(radius, lmax);
 }
 
 }  // namespace fr

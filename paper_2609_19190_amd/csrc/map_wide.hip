@@ -17,29 +17,20 @@ hipError_t launch_w(const MapArgs& a, bool debug, hipStream_t st) {
                          : launch_i<AnyRaw, R, LMAX, true, false>(a, st);
 }
 
-template <int R, int LMAX>
-hipError_t launch_wb(const BatchJob* jobs, const DiscParams* params, const int2* items, int32_t n_items,
-                     const int32_t* items_count, int32_t vpw, int grid, int2* over, int32_t* over_count,
-                     int32_t* queue, int64_t part_n, hipStream_t st) {
-  hipLaunchKernelGGL((k_map_batch<AnyRaw, R, LMAX, false>), dim3((unsigned)grid), dim3(64), 0, st, jobs, params,
-                     items, n_items, items_count, vpw, over, over_count, queue, nullptr, part_n, nullptr);
-  return hipGetLastError();
-}
-
 }  // namespace
 
 hipError_t launch_map_batch_wide(const BatchJob* jobs, const DiscParams* params, const int2* items,
                                  int32_t n_items, const int32_t* items_count, int32_t vpw, int radius, int lmax,
                                  int grid, int2* over, int32_t* over_count, int32_t* queue, int64_t part_n,
                                  hipStream_t st) {
-  auto f = radius == 4 ? (lmax <= 32 ? launch_wb<4, 32> : launch_wb<4, 64>)
-                       : (lmax <= 32 ? launch_wb<5, 32> : launch_wb<5, 64>);
+  auto f = radius == 4 ? (lmax <= 32 ? launch_b<AnyRaw, 4, 32> : launch_b<AnyRaw, 4, 64>)
+                       : (lmax <= 32 ? launch_b<AnyRaw, 5, 32> : launch_b<AnyRaw, 5, 64>);
   return f(jobs, params, items, n_items, items_count, vpw, grid, over, over_count, queue, part_n, st);
 }
 
 int map_batch_wide_blocks_per_cu(int radius, int lmax) {
-  if (radius == 4) return lmax <= 32 ? occ_b<AnyRaw, 4, 32, false>() : occ_b<AnyRaw, 4, 64, false>();
-  return lmax <= 32 ? occ_b<AnyRaw, 5, 32, false>() : occ_b<AnyRaw, 5, 64, false>();
+  if (radius == 4) return lmax <= 32 ? occ_b<AnyRaw, 4, 32>() : occ_b<AnyRaw, 4, 64>();
+  return lmax <= 32 ? occ_b<AnyRaw, 5, 32>() : occ_b<AnyRaw, 5, 64>();
 }
 
 hipError_t launch_map_wide(const MapArgs& a, int radius, int lmax, bool debug, hipStream_t st) {

@@ -356,17 +356,15 @@ hipError_t launch_job(fr_server_s* s, SJob& J, Slot& sl) {
     // MCC kernel would take every CU for its short run and stall the jobs
     // beside it (measured: served throughput fell below the plain path's).
     if ((e = fr::launch_map_batch(djob, dpar, nullptr, n_items, nullptr, vpw, B.dtype, B.radius, klmax,
-                                  n_items, over0, sl.counts + fr::kCntOver0, nullptr, nullptr, B.n_mask, nullptr,
-                                  sl.st)) != hipSuccess)
+                                  n_items, over0, sl.counts + fr::kCntOver0, nullptr, B.n_mask, sl.st)) != hipSuccess)
       return e;
     if (B.radius >= 2 && klmax == 32 && B.lcap > 32) {
-      const int grid64 = s->n_cu * fr::map_batch_blocks_per_cu(B.dtype, B.radius, 64, false);
+      const int grid64 = s->n_cu * fr::map_batch_blocks_per_cu(B.dtype, B.radius, 64);
       // a persistent grid over a list known only on the device: a work queue,
       // so jobs running beside it do not leave it a long tail
       if ((e = fr::launch_map_batch(djob, dpar, over0, 0, sl.counts + fr::kCntOver0, 1, B.dtype, B.radius, 64,
-                                    grid64, over1, sl.counts + fr::kCntOver1, sl.counts + fr::kCntQueue1, nullptr,
-                                    B.n_mask, nullptr,
-                                    sl.st)) != hipSuccess)
+                                    grid64, over1, sl.counts + fr::kCntOver1, sl.counts + fr::kCntQueue1,
+                                    B.n_mask, sl.st)) != hipSuccess)
         return e;
     }
     if (needs_generic(B)) {
