@@ -1868,8 +1868,10 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
     // 30,000 voxels of a uniform image at radius 3 take 197 us, 228 before;
     // of blocks 198 and 214; of 60,000 of noise in 32 levels 262 and 290.)
     uint32_t col = 0;
-    if ((lane & 15) < 14)
+    if ((lane & 15) < 14) {
+#pragma unroll 4
       for (int l = lane >> 4; l < L; l += 4) col += sm.u.a.gldm[l * SM::kGldmWords + (lane & 15)];
+    }
     col = (uint32_t)fold16i((int)col, (int)col);
     col = (uint32_t)fold32i((int)col, (int)col);
     long long gln = 0, dn = 0;
