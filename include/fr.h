@@ -356,10 +356,12 @@ fr_status fr_batch_destroy(fr_batch b);
  * levels per neighbourhood, from Ng and the cube size) a table of work
  * items (job, first voxel).  Allocates the batch's device workspace: level
  * volumes (1 B/voxel), mask-voxel lists (4 B/mask voxel), staging rows
- * (384 B/mask voxel), two overflow lists per variant (8 B/mask voxel each),
- * segment and item tables, and generic-kernel scratch when a job may hold
- * more than 64 levels.  Synchronous (uploads the
- * tables); replaces any previous plan and graph, so work enqueued by an
+ * (384 B/mask voxel), for radii 1..3 an MCC stash (1,072 B/mask voxel) and
+ * two overflow lists per raw type present (8 B/mask voxel of these radii
+ * each), two per raw type and radius above 3 (of its jobs), segment and item
+ * tables, and generic-kernel scratch when a job may hold more than 64
+ * levels.  Synchronous (uploads the tables); replaces any previous plan and
+ * graph, so work enqueued by an
  * earlier fr_batch_launch of this batch must have completed.  The jobs
  * array is copied.
  * Errors: FR_E_ARG, FR_E_RANGE, FR_E_CAPACITY (with the job index in

@@ -509,7 +509,7 @@ __device__ FR_INLINE inline double multisect_row(double gb, int r, int j, bool f
   for (int round = 0; round < rounds; ++round) {
     // a row stops refining once its bracket is below 1e-8 + 2e-6 lo (the
     // midpoint then errs by under 5e-9 + 1e-6 of the value, far inside
-    // the parity bound; fine: 2e-9 lo, an error of 1e-9 of the value) or
+    // the parity bound; fine: 2e-9 lo, below seven rounds' 1 / 17^7) or
     // after the last round; so its result depends on its own problem only.
     // The wave stops when every row has.
     done = done || (hi - lo) <= wabs + wrel * lo;
@@ -1953,8 +1953,9 @@ __device__ __attribute__((always_inline)) inline void map_voxel(Smem<R, LMAX, MO
         }
       }
     }
-    // every integer total is below 2^31: |V| <= 343, at most 64 present
-    // levels of value <= 255 (sum n_i i^2 <= 2.3e7, bden <= 1.2e7)
+    // every integer total is below 2^31: |V| <= 1,331, at most 64 present
+    // levels of value <= 255 (sum n_i i^2 <= 8.7e7, bden <= 2 (L - 1) sum
+    // n_i i <= 4.3e7)
     int ri[8] = {(int)sum_n, (int)pres, (int)pj, (int)pj2, (int)sum_ni, (int)sum_ni2, (int)bden, 0};
     wsum8i(ri);
     double rd[8] = {s_i, ps_acc, cplx, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -2707,9 +2708,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kMapWaves<R,
 // each (a sweep over 4..48 on the PET workload put the optimum there) and
 // at most 8 waves.  Fewer voxels than resident workgroups get one each
 // where the MCC problems leave the kernel (or are solved with their voxel):
-// a call of 1,537 voxels at radius 2 took 186 us with four each, 109 us with
-// one; of 2,176 at radius 1, 84 and 76 us.  An instance that flushes its deferred problems itself keeps four
-// voxels per workgroup (minv 4), which fill the rows of its flushes.
+// with the other stages as they were then, a call of 1,537 voxels at radius 2
+// took 186 us with four each, 109 us with one (61 now); of 2,176 at radius 1,
+// 84 and 76 (34 now).  An instance that flushes its deferred problems itself
+// keeps four voxels per workgroup (minv 4), which fill the rows of its
+// flushes.
 inline int64_t plain_blocks(int64_t n, int64_t resident, int64_t minv) {
   if (resident < 1) resident = 1;
   int64_t per = (n + resident * 8 - 1) / (resident * 8);

@@ -49,10 +49,10 @@ constexpr double kNoColumn = 1e-60;
 // 3e-5: MCCs off by that much.)
 // The signs are shifted into a word as they come (one instruction a minor)
 // and the changes counted at the end: four instructions a minor instead of
-// ten, with the reciprocals and roots of the reflections by one Newton step
-// 2.6 k -> 2.1 k VALU instructions a problem of 17..32 levels (k_mcc of 1 M
-// voxels 5.4 -> 4.5 ms), 1.1 k -> 0.8 k of the radius-2 workload (249 -> 190
-// us).
+// ten.  With the reflections' reciprocals and roots by Newton steps 2.6 k ->
+// 2.1 k VALU instructions a problem of 17..32 levels (k_mcc of 1 M voxels 5.4
+// -> 4.5 ms; 2.0 k and 4.3 now), 1.1 k -> 0.8 k of the radius-2 workload (249
+// -> 190 us).
 constexpr double kMinorShift = 1e-290;
 constexpr int kMinorOneExp = 900, kMinorRun = 32;
 constexpr double kMinorOne = 0x1p900;

@@ -1,10 +1,12 @@
 // Map kernels of radius 4 and 5: the fused per-voxel body of the smaller
 // radii with larger tables (one instance for both raw types).  One wavefront
-// per voxel, 32 or 64 present levels, MCC problems of at most 32 levels in
-// the stash; LDS (17 to 36 KB a workgroup) sets the occupancy, VALU issue
-// the rate, as at the smaller radii.  A PET VOI of 6,007 voxels, radius 4,
-// Ng 32, 93 maps: 8.28 ms on the generic kernel (one 256-thread workgroup a
-// voxel, tables in global memory), 0.44 ms here.
+// per voxel, 32 or 64 present levels; MCC problems of at most 32 levels in
+// the stash for plain calls with room for it, solved in the kernel
+// otherwise and for batched and served jobs.  LDS (16 to 35 KB a workgroup)
+// and registers (two waves a SIMD) set the occupancy, VALU issue the rate, as
+// at the smaller radii.  A PET VOI of 6,007 voxels, radius 4, Ng 32, 93 maps:
+// 8.28 ms on the generic kernel (one 256-thread workgroup a voxel, tables in
+// global memory), 0.44 ms here when it came in, 0.25 now.
 #include "map_body.h"
 
 namespace fr {

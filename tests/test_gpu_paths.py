@@ -1,5 +1,5 @@
 """GPU parity where a call's route changes with its size, alignment or data:
-the one-launch discretisation (up to 65,536 voxels) and the three kernels
+the one-launch discretisation (up to 32,768 voxels) and the three kernels
 beyond, whole and partial groups of four voxels, pointers off the vector
 alignment; maps written directly (up to 4,096 voxels) and through staging
 rows; the allocation-free entry point with and without room for the MCC

@@ -1,6 +1,6 @@
 """The committed rocprofv3 summaries under profiles/ describe the committed
-map kernel: their kernel-source hash is that of csrc/map_kernel.hip, and the
-benchmark can read its traffic and VALU-issue figures from them (no GPU)."""
+map kernel: their kernel-source hash is that of csrc/map_body.h, map_device.h
+and map_kernel.hip, and the benchmark can read its traffic and VALU-issue figures from them (no GPU)."""
 import os
 import sys
 
