@@ -26,6 +26,9 @@ fr_status fail(fr_status code, const char* fmt, ...) {
   vsnprintf(buf, sizeof buf, fmt, ap);
   va_end(ap);
   g_err = buf;
+  // an allocation that failed stays the thread's last HIP error, which the
+  // next call's launch would report as its own
+  if (code == FR_E_NOMEM) (void)hipGetLastError();
   return code;
 }
 
@@ -80,12 +83,14 @@ fr_status pool_get(int64_t nvox, Pool** out) {
     p.counts = nullptr;
     return fail(FR_E_NOMEM, "hipMalloc of the pass counters failed");
   }
-  if (!p.params) {
-    if (hipMalloc((void**)&p.params, sizeof(fr::DiscParams)) != hipSuccess)
-      return fail(FR_E_NOMEM, "hipMalloc of the parameter block failed");
-    if (hipHostMalloc((void**)&p.host_params, sizeof(fr::DiscParams), hipHostMallocDefault) !=
-        hipSuccess)
-      return fail(FR_E_NOMEM, "hipHostMalloc of the parameter block failed");
+  if (!p.params && hipMalloc((void**)&p.params, sizeof(fr::DiscParams)) != hipSuccess) {
+    p.params = nullptr;
+    return fail(FR_E_NOMEM, "hipMalloc of the parameter block failed");
+  }
+  if (!p.host_params &&
+      hipHostMalloc((void**)&p.host_params, sizeof(fr::DiscParams), hipHostMallocDefault) != hipSuccess) {
+    p.host_params = nullptr;
+    return fail(FR_E_NOMEM, "hipHostMalloc of the parameter block failed");
   }
   if (nvox > p.cap_vox) {
     pool_drain();
@@ -106,6 +111,9 @@ fr_status pool_get(int64_t nvox, Pool** out) {
     (void)hipFree(p.block_offset);
     (void)hipFree(p.block_min);
     (void)hipFree(p.block_max);
+    p.block_count = nullptr;
+    p.block_offset = nullptr;
+    p.block_min = p.block_max = nullptr;
     p.cap_blocks = 0;
     if (hipMalloc((void**)&p.block_count, nb * sizeof(int32_t)) != hipSuccess ||
         hipMalloc((void**)&p.block_offset, nb * sizeof(int64_t)) != hipSuccess ||
@@ -550,7 +558,6 @@ fr_status map_common(const void* volume, int32_t dtype, int32_t nx, int32_t ny, 
     // no room (1,072 bytes a voxel): radii 4 and 5 have instances that solve
     // the MCC themselves, and need no more than the maps do
     if (kernel_radius <= 3) return st;
-    (void)hipGetLastError();
     stashed = false;
   }
   const PassBuffers pb = {p->params, p->counts, {p->over[0], p->over[1]}, p->gscratch, fr::kGenericGrid,

@@ -51,6 +51,8 @@ fr_status bfail(fr_status code, const char* fmt, ...) {
   vsnprintf(buf, sizeof buf, fmt, ap);
   va_end(ap);
   fr::set_error(buf);
+  // (else the next launch of the thread would report the failed allocation)
+  if (code == FR_E_NOMEM) (void)hipGetLastError();
   return code;
 }
 

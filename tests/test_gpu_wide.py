@@ -151,3 +151,27 @@ def test_no_room_for_the_stash(B):
     B.fr_map(*args, out)
     B.fr_map_check()
     assert torch.equal(without.view(torch.int32), out[:, ::997].clone().view(torch.int32))
+
+
+def test_a_call_after_one_without_room(B):
+    """A call refused for want of memory leaves nothing behind: the next one
+    that fits is mapped."""
+    import torch
+    small = make(2, 16, (9, 9, 9), np.float32, ALL)
+    v, m = to_dev(small)
+    args = (v, m, small.spacing, small.mode, small.value, small.lower, 2, ALL, small.n_mask)
+    ref = B.fr_map(*args)
+    B.fr_map_check()
+    vol = torch.zeros((200, 200, 200), device="cuda:0")  # staging rows of 3.1 GB, a stash of 8.6 GB
+    mask = torch.ones(vol.shape, dtype=torch.uint8, device="cuda:0")
+    out = torch.empty((18, mask.numel()), device="cuda:0")
+    free, _ = torch.cuda.mem_get_info()
+    fill = torch.empty(free - (3 << 30), dtype=torch.uint8, device="cuda:0")
+    with pytest.raises(B.FrError) as ei:
+        B.fr_map(vol, mask, (1.0, 1.0, 1.0), O.FBN, 8, float("nan"), 1, 1, mask.numel(), out)
+    assert ei.value.code == B.FR_E_NOMEM
+    got = B.fr_map(*args)
+    B.fr_map_check()
+    del fill
+    torch.cuda.empty_cache()
+    assert torch.equal(got.view(torch.int32), ref.view(torch.int32))
